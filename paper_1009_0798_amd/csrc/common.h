@@ -68,6 +68,11 @@ struct AmrLevelDev {
     double *inv_h = nullptr;   // [nprob] 1 / h
     int *dense_map = nullptr;  // level 0 only: [nb] cell offset of the block's 4^3 coarse
                                // cells inside the problem's first dense level (-1 level)
+    // level 0 only: block at each position of the problems' boxes (x fastest,
+    // problem after problem) and the column segments of the marching kernels
+    int *bmap = nullptr;
+    int nmarch = 0;
+    int *march = nullptr;
     // refluxing: coarse cells of this level with faces next to covered cells
     int nrf = 0;
     int *rf = nullptr;         // [nrf][RF_INTS]
@@ -228,6 +233,10 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
                             const double *coef_dev, T *out, const int *active, hipStream_t s,
                             const T *coarse = nullptr, long long ccs = 0, const T *Bg = nullptr, long long gcs = 0,
                             const T *etag = nullptr, double *out64 = nullptr);
+
+template <typename T, typename TO>
+ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
+                              const double *coef_dev, TO *out, const int *active, hipStream_t s);
 
 template <typename T>
 ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *S,

@@ -718,6 +718,9 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
                 k_blk_sweep<T, 2, true><<<L.nb, SWEEP_THREADS, 0, s>>>(
                     L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs,
                     coarse, ccs, nullptr, 0, nullptr, out64);
+            } else if (level == 0 && L.nmarch > 0 &&
+                       ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0) {
+                return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s);
             } else {
                 k_blk_sweep<T, 0, true><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev,
                                                                        B, cs, S, eta, out, nullptr, nullptr, nullptr,
@@ -758,6 +761,8 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
         k_blk_sweep<T, 2><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta,
                                                          out, L.ijk, h->dense[1].probs, coarse, ccs, nullptr, 0,
                                                          nullptr);
+    } else if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
+        return launch_march_sweep<T, T>(h, B, cs, S, eta, coef_dev, out, active, s);
     } else if (B) {
         // FP64 tiles go straight from global memory into LDS (16-byte pairs)
         k_blk_sweep<T, 0, false, std::is_same<T, double>::value><<<L.nb, SWEEP_THREADS, 0, s>>>(

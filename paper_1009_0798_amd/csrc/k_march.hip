@@ -1,0 +1,347 @@
+// Plane-marching fused red-black sweep (eq. 19) of the base level.
+//
+// A workgroup takes a column segment of 16 x 16 cells and marches along z.  At
+// step q plane q of B and eta, with a halo of two cells, goes to LDS, the red
+// cells of plane q - 1 and the black cells of plane q - 2 are updated, and
+// plane q - 2 is written: the operations of the sweep per 8^3 block (sweep.h)
+// on the same values, hence the same bits.  A cell's neighbours above and
+// below are its own thread's registers, the others come from rings of planes
+// in LDS, kept by colour so that consecutive lanes read consecutive elements.
+//
+// What bounds it: on large levels HBM, on the smallest it takes the issue of
+// the wavefronts that update both colours (a step is about 300 vector
+// instructions and 60 LDS reads of theirs, 1.1 us in FP64).  Against the sweep
+// per block it loads 1.56 instead of 3.4 cells per cell (plus four planes per
+// segment) and asks the L2 for 2.5 instead of 6.7 lines per line, and its
+// loads run two planes ahead instead of in front of each block's updates.
+// Measured per launch on one box, us, sweep per block -> this kernel: FP64
+// 128^3 56 -> 44, 160x128x192 119 -> 83, 256^3 515 -> 324 (2.6 -> 4.1 TB/s of
+// algorithmic bytes); FP32 35 -> 29, 56 -> 42, 287 -> 193.
+#include "march.h"
+#include "stencil.h"
+#include "sweep.h"
+
+namespace ohm {
+
+namespace {
+
+// B (3 components) and eta of a pair of x-neighbours on one plane, and S on
+// the plane before
+template <typename T>
+struct Stage {
+    Pair<T> b[3], e, s[3];
+};
+
+// a value every lane holds, kept in scalar registers
+__device__ __forceinline__ float uniform(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)b),
+                   hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
+// waits for this wave's LDS accesses only: global loads stay in flight
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Two consecutive results at a byte offset; an offset past the array (lanes
+// without a result) is dropped by the buffer's bounds check, so the store
+// stays outside any branch and the loads in flight are counted exactly.
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, unsigned off, Pair<double> v)
+{
+    typedef unsigned __attribute__((ext_vector_type(4))) u4;
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, off, 0, 0);
+}
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, unsigned off, Pair<float> v)
+{
+    typedef unsigned __attribute__((ext_vector_type(2))) u2;
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, 0, 0);
+}
+
+// LDS rings of planes, plane q in slot (q - first plane) mod 4 (mod 2 for the
+// updated red cells): red and black cells before the sweep, red cells after
+// it, resistivity at the red and at the black cells
+constexpr int RB = MNP;                               // elements per ring row (one component of one plane)
+constexpr int O_ER = 0, O_EK = O_ER + 4 * RB, O_R1 = O_EK + 4 * RB, O_R0 = O_R1 + 2 * 3 * RB, O_K0 = O_R0 + 4 * 3 * RB,
+              N_ZERO = O_R0, N_FULL = O_K0 + 4 * 3 * RB;
+
+// hardware placement of a wavefront: bits 0-3 its slot on the SIMD, 4-5 the SIMD
+constexpr int HWREG_PLACE = 4 | (5 << 11);
+
+// Wavefronts of a group: two update the tile's 128 pairs of x-neighbours (a
+// pair holds one red and one black cell on every plane), one the red cells of
+// the first halo layer that face the tile, one only loads the rest of the halo
+enum { ROLE_INNER = 0, ROLE_RING = 1, ROLE_LOAD = 2 };
+
+template <typename T, typename TO, int ROLE, bool ZERO>
+__device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__restrict__ B, long long cs,
+                                           const T *__restrict__ S, const T *__restrict__ eta, TO *__restrict__ out,
+                                           unsigned obytes, T cih2, int x, int y, int z0, int n, bool in)
+{
+    constexpr bool RED = ROLE != ROLE_LOAD, BLACK = ROLE == ROLE_INNER;
+    const T c8 = uniform(cih2 * T(0.125)), c2 = uniform(cih2 * T(0.5));
+    const int u = (x + 2) / 2 + MHW * (y + 2);
+    const T *B0 = B, *B1 = ZERO ? B : B + cs, *B2 = ZERO ? B : B + 2 * cs;
+    const T *S0 = S, *S1 = S + cs, *S2 = S + 2 * cs;
+    const __amdgpu_buffer_rsrc_t O0 = __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)obytes, 0x00027000),
+                                 O1 = __builtin_amdgcn_make_buffer_rsrc(out + cs, 0, (int)obytes, 0x00027000),
+                                 O2 = __builtin_amdgcn_make_buffer_rsrc(out + 2 * cs, 0, (int)obytes, 0x00027000);
+
+    Stage<T> st[2];
+    // block of the pair on plane P
+    auto block = [&](int P) {
+        int v = u;
+        asm volatile("" : "+v"(v));   // formed when needed, once in 8 planes: not held in registers
+        const int ry = v / MHW, hx = v - ry * MHW;
+        return (unsigned)ids[((hx + 3) >> 2) + 4 * ((ry + 6) >> 3) + 16 * (((P - z0) >> 3) + 1)];
+    };
+    // byte offset of the pair on plane P, given the one on plane P - 1
+    auto offset = [&](int P, unsigned before) -> unsigned {
+        constexpr unsigned PLANE = 64 * (unsigned)sizeof(T);
+        return (P & 7) == 0 ? block(P) * 8u * PLANE + before % PLANE : before + PLANE;
+    };
+    auto issue = [&](Stage<T> &v, unsigned off, unsigned offs) {
+        if (!ZERO) {
+            v.b[0] = load_pair(B0, off);
+            v.b[1] = load_pair(B1, off);
+            v.b[2] = load_pair(B2, off);
+        }
+        v.e = load_pair(eta, off);
+        if (RED) {
+            v.s[0] = load_pair(S0, offs);
+            v.s[1] = load_pair(S1, offs);
+            v.s[2] = load_pair(S2, offs);
+        }
+    };
+    const int zs = z0 - 2, zend = z0 + n + 2;                   // planes zs .. zend - 1
+    const unsigned o_p0 = (block(zs) * (unsigned)NC + (unsigned)((x & 7) + 8 * (y & 7) + 64 * (zs & 7))) * (unsigned)sizeof(T),
+                   o_p1 = offset(zs + 1, o_p0);
+    // (as in the loop, each plane's loads are followed by three stores, here
+    // dropped ones: the waits count the accesses behind the plane they need)
+    const Pair<TO> none = {TO(0), TO(0)};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        issue(st[h], h ? o_p1 : o_p0, o_p0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (BLACK) {
+            store_pair(O0, 0xFFFFFFF0u, none);
+            store_pair(O1, 0xFFFFFFF0u, none);
+            store_pair(O2, 0xFFFFFFF0u, none);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // register history of this thread's column, by plane mod 4 (a pair holds
+    // one red and one black cell on every plane): values before the sweep,
+    // resistivity, red values after it, S of the black cell, offset, and what
+    // a plane's red (black) cells contribute to the planes around it
+    T k[4][3], er[4], nw[4][3], sk[4][3];
+    unsigned off[4] = {o_p0, o_p1, 0u, 0u};
+    PlaneEdges<T> xk[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        er[h] = T(0);
+        xk[h] = PlaneEdges<T>{T(0), T(0), T(0), T(0), T(0), T(0)};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) k[h][c] = nw[h][c] = sk[h][c] = T(0);
+    }
+    int q0 = zs;
+    do {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const int q = q0 + h;
+            constexpr int m = 3;
+            const int h1 = (h + 3) & m, h2 = (h + 2) & m, h3 = (h + 1) & m;   // planes q - 1, q - 2, q - 3
+            const bool par = ((y + h) & 1) != 0;                // red is the pair's second cell on plane q (zs is even)
+            // plane q (and S of plane q - 1) arrive
+            Stage<T> &v = st[h & 1];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if (ZERO) continue;
+                sh[O_R0 + (h * 3 + c) * RB + u] = par ? v.b[c].b : v.b[c].a;
+                k[h][c] = par ? v.b[c].a : v.b[c].b;
+                sh[O_K0 + (h * 3 + c) * RB + u] = k[h][c];
+            }
+            const T ek0 = par ? v.e.a : v.e.b;
+            sh[O_ER + h * RB + u] = par ? v.e.b : v.e.a;
+            sh[O_EK + h * RB + u] = ek0;
+            T sr[3];
+            if (RED) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {                   // plane q - 1 has the other parity
+                    sr[c] = par ? v.s[c].a : v.s[c].b;
+                    sk[h1][c] = par ? v.s[c].b : v.s[c].a;
+                }
+            }
+            const unsigned o_m2 = off[h2];
+            off[h2] = q + 2 < zend ? offset(q + 2, off[h3]) : off[h3];   // plane q + 2
+            issue(v, off[h2], off[h3]);                         // ... and S of q + 1
+            lds_barrier();
+            // x-neighbours: of the red cell at q - 1 and of the black cell at
+            // q - 2 alike, the same-row (and row +-1, plane +-1) partner on
+            // the right at pair ix, on the left at ix - 1
+            const int ix = u + (par ? 0 : 1);
+            er[h1] = sh[O_ER + h1 * RB + u];
+            const T ek2 = sh[O_EK + h2 * RB + u];
+            if (RED) {
+                const T *E0 = sh + O_EK + h1 * RB;
+                if (ZERO) {
+                    // S over the diagonal
+                    Nbr<T> nb;
+                    nb.e0 = er[h1], nb.e_zp = ek0, nb.e_zm = ek2;
+                    nb.e_xp = E0[ix], nb.e_xm = E0[ix - 1], nb.e_yp = E0[u + MHW], nb.e_ym = E0[u - MHW];
+                    T al[3];
+                    alpha_core(nb, al);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) nw[h1][c] = relax_div(sr[c], fma(c2, al[c], T(1)));
+                } else {
+                    const T *R = sh + O_R0 + h1 * 3 * RB;
+                    const T r0[3] = {R[u], R[RB + u], R[2 * RB + u]};
+                    Nbr<T> nb;
+                    nb.x0 = r0[0], nb.y0 = r0[1], nb.z0 = r0[2], nb.e0 = er[h1];
+                    nb.e_zp = ek0, nb.e_zm = ek2;
+                    nb.x_zp = k[h][0], nb.x_zm = k[h2][0], nb.y_zp = k[h][1], nb.y_zm = k[h2][1];
+                    fill_faces<T, MHW, RB>(nb, sh + O_K0 + h1 * 3 * RB, E0, u, ix);
+                    fill_corners<T, MHW, RB>(nb, R, u, ix);
+                    nb.p = plane_edges<T, MHW, RB>(sh + O_R0 + h * 3 * RB, u, ix);
+                    nb.m = plane_edges<T, MHW, RB>(sh + O_R0 + h2 * 3 * RB, u, ix);
+                    T dv[3], al[3];
+                    divF_core(nb, dv, al);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) nw[h1][c] = relax_point(r0[c], sr[c], dv[c], al[c], c8, c2);
+                }
+            }
+            if (BLACK) {
+                Nbr<T> nb;
+                nb.x0 = k[h2][0], nb.y0 = k[h2][1], nb.z0 = k[h2][2], nb.e0 = ek2;
+                nb.e_zp = er[h1], nb.e_zm = er[h3];
+                nb.x_zp = nw[h1][0], nb.x_zm = nw[h3][0], nb.y_zp = nw[h1][1], nb.y_zm = nw[h3][1];
+                fill_faces<T, MHW, RB>(nb, sh + O_R1 + (h & 1) * 3 * RB, sh + O_ER + h2 * RB, u, ix);
+                if (ZERO) {
+                    nb.x_xpyp = nb.x_xpym = nb.x_xmyp = nb.x_xmym = T(0);
+                    nb.y_xpyp = nb.y_xpym = nb.y_xmyp = nb.y_xmym = T(0);
+                } else {
+                    fill_corners<T, MHW, RB>(nb, sh + O_K0 + h2 * 3 * RB, u, ix);
+                    xk[h1] = plane_edges<T, MHW, RB>(sh + O_K0 + h1 * 3 * RB, u, ix);
+                }
+                nb.p = xk[h1], nb.m = xk[h3];
+                T dv[3], al[3];
+                divF_core(nb, dv, al);
+                // plane q - 2 (its offset is in the slot that q + 2 takes)
+                const unsigned oo = in && q - 2 >= z0 ? o_m2 / (unsigned)sizeof(T) * (unsigned)sizeof(TO) : 0xFFFFFFF0u;
+                Pair<TO> o[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const T kv = relax_point(k[h2][c], sk[h2][c], dv[c], al[c], c8, c2);
+                    o[c].a = TO(par ? kv : nw[h2][c]);         // plane q - 2 has plane q's parity
+                    o[c].b = TO(par ? nw[h2][c] : kv);
+                }
+                store_pair(O0, oo, o[0]);
+                store_pair(O1, oo, o[1]);
+                store_pair(O2, oo, o[2]);
+            }
+            // (after the black update's reads, which may then be issued early)
+            if (RED) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sh[O_R1 + ((h1 & 1) * 3 + c) * RB + u] = nw[h1][c];
+            }
+        }
+        q0 += 4;
+    } while (q0 < zend);
+}
+
+template <typename T, typename TO, bool ZERO>
+__global__ void __launch_bounds__(MARCH_THREADS, 2)
+k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
+              const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+              const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
+              TO *__restrict__ out, unsigned obytes)
+{
+    __shared__ T sh[ZERO ? N_ZERO : N_FULL];
+    __shared__ int place[MARCH_THREADS / 64];
+    __shared__ int ids[16 * (MARCH_MAX_NBZ + 2)];
+    const int w = blockIdx.x, q8 = ntile / NXCD, r8 = ntile % NXCD, xc = w % NXCD;
+    const MarchTile &M = tiles[xc * q8 + min(xc, r8) + w / NXCD];
+    const int pr = M.prob;
+    if (active && !active[pr]) return;
+    const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
+    const int nbx = M.nx, nby = M.ny, nbz = M.nz;
+    const int ex = min(MT, 8 * (nbx - M.bx)), ey = min(MT, 8 * (nby - M.by));   // cells of the tile inside the box
+    const int z0 = 8 * M.bz, n = 8 * M.nbz;
+    // block at each position along the segment (one layer more on each side)
+    // of the 4 x 4 columns the tile and its halo touch
+    for (int t = threadIdx.x; t < 16 * (M.nbz + 2); t += MARCH_THREADS) {
+        int i = M.bx - 1 + (t & 3), j = M.by - 1 + ((t >> 2) & 3), k = M.bz - 1 + (t >> 4);
+        i = i < 0 ? i + nbx : i % nbx;
+        j = j < 0 ? j + nby : j % nby;
+        k = k < 0 ? k + nbz : k % nbz;
+        ids[t] = bmap[M.map + i + nbx * (j + nby * k)];
+    }
+    if ((threadIdx.x & 63) == 0) place[threadIdx.x >> 6] = __builtin_amdgcn_s_getreg(HWREG_PLACE);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    // the two inner wavefronts go to SIMDs 0 and 2 in a compute unit's first
+    // group and to 1 and 3 in its second, so that they do not share one
+    const int first = place[0], mine = place[threadIdx.x >> 6] >> 4;
+    const bool spread = ((1 << (first >> 4)) | (1 << (place[1] >> 4)) | (1 << (place[2] >> 4)) |
+                         (1 << (place[3] >> 4))) == 15;
+    const int simd = (spread ? mine : (int)(threadIdx.x >> 6)) ^ (first & 1), role = (simd >> 1) | ((simd & 1) << 1);
+    if (__builtin_amdgcn_readfirstlane(role) < 2) {
+        // wavefronts of 8 rows of 8 pairs: the rows r, r + 4, r + 8 and r + 12
+        // of 32 consecutive lanes start 8 elements apart modulo 32, so that
+        // reads of a plane meet no bank twice (rows 0 to 7 and 8 to 15
+        // instead: FP32 sweep of 128^3 34.9 instead of 29.2 us)
+        const int r = 2 * role + (lane >> 5) + 4 * ((lane >> 3) & 3), x = 2 * (lane & 7);
+        march_loop<T, TO, ROLE_INNER, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, min(x, ex - 2), min(r, ey - 1), z0, n,
+                                      x < ex && r < ey);
+    } else if (__builtin_amdgcn_readfirstlane(role) == 2) {
+        // red cells of the first halo layer that face the tile
+        const int l = min(lane, 47);
+        const int x = l < 16 ? min(2 * (l & 7), ex - 2) : (l < 32 ? -2 : ex),
+                  y = l < 16 ? (l < 8 ? -1 : ey) : min(l & 15, ey - 1);
+        march_loop<T, TO, ROLE_RING, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false);
+    } else {
+        // the rest of the halo: rows -2 and ey + 1, the corners of rows -1 and ey
+        const int l = min(lane, 23);
+        const int x = l < 20 ? min(2 * (l % 10) - 2, ex) : ((l & 1) ? ex : -2),
+                  y = l < 20 ? (l < 10 ? -2 : ey + 1) : (l < 22 ? -1 : ey);
+        march_loop<T, TO, ROLE_LOAD, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false);
+    }
+}
+
+}  // namespace
+
+template <typename T, typename TO>
+ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
+                              const double *coef_dev, TO *out, const int *active, hipStream_t s)
+{
+    const AmrLevelDev &L = h->amr[0];
+    const unsigned obytes = (unsigned)((unsigned long long)L.nb * NC * sizeof(TO));   // (the callers allow 4 GiB)
+    const MarchTile *tiles = (const MarchTile *)L.march;
+    if (B)
+        k_march_sweep<T, TO, false><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
+                                                                       coef_dev, B, cs, S, eta, out, obytes);
+    else
+        k_march_sweep<T, TO, true><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
+                                                                      coef_dev, B, cs, S, eta, out, obytes);
+    return check_launch("marching sweep");
+}
+template ohm_status launch_march_sweep<double, double>(const ohm_hier *, const double *, long long, const double *,
+                                                       const double *, const double *, double *, const int *,
+                                                       hipStream_t);
+template ohm_status launch_march_sweep<float, float>(const ohm_hier *, const float *, long long, const float *,
+                                                     const float *, const double *, float *, const int *,
+                                                     hipStream_t);
+template ohm_status launch_march_sweep<float, double>(const ohm_hier *, const float *, long long, const float *,
+                                                      const float *, const double *, double *, const int *,
+                                                      hipStream_t);
+
+}  // namespace ohm
