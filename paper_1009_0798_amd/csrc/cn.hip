@@ -30,7 +30,7 @@ struct Plan {
     size_t rhs, e, tmp, res, mg_g, eta_t, eta_tg;
     size_t d_rhs[16], d_e[16], d_tmp[16], d_res[16], d_eta[16], d_eta64[16];
     size_t inv, aug, jobs, force, part, dots, scal, ranges, mlprob, active, cmask, coefs;
-    size_t ring, tol2;          // norms of queued BiCGStab iterations, convergence thresholds
+    size_t tol2;                // convergence thresholds
     size_t hold;                // set on the device when a norm is non-finite: no copy out
     size_t rf;                  // FMG over AMR levels: right-hand side restricted under finer blocks
     size_t inv_elems = 0, aug_elems = 0;
@@ -90,7 +90,6 @@ Plan make_plan(const ohm_hier *h, const ohm_cn_opts *o)
     P.part = take(8 * (size_t)P.NBt * 8);
     P.dots = take(8 * (size_t)h->nprob * 8);
     P.scal = take(8 * (size_t)h->nprob * scal_stride());
-    P.ring = take(8 * (size_t)h->nprob * 2 * ITER_SLOTS);
     P.tol2 = take(8 * (size_t)h->nprob);
     // tables the host builds each step, contiguous from jobs to coefs (one
     // staged upload): coarse jobs and force flags per depth, block ranges
@@ -184,17 +183,19 @@ struct Solver {
         return launch_reduce_problem(h->nprob, nlev(), at<long long>(P.ranges), at<double>(P.part), k, ksum, out, st);
     }
 
-    ohm_status dots(const double *const *x, const double *const *y, int nq, int stage = -1, double *copy = nullptr)
+    // host: pinned memory that also receives the sums
+    ohm_status dots(const double *const *x, const double *const *y, int nq, int stage = -1, double *copy = nullptr,
+                    double *host = nullptr)
     {
         OHM_TRY(vdot((int)P.NBt, mlprob, active, VN, x, y, nq, at<double>(P.part), st, copy));
-        return reduce_scal(nq, stage);
+        return reduce_scal(nq, stage, host);
     }
     // per-problem sums of the nq partials into dots, then BiCGStab scalar
     // update `stage` (< 0: none), one launch
-    ohm_status reduce_scal(int nq, int stage)
+    ohm_status reduce_scal(int nq, int stage, double *host = nullptr)
     {
         return launch_reduce_scal(h->nprob, nlev(), at<long long>(P.ranges), at<double>(P.part), nq,
-                                  at<double>(P.dots), stage, active, at<double>(P.scal), st);
+                                  at<double>(P.dots), stage, active, at<double>(P.scal), st, IterRing(), host);
     }
 
     // y = L x (lam dt) followed by the per-problem dots (xs[q], ys[q]), where
@@ -629,7 +630,7 @@ struct Solver {
             OHM_TRY(ensure_coarse_storage(h));
         }
         act_dev = ones;
-        mlprob = at<int>(P.mlprob);
+        mlprob = np == 1 ? nullptr : at<int>(P.mlprob);
         active_mut = at<int>(P.active);
         active = active_mut;
         lam_dt = at<double>(P.coefs);
@@ -658,7 +659,7 @@ struct Solver {
     // device part of the start of a step: the staged tables, coarse-fine
     // ghosts of eta (FP64) and FP32 copies, dense-level resistivity, coarsest
     // inverses, S = b - (1 - lambda) dt div F(b), and (multigrid) the initial
-    // residual with |r|^2 and |S|^2 copied to the pinned buffer, the stop
+    // residual with |r|^2 and |S|^2 written to the pinned buffer, the stop
     // rule's thresholds and, for BiCGStab, the first restart
     ohm_status start_device(bool multigrid)
     {
@@ -701,10 +702,9 @@ struct Solver {
         // the first restart (rhat = r, its scalars from (r, r))
         const double *xs[2] = {at<double>(P.r), at<double>(P.S)};
         if (o->outer == 1)
-            OHM_TRY(dots(xs, xs, 2, 0, at<double>(P.rhat)));
+            OHM_TRY(dots(xs, xs, 2, 0, at<double>(P.rhat), h->h_dots));
         else
-            OHM_TRY(dots(xs, xs, 2));
-        OHM_TRY(copy_dots(2));
+            OHM_TRY(dots(xs, xs, 2, -1, nullptr, h->h_dots));
         // thresholds of the stop rule; problems the initial guess already
         // satisfies leave the active set before any iteration is queued
         return launch_conv_init(h->nprob, at<double>(P.dots), o->rtol, at<double>(P.tol2), active_mut, at<int>(P.hold),
@@ -727,10 +727,9 @@ struct Solver {
         active = nullptr;
         ohm_status s = composite(P.x, into, MODE_RESID, lam_dt, neg_lam_dt, P.S);
         const double *xs[1] = {at<double>(into)};
-        if (s == OHM_OK) s = dots(xs, xs, 1);
+        if (s == OHM_OK) s = dots(xs, xs, 1, -1, nullptr, h->h_dots + 2 * (size_t)h->nprob);
         active = keep;
-        OHM_TRY(s);
-        return copy_dots(1, 2 * (size_t)h->nprob);
+        return s;
     }
 
     // device flags as last uploaded (setup uploads all ones)
@@ -770,34 +769,19 @@ struct Solver {
             OHM_TRY(vbicg_xr((int)P.NBt, mlprob, active, VN, at<double>(P.scal), at<double>(P.x),
                              at<double>(P.ph), at<double>(P.sh), at<double>(P.s), at<double>(P.t),
                              at<double>(P.r), at<double>(P.rhat), at<double>(P.part), st));
-            // (r, r) and (rhat, r) into the iteration ring, which goes to
-            // the pinned buffer whole (one copy node)
+            // (r, r) and (rhat, r) into the iteration ring in pinned memory
             IterRing ring;
-            ring.buf = at<double>(P.ring);
+            ring.buf = h_ring();
             ring.flags = active_mut;
             ring.tol2 = at<double>(P.tol2);
             ring.hold = at<int>(P.hold);
-            OHM_TRY(launch_reduce_scal(h->nprob, nlev(), at<long long>(P.ranges), at<double>(P.part), 2,
-                                       at<double>(P.dots), 4, active, at<double>(P.scal), st, ring));
-            OHM_HIP(hipMemcpyAsync(h_ring(), at<double>(P.ring), sizeof(double) * 2 * ITER_SLOTS * h->nprob,
-                                   hipMemcpyDeviceToHost, st));
-            return OHM_OK;
+            return launch_reduce_scal(h->nprob, nlev(), at<long long>(P.ranges), at<double>(P.part), 2,
+                                      at<double>(P.dots), 4, active, at<double>(P.scal), st, ring);
     }
     // pinned regions after the first 8 nprob values: the iteration ring, then
     // the final norms of a step
     double *h_ring() const { return h->h_dots + 8 * (size_t)h->nprob; }
     double *h_final() const { return h->h_dots + (8 + 2 * ITER_SLOTS) * (size_t)h->nprob; }
-    // the first nq * nprob norms to the handle's pinned host buffer (part of a
-    // captured iteration: one node, no separate copy command); read after a
-    // synchronisation of the stream
-    // (at element `at_host` of the pinned buffer)
-    ohm_status copy_dots(int nq, size_t at_host = 0)
-    {
-        OHM_HIP(hipMemcpyAsync(h->h_dots + at_host, at<double>(P.dots), sizeof(double) * nq * h->nprob,
-                               hipMemcpyDeviceToHost, st));
-        return OHM_OK;
-    }
-
     // one iteration of eqs. (16)-(18): B += M(R); R = S - L B; |R|^2 per problem
     ohm_status ir_iter()
     {
@@ -805,8 +789,7 @@ struct Solver {
         OHM_TRY(vaxpy1((int)P.NBt, mlprob, active, VN, at<double>(P.x), at<double>(P.ph), st));
         OHM_TRY(composite(P.x, P.r, MODE_RESID, lam_dt, neg_lam_dt, P.S));
         const double *xs[1] = {at<double>(P.r)};
-        OHM_TRY(dots(xs, xs, 1));
-        return copy_dots(1);
+        return dots(xs, xs, 1, -1, nullptr, h->h_dots);
     }
 
     // the norms an iteration copied to the pinned buffer (stride nq)
@@ -912,10 +895,9 @@ struct Solver {
     // queued again.
     ohm_status finish_async(size_t res)
     {
-        const int np = h->nprob, L = nlev();
+        const int L = nlev();
         OHM_TRY(vnorms((int)P.NBt, mlprob, nullptr, VN, at<double>(res), at<double>(P.part), st));
-        OHM_TRY(reduce(6, 3, at<double>(P.dots)));
-        OHM_HIP(hipMemcpyAsync(h_final(), at<double>(P.dots), sizeof(double) * 6 * np, hipMemcpyDeviceToHost, st));
+        OHM_TRY(reduce(6, 3, h_final()));
         for (int l = L - 1; l >= 1; --l)
             OHM_TRY(launch_restrict_blk<double>(h, l, vec(P.x, l), VN, vec(P.x, l - 1), VN, 3, nullptr, st));
         for (int l = 0; l < L; ++l)

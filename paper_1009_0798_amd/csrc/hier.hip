@@ -597,6 +597,7 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
         OHM_TRY(upload(&D.ptiles, pt));
         OHM_TRY(upload(&D.ptiles_all, pt_all));
         OHM_TRY(upload(&D.probs, dp));
+        D.one = dp[0];
     }
     // ---- scratch ---------------------------------------------------------------
     std::lock_guard<std::mutex> lock(capture_mutex());

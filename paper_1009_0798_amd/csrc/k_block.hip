@@ -24,6 +24,16 @@ __device__ __forceinline__ int xcd_block(int w, int n)
     return x * q + min(x, r) + i;
 }
 
+// The loads in front of a block's fields -- its problem, that problem's active
+// flag, its neighbours -- are what a small launch waits for, one after the
+// other: a handle of one problem passes no problem table, and the neighbour
+// entries are requested before the flag is known.
+__device__ __forceinline__ int problem_of(const int *prob_of, int b) { return prob_of ? prob_of[b] : 0; }
+__device__ __forceinline__ int load_nbr(const int *nbr_tab, int b)
+{
+    return threadIdx.x < 27 ? nbr_tab[27 * (long long)b + threadIdx.x] : 0;
+}
+
 __device__ __forceinline__ int side(int c) { return c < 0 ? -1 : (c >= NB ? 1 : 0); }
 
 // B (3 components) and eta of block b plus the one-cell halo into LDS: thread
@@ -88,12 +98,13 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
     __shared__ int snbr[27];
     __shared__ double sred[6][4];
     const int b = xcd_block(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int mine = load_nbr(nbr_tab, b);
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) {
         if (MODE == MODE_APPLY && threadIdx.x < dots.ndot) dots.dot_part[(long long)b * dots.ndot + threadIdx.x] = 0.0;
         return;
     }
-    if (threadIdx.x < 27) snbr[threadIdx.x] = nbr_tab[27 * (long long)b + threadIdx.x];
+    if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
     __syncthreads();
     load_tile_b_eta<T>(sB, sE[0], B, Bg, cs, gcs, eta, etag, snbr);
     // values read per cell after the stencil (S, or the other vector of the
@@ -292,9 +303,10 @@ k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ p
     __shared__ T sC[MODE == 2 ? 3 * 512 : 1];
     __shared__ int snbr[27];
     const int b = xcd_block(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int mine = load_nbr(nbr_tab, b);
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
-    if (threadIdx.x < 27) snbr[threadIdx.x] = nbr_tab[27 * (long long)b + threadIdx.x];
+    if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
     __syncthreads();
     const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
     if constexpr (DIRECT) {
@@ -334,7 +346,7 @@ k_restrict_blk(int nfine, const int *__restrict__ parent, const int *__restrict_
                long long fcs, T *__restrict__ coarse, long long ccs, int ncomp)
 {
     const int b = xcd_block(blockIdx.x, nfine);
-    if (active && !active[fprob[b]]) return;
+    if (active && !active[problem_of(fprob, b)]) return;
     const int t = threadIdx.x;          // 4^3 coarse cells of the octant
     const int i = t & 3, j = (t >> 2) & 3, k = t >> 4;
     const int o = octant[b];
@@ -361,7 +373,7 @@ k_restrict_blk0_dense(int nblk, const int *__restrict__ dense_map, const int *__
                       int ncomp)
 {
     const int b = xcd_block(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
     const int t = threadIdx.x;
     const int i = t & 3, j = (t >> 2) & 3, k = t >> 4;
@@ -395,7 +407,7 @@ k_prolong_blk(int nfine, const int *__restrict__ parent, const int *__restrict__
     __shared__ T sc[3][216];
     __shared__ int snbr[27];
     const int b = xcd_block(blockIdx.x, nfine);
-    if (active && !active[fprob[b]]) return;
+    if (active && !active[problem_of(fprob, b)]) return;
     const int pb = parent[b];
     const int o = octant[b];
     const int ox = 4 * (o & 1), oy = 4 * ((o >> 1) & 1), oz = 4 * (o >> 2);
@@ -438,7 +450,7 @@ k_prolong_dense_blk0(int nblk, const int *__restrict__ ijk, const int *__restric
     // 4^3 parents and one layer around them, periodic) are staged in LDS
     __shared__ T sc[3][216];
     const int b = xcd_block(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
     const DenseProbDev q = dp[pr];
     const int bi = ijk[3 * b], bj = ijk[3 * b + 1], bk = ijk[3 * b + 2];
@@ -670,7 +682,7 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
     if (dots.ndot < 0 || dots.ndot > 2 || (dots.ndot > 0 && (mode != MODE_APPLY || !dots.dot_part)))
         return fail(OHM_ERR_ARG, "fused dot products need MODE_APPLY, 1 or 2 products and a partials buffer");
     dim3 grid(L.nb), blk(256);
-#define ARGS L.nb, L.nbr, L.prob, cov_zero, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, out, colour, \
+#define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, out, colour, \
              partials, dots, nullptr, nullptr, 0
     switch (mode) {
     case MODE_APPLY: k_blk_stencil<T, MODE_APPLY><<<grid, blk, 0, s>>>(ARGS); break;
@@ -691,7 +703,7 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     if (L.nb == 0) return OHM_OK;
     if (h->min_level > -1) return fail(OHM_ERR_ARG, "no dense level below level 0");
     k_blk_stencil<T, MODE_RESID_RESTRICT><<<L.nb, 256, 0, s>>>(
-        L.nb, L.nbr, L.prob, nullptr, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
+        L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
         nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs);
     return check_launch("residual + restriction to dense");
 }
@@ -716,13 +728,13 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
                 if (level != 0 || h->min_level > -1)
                     return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0 and a dense level below it");
                 k_blk_sweep<T, 2, true><<<L.nb, SWEEP_THREADS, 0, s>>>(
-                    L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs,
+                    L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs,
                     coarse, ccs, nullptr, 0, nullptr, out64);
             } else if (level == 0 && L.nmarch > 0 &&
                        ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0) {
                 return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s);
             } else {
-                k_blk_sweep<T, 0, true><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev,
+                k_blk_sweep<T, 0, true><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev,
                                                                        B, cs, S, eta, out, nullptr, nullptr, nullptr,
                                                                        0, nullptr, 0, nullptr, out64);
             }
@@ -748,17 +760,17 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
             return fail(OHM_ERR_ARG, "level %d: fused sweep needs the ghost arrays and their stride %zu-byte aligned",
                         level, 2 * sizeof(T));
         if (B)
-            k_blk_sweep<T, 3><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S,
+            k_blk_sweep<T, 3><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S,
                                                              eta, out, nullptr, nullptr, nullptr, 0, Bg, gcs, etag);
         else
-            k_blk_sweep<T, 4><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S,
+            k_blk_sweep<T, 4><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S,
                                                              eta, out, nullptr, nullptr, nullptr, 0, nullptr, 0, etag);
         return check_launch("fused sweep with ghosts");
     }
     if (coarse) {
         if (level != 0 || h->min_level > -1 || !B)
             return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0, a dense level below it and an input");
-        k_blk_sweep<T, 2><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta,
+        k_blk_sweep<T, 2><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta,
                                                          out, L.ijk, h->dense[1].probs, coarse, ccs, nullptr, 0,
                                                          nullptr);
     } else if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
@@ -766,10 +778,10 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
     } else if (B) {
         // FP64 tiles go straight from global memory into LDS (16-byte pairs)
         k_blk_sweep<T, 0, false, std::is_same<T, double>::value><<<L.nb, SWEEP_THREADS, 0, s>>>(
-            L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta, out, nullptr, nullptr, nullptr, 0, nullptr,
+            L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, nullptr, nullptr, nullptr, 0, nullptr,
             0, nullptr);
     } else {
-        k_blk_sweep<T, 1><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, L.prob, active, L.inv_h2, coef_dev, B, cs, S, eta,
+        k_blk_sweep<T, 1><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta,
                                                          out, nullptr, nullptr, nullptr, 0, nullptr, 0, nullptr);
     }
     return check_launch("fused sweep");
@@ -782,12 +794,12 @@ ohm_status launch_restrict_blk(const ohm_hier *h, int fine_level, const T *fine,
     if (fine_level >= 1) {
         const AmrLevelDev &L = h->amr[fine_level];
         if (L.nb == 0) return OHM_OK;
-        k_restrict_blk<T><<<L.nb, 64, 0, s>>>(L.nb, L.parent, L.octant, L.prob, active, fine, fcs, coarse, ccs,
+        k_restrict_blk<T><<<L.nb, 64, 0, s>>>(L.nb, L.parent, L.octant, problem_table(h, L), active, fine, fcs, coarse, ccs,
                                               ncomp);
         return check_launch("restrict");
     }
     const AmrLevelDev &L = h->amr[0];
-    k_restrict_blk0_dense<T><<<L.nb, 64, 0, s>>>(L.nb, L.dense_map, L.prob, h->dense[1].probs, active, fine, fcs,
+    k_restrict_blk0_dense<T><<<L.nb, 64, 0, s>>>(L.nb, L.dense_map, problem_table(h, L), h->dense[1].probs, active, fine, fcs,
                                                  coarse, ccs, ncomp);
     return check_launch("restrict to dense");
 }
@@ -801,7 +813,7 @@ ohm_status launch_prolong_blk(const ohm_hier *h, int coarse_level, const T *coar
         if (base) return fail(OHM_ERR_ARG, "prolongation between block levels is in place");
         const AmrLevelDev &F = h->amr[coarse_level + 1];
         if (F.nb == 0) return OHM_OK;
-        k_prolong_blk<T><<<F.nb, 256, 0, s>>>(F.nb, F.parent, F.octant, F.prob, active, h->amr[coarse_level].nbr,
+        k_prolong_blk<T><<<F.nb, 256, 0, s>>>(F.nb, F.parent, F.octant, problem_table(h, F), active, h->amr[coarse_level].nbr,
                                               coarse, ccs, fine, fcs, ncomp, accumulate);
         return check_launch("prolong");
     }
@@ -809,7 +821,7 @@ ohm_status launch_prolong_blk(const ohm_hier *h, int coarse_level, const T *coar
     if (base && !accumulate) return fail(OHM_ERR_ARG, "prolongation onto a base field must accumulate");
     if (ncomp < 1 || ncomp > 3) return fail(OHM_ERR_ARG, "prolongation takes 1 to 3 components, got %d", ncomp);
     if (accumulate && !base) base = fine;
-    k_prolong_dense_blk0<T><<<L.nb, 256, 0, s>>>(L.nb, L.ijk, L.prob, h->dense[1].probs, active, coarse, ccs, base,
+    k_prolong_dense_blk0<T><<<L.nb, 256, 0, s>>>(L.nb, L.ijk, problem_table(h, L), h->dense[1].probs, active, coarse, ccs, base,
                                                  fine, fcs, ncomp);
     return check_launch("prolong from dense");
 }
@@ -820,7 +832,8 @@ ohm_status launch_fill_ghosts(const ohm_hier *h, int level, const T *coarse, lon
 {
     const AmrLevelDev &L = h->amr[level];
     if (level < 1 || L.ng == 0) return OHM_OK;
-    k_prolong_blk<T><<<L.ng, 256, 0, s>>>(L.ng, L.gparent, L.goctant, L.gprob, active, h->amr[level - 1].nbr,
+    k_prolong_blk<T><<<L.ng, 256, 0, s>>>(L.ng, L.gparent, L.goctant, h->nprob == 1 ? nullptr : L.gprob, active,
+                                          h->amr[level - 1].nbr,
                                           coarse, ccs, ghost, gcs, ncomp, 0);
     return check_launch("fill ghosts");
 }

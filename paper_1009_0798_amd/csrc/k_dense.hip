@@ -77,17 +77,6 @@ k_dense_stencil(const int *__restrict__ tiles, const DenseProbDev *__restrict__ 
 // copies of cells at the start (an even period keeps their colour), computed
 // from the same values as by the tile that owns them, so the duplicate
 // stores write equal values.
-__device__ __forceinline__ int wrap_cell(int i, int n)
-{
-    // i >= -2; past the first period only on grids narrower than a tile
-    if (i < 0) return i + n;
-    if (i >= n) {
-        i -= n;
-        if (i >= n) i %= n;
-    }
-    return i;
-}
-
 struct DenseAddr {
     static constexpr bool ghosts = false;
     DenseProbDev q;
@@ -106,25 +95,24 @@ __device__ __forceinline__ DenseAddr dense_tile(const DenseProbDev &q, int t)
 }
 
 // MODE 0: sweep B -> out; 1: zero input (B not read); 2: sweep of B plus the
-// trilinear prolongation of the next coarser grid's field (coarse, problems
-// cdp), B -> out, without storing the corrected input
+// trilinear prolongation of the next coarser grid's field (coarse, grids
+// clist), B -> out, without storing the corrected input
 template <typename T, int MODE>
 __global__ void __launch_bounds__(SWEEP_THREADS)
-k_dense_sweep(const int *__restrict__ ftiles, const DenseProbDev *__restrict__ dp, const int *__restrict__ active,
-              const double *__restrict__ coef_p, const T *__restrict__ B, long long cs, const T *__restrict__ S,
-              const T *__restrict__ eta, T *__restrict__ out, const T *__restrict__ coarse, long long ccs,
-              const DenseProbDev *__restrict__ cdp)
+k_dense_sweep(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p,
+              const T *__restrict__ B, long long cs, const T *__restrict__ S,
+              const T *__restrict__ eta, T *__restrict__ out, const T *__restrict__ coarse, long long ccs)
 {
     __shared__ T sB[3][TC2];
     __shared__ T sE[TC2];
-    const int pr = ftiles[2 * blockIdx.x], t = ftiles[2 * blockIdx.x + 1];
+    const int pr = list.prob(), t = list.tile();
     if (active && !active[pr]) return;
-    const DenseProbDev q = dp[pr];
+    const DenseProbDev q = list.grid(pr);
     const DenseAddr A = dense_tile(q, t);
     const T cih2 = T(coef_p[pr]) * T(q.inv_h2);
     if constexpr (MODE == 2) {
         __shared__ T sC[3 * 512];
-        TileCoarse<T> cor{coarse, ccs, cdp[pr], A.ox / 2 - 2, A.oy / 2 - 2, A.oz / 2 - 2, sC, {}};
+        TileCoarse<T> cor{coarse, ccs, clist.grid(pr), A.ox / 2 - 2, A.oy / 2 - 2, A.oz / 2 - 2, sC, {}};
         fused_sweep_tile<T, false>(A, B, cs, S, eta, out, cih2, sB, sE, cor);
     } else {
         fused_sweep_tile<T, MODE == 1>(A, B, cs, S, eta, out, cih2, sB, sE);
@@ -166,17 +154,16 @@ k_dense_run_copy(const int *__restrict__ runs, const DenseProbDev *__restrict__ 
 // the same 8-child sums as k_dense_stencil<RESID> followed by k_dense_restrict
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_dense_resid_restrict(const int *__restrict__ ftiles, const DenseProbDev *__restrict__ dp,
-                       const DenseProbDev *__restrict__ cdp, const int *__restrict__ active,
+k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ active,
                        const double *__restrict__ coef_p, const T *__restrict__ B, const T *__restrict__ S,
                        const T *__restrict__ eta, T *__restrict__ coarse, long long cs, long long ccs)
 {
     constexpr int W = 10;
     __shared__ T sB[3][W * W * W];
     __shared__ T sE[W * W * W];
-    const int pr = ftiles[2 * blockIdx.x], tile = ftiles[2 * blockIdx.x + 1];
+    const int pr = list.prob(), tile = list.tile();
     if (active && !active[pr]) return;
-    const DenseProbDev q = dp[pr];
+    const DenseProbDev q = list.grid(pr);
     const DenseAddr A = dense_tile(q, tile);
     // thread u < 200 owns tile column (x, y) = u mod 100 and five z: all loads
     // first, then the LDS stores
@@ -229,7 +216,7 @@ k_dense_resid_restrict(const int *__restrict__ ftiles, const DenseProbDev *__res
         for (int c = 0; c < 3; ++c) sB[c][threadIdx.x + 256 * half] = r[half][c];
     __syncthreads();
     const int i = threadIdx.x & 3, j = (threadIdx.x >> 2) & 3, k = threadIdx.x >> 4;
-    const DenseProbDev cq = cdp[pr];
+    const DenseProbDev cq = clist.grid(pr);
     // a coarse cell past the grid's edge belongs to the tile that owns its
     // children (they are copies here)
     if (threadIdx.x < 64 && A.ox / 2 + i < cq.nx && A.oy / 2 + j < cq.ny && A.oz / 2 + k < cq.nz) {
@@ -248,13 +235,12 @@ k_dense_resid_restrict(const int *__restrict__ ftiles, const DenseProbDev *__res
 // dense level -d -> -(d+1): mean of 8 children; one thread per coarse cell
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_dense_restrict(const int *__restrict__ ctiles, const DenseProbDev *__restrict__ cdp,
-                 const DenseProbDev *__restrict__ fdp, const int *__restrict__ active, const T *__restrict__ fine,
+k_dense_restrict(DenseList clist, DenseList flist, const int *__restrict__ active, const T *__restrict__ fine,
                  long long fcs, T *__restrict__ coarse, long long ccs, int ncomp)
 {
-    const int pr = ctiles[2 * blockIdx.x], start = ctiles[2 * blockIdx.x + 1];
+    const int pr = clist.prob(), start = clist.first_cell();
     if (active && !active[pr]) return;
-    const DenseProbDev c = cdp[pr], f = fdp[pr];
+    const DenseProbDev c = clist.grid(pr), f = flist.grid(pr);
     const int cell = start + threadIdx.x;
     if (cell >= c.nx * c.ny * c.nz) return;
     const int i = cell % c.nx, j = (cell / c.nx) % c.ny, k = cell / (c.nx * c.ny);
@@ -271,13 +257,12 @@ k_dense_restrict(const int *__restrict__ ctiles, const DenseProbDev *__restrict_
 // dense -(d+1) -> -d trilinear prolongation; one thread per fine cell
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_dense_prolong(const int *__restrict__ ftiles, const DenseProbDev *__restrict__ fdp,
-                const DenseProbDev *__restrict__ cdp, const int *__restrict__ active, const T *__restrict__ coarse,
+k_dense_prolong(DenseList flist, DenseList clist, const int *__restrict__ active, const T *__restrict__ coarse,
                 long long ccs, const T *base, T *fine, long long fcs, int ncomp)
 {
-    const int pr = ftiles[2 * blockIdx.x], start = ftiles[2 * blockIdx.x + 1];
+    const int pr = flist.prob(), start = flist.first_cell();
     if (active && !active[pr]) return;
-    const DenseProbDev f = fdp[pr], c = cdp[pr];
+    const DenseProbDev f = flist.grid(pr), c = clist.grid(pr);
     const int cell = start + threadIdx.x;
     if (cell >= f.nx * f.ny * f.nz) return;
     const int X = cell % f.nx, Y = (cell / f.nx) % f.ny, Z = cell / (f.nx * f.ny);
@@ -300,6 +285,7 @@ k_dense_prolong(const int *__restrict__ ftiles, const DenseProbDev *__restrict__
 // with partial pivoting (one workgroup per problem), apply as a mat-vec
 // ---------------------------------------------------------------------------
 constexpr int COARSE_MAX_DEV = 768;
+constexpr int COARSE_AHEAD = 24;   // columns of a slice of k_coarse_apply in registers
 
 struct CoarseJob {
     int prob;
@@ -596,17 +582,23 @@ k_coarse_apply(const CoarseJob *__restrict__ jobs, const int *__restrict__ activ
     if (row0 >= n) return;
     __shared__ double sr[COARSE_MAX_DEV];
     __shared__ double part[8][64];
-    for (int t = threadIdx.x; t < n; t += blockDim.x) sr[t] = (double)r[(t / cells) * cs + J.q.off + t % cells];
-    __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int row = row0 + lane;
-    const double *X = inv + J.inv_off;
+    const double *X = inv + J.inv_off + min(row, n - 1);
     const int per = (n + 7) / 8, c0 = w * per, c1 = min(n, c0 + per);
+    // the first columns of the slice (all of them up to 192 unknowns) are
+    // requested together with the right-hand side
+    double x[COARSE_AHEAD];
+#pragma unroll
+    for (int k = 0; k < COARSE_AHEAD; ++k) x[k] = X[(long long)min(c0 + k, n - 1) * n];
+    for (int t = threadIdx.x; t < n; t += blockDim.x) sr[t] = (double)r[(t / cells) * cs + J.q.off + t % cells];
+    __syncthreads();
     double acc = 0.0;
-    if (row < n) {
+#pragma unroll
+    for (int k = 0; k < COARSE_AHEAD; ++k)
+        if (c0 + k < c1) acc = fma(x[k], sr[c0 + k], acc);
 #pragma unroll 8
-        for (int c = c0; c < c1; ++c) acc = fma(X[(long long)c * n + row], sr[c], acc);
-    }
+    for (int c = c0 + COARSE_AHEAD; c < c1; ++c) acc = fma(X[(long long)c * n], sr[c], acc);
     part[w][lane] = acc;
     __syncthreads();
     if (w == 0 && row < n) {
@@ -692,7 +684,7 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
     if ((coarse || last) && (npt > 0 || zero || nsweeps < 1 || -level >= -h->min_level))
         return fail(OHM_ERR_ARG, "dense level %d: a fused coarse correction or a result left in place needs whole "
                                  "tiles, an input, a sweep and a coarser level", level);
-    const DenseLevelDev *Dc = coarse ? &h->dense[-level + 1] : nullptr;
+    const DenseList list = dense_list(h, D, ft), none{};
     if (nft > 0) {
         // fused tiles ping-pong between B and tmp; a zero input is not read, so
         // the first sweep may write either buffer: pick the one that makes the
@@ -702,16 +694,17 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
             T *dst;
             if (k == 0 && zero) {
                 dst = (nsweeps & 1) ? B : tmp;
-                k_dense_sweep<T, 1><<<nft, SWEEP_THREADS, 0, s>>>(ft, D.probs, active, coef_dev, nullptr, cs, S, eta,
-                                                                  dst, nullptr, 0, nullptr);
+                k_dense_sweep<T, 1><<<nft, SWEEP_THREADS, 0, s>>>(list, none, active, coef_dev, nullptr, cs, S, eta,
+                                                                  dst, nullptr, 0);
             } else if (k == 0 && coarse) {
                 dst = cur == B ? tmp : B;
-                k_dense_sweep<T, 2><<<nft, SWEEP_THREADS, 0, s>>>(ft, D.probs, active, coef_dev, cur, cs, S, eta,
-                                                                  dst, coarse, Dc->ncells, Dc->probs);
+                const DenseLevelDev &C = h->dense[-level + 1];
+                k_dense_sweep<T, 2><<<nft, SWEEP_THREADS, 0, s>>>(list, dense_list(h, C, C.tiles_all), active, coef_dev,
+                                                                  cur, cs, S, eta, dst, coarse, C.ncells);
             } else {
                 dst = cur == B ? tmp : B;
-                k_dense_sweep<T, 0><<<nft, SWEEP_THREADS, 0, s>>>(ft, D.probs, active, coef_dev, cur, cs, S, eta,
-                                                                  dst, nullptr, 0, nullptr);
+                k_dense_sweep<T, 0><<<nft, SWEEP_THREADS, 0, s>>>(list, none, active, coef_dev, cur, cs, S, eta, dst,
+                                                                  nullptr, 0);
             }
             OHM_TRY(check_launch("dense fused sweep"));
             cur = dst;
@@ -759,8 +752,8 @@ ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B,
         OHM_TRY(launch_dense_stencil<T>(h, level, MODE_RESID, B, S, eta, coef_dev, res, 0, false, active, s));
         return launch_dense_restrict<T>(h, level, res, coarse, 3, active, s);
     }
-    k_dense_resid_restrict<T><<<D.nftile, 256, 0, s>>>(D.ftiles, D.probs, C.probs, active, coef_dev, B, S, eta,
-                                                        coarse, D.ncells, C.ncells);
+    k_dense_resid_restrict<T><<<D.nftile, 256, 0, s>>>(dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active,
+                                                        coef_dev, B, S, eta, coarse, D.ncells, C.ncells);
     return check_launch("dense residual + restriction");
 }
 
@@ -770,8 +763,8 @@ ohm_status launch_dense_restrict(const ohm_hier *h, int fine_level, const T *fin
 {
     const DenseLevelDev &F = h->dense[-fine_level], &C = h->dense[-fine_level + 1];
     if (C.ntile_all == 0) return OHM_OK;
-    k_dense_restrict<T><<<C.ntile_all, 256, 0, s>>>(C.tiles_all, C.probs, F.probs, active, fine, F.ncells, coarse,
-                                                    C.ncells, ncomp);
+    k_dense_restrict<T><<<C.ntile_all, 256, 0, s>>>(dense_list(h, C, C.tiles_all), dense_list(h, F, F.tiles), active,
+                                                    fine, F.ncells, coarse, C.ncells, ncomp);
     return check_launch("dense restrict");
 }
 
@@ -783,8 +776,8 @@ ohm_status launch_dense_prolong(const ohm_hier *h, int coarse_level, const T *co
     if (F.ntile == 0) return OHM_OK;
     if (base && !accumulate) return fail(OHM_ERR_ARG, "prolongation onto a base field must accumulate");
     if (accumulate && !base) base = fine;
-    k_dense_prolong<T><<<F.ntile, 256, 0, s>>>(F.tiles, F.probs, C.probs, active, coarse, C.ncells, base, fine,
-                                               F.ncells, ncomp);
+    k_dense_prolong<T><<<F.ntile, 256, 0, s>>>(dense_list(h, F, F.tiles), dense_list(h, C, C.tiles_all), active, coarse,
+                                               C.ncells, base, fine, F.ncells, ncomp);
     return check_launch("dense prolong");
 }
 

@@ -15,6 +15,25 @@ __device__ __forceinline__ int xcd_block2(int w, int n)
     return x * q + min(x, r) + i;
 }
 
+// problem of block b; a handle of one problem passes no table, which takes one
+// of the dependent loads in front of the fields away (a small launch is little
+// else)
+__device__ __forceinline__ int problem_of(const int *prob_of, int b) { return prob_of ? prob_of[b] : 0; }
+
+// A block's 3 x 512 elements of a vector by a group of 256: element k of a
+// thread is cell t + 256 (k mod 2) of component k / 2.  All loads of a kernel
+// are issued before the first use.
+constexpr int PER = 6;
+__device__ __forceinline__ long long elem(long long cs, int b, int k)
+{
+    return (k >> 1) * cs + (long long)b * NC + threadIdx.x + 256 * (k & 1);
+}
+__device__ __forceinline__ void load_block(double v[PER], const double *__restrict__ a, long long cs, int b)
+{
+#pragma unroll
+    for (int k = 0; k < PER; ++k) v[k] = a[elem(cs, b, k)];
+}
+
 template <typename T>
 __global__ void k_fill(T *__restrict__ a, long long n, T v)
 {
@@ -53,16 +72,20 @@ k_dot(int nblk, const int *__restrict__ prob_of, const int *__restrict__ active,
 {
     __shared__ double sred[3][4];
     const int b = xcd_block2(blockIdx.x, nblk);
-    if (active && !active[prob_of[b]]) {
+    if (active && !active[problem_of(prob_of, b)]) {
         if (threadIdx.x < nq) part[(long long)b * nq + threadIdx.x] = 0.0;
         return;
     }
     double acc[3] = {0, 0, 0};
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const int c = t / NC, cell = t % NC;
-        const long long gi = c * cs + (long long)b * NC + cell;
-        for (int q = 0; q < nq; ++q) acc[q] += a.x[q][gi] * a.y[q][gi];
-        if (a.copy) a.copy[gi] = a.x[0][gi];
+    for (int q = 0; q < nq; ++q) {
+        double x[PER], y[PER];
+        load_block(x, a.x[q], cs, b);
+        load_block(y, a.y[q], cs, b);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) acc[q] += x[k] * y[k];
+        if (q == 0 && a.copy)
+#pragma unroll
+            for (int k = 0; k < PER; ++k) a.copy[elem(cs, b, k)] = x[k];
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int q = 0; q < nq; ++q) {
@@ -85,12 +108,13 @@ k_norms(int nblk, const int *__restrict__ prob_of, const int *__restrict__ activ
     __shared__ double sred[6][4];
     const int b = xcd_block2(blockIdx.x, nblk);
     double ss[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
-    if (!(active && !active[prob_of[b]])) {
-        for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-            const int c = t / NC;
-            const double v = x[c * cs + (long long)b * NC + t % NC];
-            ss[c] += v * v;
-            mx[c] = fmax(mx[c], fabs(v));
+    if (!(active && !active[problem_of(prob_of, b)])) {
+        double v[PER];
+        load_block(v, x, cs, b);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            ss[k >> 1] += v[k] * v[k];
+            mx[k >> 1] = fmax(mx[k >> 1], fabs(v[k]));
         }
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -133,20 +157,22 @@ k_bicg_p(int nblk, const int *__restrict__ prob_of, const int *__restrict__ acti
          double *__restrict__ p, float *__restrict__ c32, double *__restrict__ c64)
 {
     const int b = xcd_block2(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
     const double beta = scal[SC_N * pr + SC_BETA], omega = scal[SC_N * pr + SC_OMEGA];
     if (beta == 0.0) {   // restart: p = r; p and v are not read (they hold no state yet)
-        for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-            const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-            put(p, c32, c64, gi, r[gi]);
-        }
+        double r6[PER];
+        load_block(r6, r, cs, b);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) put(p, c32, c64, elem(cs, b, k), r6[k]);
         return;
     }
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-        put(p, c32, c64, gi, r[gi] + beta * (p[gi] - omega * v[gi]));
-    }
+    double r6[PER], p6[PER], v6[PER];
+    load_block(r6, r, cs, b);
+    load_block(p6, p, cs, b);
+    load_block(v6, v, cs, b);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) put(p, c32, c64, elem(cs, b, k), r6[k] + beta * (p6[k] - omega * v6[k]));
 }
 
 // s = r - alpha v
@@ -156,13 +182,14 @@ k_bicg_s(int nblk, const int *__restrict__ prob_of, const int *__restrict__ acti
          double *__restrict__ s, float *__restrict__ c32, double *__restrict__ c64)
 {
     const int b = xcd_block2(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
     const double alpha = scal[SC_N * pr + SC_ALPHA];
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-        put(s, c32, c64, gi, r[gi] - alpha * v[gi]);
-    }
+    double r6[PER], v6[PER];
+    load_block(r6, r, cs, b);
+    load_block(v6, v, cs, b);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) put(s, c32, c64, elem(cs, b, k), r6[k] - alpha * v6[k]);
 }
 
 // x += alpha ph + omega sh;  r = s - omega t;  partial (r, r) and (rhat, r)
@@ -174,20 +201,28 @@ k_bicg_xr(int nblk, const int *__restrict__ prob_of, const int *__restrict__ act
 {
     __shared__ double sred[2][4];
     const int b = xcd_block2(blockIdx.x, nblk);
-    const int pr = prob_of[b];
+    const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) {
         if (threadIdx.x < 2) part[2 * (long long)b + threadIdx.x] = 0.0;
         return;
     }
     const double alpha = scal[SC_N * pr + SC_ALPHA], omega = scal[SC_N * pr + SC_OMEGA];
     double rr = 0.0, rh = 0.0;
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-        x[gi] += alpha * ph[gi] + omega * sh[gi];
-        const double rn = s[gi] - omega * t_[gi];
+    double s6[PER], t6[PER], h6[PER], x6[PER], p6[PER], q6[PER];
+    load_block(s6, s, cs, b);
+    load_block(t6, t_, cs, b);
+    load_block(h6, rhat, cs, b);
+    load_block(x6, x, cs, b);
+    load_block(p6, ph, cs, b);
+    load_block(q6, sh, cs, b);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const long long gi = elem(cs, b, k);
+        const double rn = s6[k] - omega * t6[k];
         r[gi] = rn;
         rr += rn * rn;
-        rh += rhat[gi] * rn;
+        rh += h6[k] * rn;
+        x[gi] = x6[k] + (alpha * p6[k] + omega * q6[k]);
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int o = 32; o > 0; o >>= 1) {
@@ -210,11 +245,12 @@ k_axpy1(int nblk, const int *__restrict__ prob_of, const int *__restrict__ activ
         double *__restrict__ x, const double *__restrict__ y)
 {
     const int b = xcd_block2(blockIdx.x, nblk);
-    if (active && !active[prob_of[b]]) return;
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-        x[gi] += y[gi];
-    }
+    if (active && !active[problem_of(prob_of, b)]) return;
+    double x6[PER], y6[PER];
+    load_block(x6, x, cs, b);
+    load_block(y6, y, cs, b);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) x[elem(cs, b, k)] = x6[k] + y6[k];
 }
 
 // x = (x + y) / 2 (the corrector of the explicit predictor-corrector step)
@@ -223,11 +259,12 @@ k_mean2(int nblk, const int *__restrict__ prob_of, const int *__restrict__ activ
         double *__restrict__ x, const double *__restrict__ y)
 {
     const int b = xcd_block2(blockIdx.x, nblk);
-    if (active && !active[prob_of[b]]) return;
-    for (int t = threadIdx.x; t < 3 * NC; t += 256) {
-        const long long gi = (t / NC) * cs + (long long)b * NC + t % NC;
-        x[gi] = 0.5 * (x[gi] + y[gi]);
-    }
+    if (active && !active[problem_of(prob_of, b)]) return;
+    double x6[PER], y6[PER];
+    load_block(x6, x, cs, b);
+    load_block(y6, y, cs, b);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) x[elem(cs, b, k)] = 0.5 * (x6[k] + y6[k]);
 }
 
 // BiCGStab scalars of one problem from the reduced products d of the
@@ -274,11 +311,21 @@ __device__ __forceinline__ void scal_update(int stage, double *S, const double *
 // slot of an iteration is the same for all problems.
 __global__ void __launch_bounds__(1024)
 k_reduce_scal(int nrange, const long long *__restrict__ range, const double *__restrict__ part, int k,
-              double *__restrict__ out, int stage, const int *active, double *__restrict__ scal, IterRing ring)
+              double *__restrict__ out, double *__restrict__ host_out, int stage, const int *active,
+              double *__restrict__ scal, IterRing ring)
 {
     __shared__ double sred[4][4];
     const int p = blockIdx.x;
     const int g = threadIdx.x >> 8, tid = threadIdx.x & 255;
+    // what the last thread to act reads, on its way while the sums are formed
+    double S[SC_N];
+    bool on = true;
+    if (threadIdx.x == 0) {
+        on = !(active && !active[p]);
+        if (stage >= 0)
+#pragma unroll
+            for (int k = 0; k <= SC_IT; ++k) S[k] = scal[SC_N * p + k];
+    }
     if (g < k) {
         double v = 0.0;
         long long base = 0;
@@ -309,10 +356,10 @@ k_reduce_scal(int nrange, const long long *__restrict__ range, const double *__r
             for (int w = 1; w < 4; ++w) t = t + sred[q][w];
             d[q] = t;
             out[(long long)p * k + q] = t;
+            if (host_out) host_out[(long long)p * k + q] = t;
         }
-        double *S = scal + SC_N * p;
-        const bool on = !(active && !active[p]);
-        if (stage >= 0 && on) scal_update(stage, S, d);
+        if (stage < 0) return;
+        if (on) scal_update(stage, S, d);
         if (stage == 0) S[SC_IT] = 0.0;
         if (stage == 4 && ring.buf) {
             const int it = (int)S[SC_IT];
@@ -323,6 +370,8 @@ k_reduce_scal(int nrange, const long long *__restrict__ range, const double *__r
             if (on && !(d[0] > ring.tol2[p])) ring.flags[p] = 0;
             if (on && !isfinite(d[0])) *ring.hold = 1;
         }
+#pragma unroll
+        for (int q = 0; q <= SC_IT; ++q) scal[SC_N * p + q] = S[q];
     }
 }
 
@@ -404,12 +453,13 @@ ohm_status vbicg_xr(int nblk, const int *prob_of, const int *active, long long c
 }
 
 ohm_status launch_reduce_scal(int nprob, int nrange, const long long *range_dev, const double *part, int k,
-                              double *out, int stage, const int *active, double *scal, hipStream_t s, IterRing ring)
+                              double *out, int stage, const int *active, double *scal, hipStream_t s, IterRing ring,
+                              double *host_out)
 {
     if (k < 1 || k > 4) return fail(OHM_ERR_ARG, "reduce + scalars takes 1 to 4 quantities, got %d", k);
     if (ring.buf && (stage != 4 || k < 2 || !ring.flags || !ring.tol2 || !ring.hold))
         return fail(OHM_ERR_ARG, "the iteration ring is written by stage 4 with two norms and needs flags and thresholds");
-    k_reduce_scal<<<nprob, 256 * k, 0, s>>>(nrange, range_dev, part, k, out, stage, active, scal, ring);
+    k_reduce_scal<<<nprob, 256 * k, 0, s>>>(nrange, range_dev, part, k, out, host_out, stage, active, scal, ring);
     return check_launch("reduce + scalars");
 }
 

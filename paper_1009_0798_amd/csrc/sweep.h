@@ -33,6 +33,17 @@ constexpr int TC2 = TW2 * TW2 * TW2;
 
 __device__ __forceinline__ int tix2(int x, int y, int z) { return (x + 2) + TW2 * ((y + 2) + TW2 * (z + 2)); }
 
+__device__ __forceinline__ int wrap_cell(int i, int n)
+{
+    // i >= -2; past the first period only on grids narrower than a tile
+    if (i < 0) return i + n;
+    if (i >= n) {
+        i -= n;
+        if (i >= n) i %= n;
+    }
+    return i;
+}
+
 // two consecutive elements, loaded and stored as one 2 sizeof(T) access
 template <typename T>
 struct alignas(2 * sizeof(T)) Pair {
@@ -86,8 +97,8 @@ struct TileCoarse {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const int t = threadIdx.x + SWEEP_THREADS * k, c = t >> 9, m = t & 511;
-            const int i = (i0 + (m & 7) + q.nx) % q.nx, j = (j0 + ((m >> 3) & 7) + q.ny) % q.ny,
-                      kk = (k0 + (m >> 6) + q.nz) % q.nz;
+            const int i = wrap_cell(i0 + (m & 7), q.nx), j = wrap_cell(j0 + ((m >> 3) & 7), q.ny),
+                      kk = wrap_cell(k0 + (m >> 6), q.nz);
             r[k] = coarse[c * ccs + q.off + i + (long long)q.nx * (j + (long long)q.ny * kk)];
         }
     }
