@@ -121,12 +121,9 @@ struct DenseList {
     const DenseProbDev *probs;
     DenseProbDev one;
     bool single;
-    __device__ __forceinline__ int prob() const { return single ? 0 : tiles[2 * blockIdx.x]; }
-    __device__ __forceinline__ int tile() const { return single ? (int)blockIdx.x : tiles[2 * blockIdx.x + 1]; }
-    __device__ __forceinline__ int first_cell() const
-    {
-        return single ? 256 * (int)blockIdx.x : tiles[2 * blockIdx.x + 1];
-    }
+    __device__ __forceinline__ int prob(int g) const { return single ? 0 : tiles[2 * g]; }
+    __device__ __forceinline__ int tile(int g) const { return single ? g : tiles[2 * g + 1]; }
+    __device__ __forceinline__ int first_cell(int g) const { return single ? 256 * g : tiles[2 * g + 1]; }
     __device__ __forceinline__ DenseProbDev grid(int pr) const { return single ? one : probs[pr]; }
 };
 

@@ -287,52 +287,42 @@ struct GhostBlockAddr {
 // MODE 0: sweep B -> out; 1: zero input (B not read); 2: sweep of B plus the
 // prolonged correction from the first dense level (coarse), B -> out; MODE 3
 // and 4 as 0 and 1 on a level with coarse-fine ghost blocks (Bg, etag).  With
-// O64 (MODE 0 or 2 of an FP32 sweep) the result is written as FP64 to out64.
-template <typename T, int MODE, bool O64 = false, bool DIRECT = false>
-__global__ void __launch_bounds__(SWEEP_THREADS)
+// O64 (MODE 0 or 2 of an FP32 sweep) the result is written as FP64.
+template <typename T, int MODE, bool O64, bool DIRECT, typename Tl>
+__global__ void __launch_bounds__(Tl::THREADS)
 k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
             const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
             const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
-            T *__restrict__ out, const int *__restrict__ ijk, const DenseProbDev *__restrict__ dp,
+            void *__restrict__ out, const int *__restrict__ ijk, const DenseProbDev *__restrict__ dp,
             const T *__restrict__ coarse, long long ccs, const T *__restrict__ Bg, long long gcs,
-            const T *__restrict__ etag, double *__restrict__ out64 = nullptr)
+            const T *__restrict__ etag)
 {
-    constexpr int TS = DIRECT ? TC2 + 64 : TC2;
+    using TO = typename std::conditional<O64, double, T>::type;
+    using Addr = typename std::conditional<(MODE >= 3), GhostBlockAddr<T>, BlockAddr>::type;
+    using Part = typename std::conditional<Tl::whole, Addr, PartAddr<Addr>>::type;
+    using Coarse = typename std::conditional<MODE == 2, TileCoarse<T, Tl>, NoCoarse<T>>::type;
+    constexpr int TS = Tl::N + (DIRECT && Tl::whole ? 64 : 0);
     __shared__ T sB[3][TS];
     __shared__ T sE[TS];
-    __shared__ T sC[MODE == 2 ? 3 * 512 : 1];
+    __shared__ T sC[MODE == 2 ? 3 * Tl::NCOARSE : 1];
     __shared__ int snbr[27];
-    const int b = xcd_block(blockIdx.x, nblk);
+    const int w = xcd_block(blockIdx.x, nblk * Tl::PARTS), b = w / Tl::PARTS, part = w % Tl::PARTS;
     const int mine = load_nbr(nbr_tab, b);
     const int pr = problem_of(prob_of, b);
     if (active && !active[pr]) return;
     if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
     __syncthreads();
     const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
-    if constexpr (DIRECT) {
-        const BlockAddr A{snbr, b};
-        fused_sweep_tile<T, false, BlockAddr, NoCoarse<T>, T, TS, true>(A, B, cs, S, eta, out, cih2, sB, sE);
-        return;
-    } else {
-    if constexpr (MODE >= 3) {
-        const GhostBlockAddr<T> A{snbr, Bg, gcs, etag};
-        fused_sweep_tile<T, MODE == 4>(A, B, cs, S, eta, out, cih2, sB, sE);
-    } else if constexpr (MODE == 2) {
-        const BlockAddr A{snbr, b};
-        TileCoarse<T> cor{coarse, ccs, dp[pr], 4 * ijk[3 * b] - 2, 4 * ijk[3 * b + 1] - 2, 4 * ijk[3 * b + 2] - 2,
-                          sC, {}};
-        if constexpr (O64)
-            fused_sweep_tile<T, false, BlockAddr, TileCoarse<T>, double>(A, B, cs, S, eta, out64, cih2, sB, sE, cor);
-        else
-            fused_sweep_tile<T, false>(A, B, cs, S, eta, out, cih2, sB, sE, cor);
-    } else {
-        const BlockAddr A{snbr, b};
-        if constexpr (O64)
-            fused_sweep_tile<T, MODE == 1, BlockAddr, NoCoarse<T>, double>(A, B, cs, S, eta, out64, cih2, sB, sE);
-        else
-            fused_sweep_tile<T, MODE == 1>(A, B, cs, S, eta, out, cih2, sB, sE);
-    }
-    }
+    Part A;
+    if constexpr (MODE >= 3) static_cast<Addr &>(A) = Addr{snbr, Bg, gcs, etag};
+    else static_cast<Addr &>(A) = Addr{snbr, b};
+    if constexpr (!Tl::whole) A.y0 = Tl::y0(part), A.z0 = Tl::z0(part);
+    Coarse cor;
+    if constexpr (MODE == 2)
+        cor = {coarse, ccs, dp[pr], 4 * ijk[3 * b] - 2, 4 * ijk[3 * b + 1] - 2 + Tl::y0(part) / 2,
+               4 * ijk[3 * b + 2] - 2 + Tl::z0(part) / 2, sC, {}};
+    fused_sweep_tile<T, MODE == 1 || MODE == 4, Part, Coarse, TO, Tl, TS, DIRECT>(A, B, cs, S, eta, (TO *)out, cih2,
+                                                                                  sB, sE, cor);
 }
 
 // ---------------------------------------------------------------------------
@@ -708,6 +698,21 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     return check_launch("residual + restriction to dense");
 }
 
+template <typename T, int MODE, bool O64, bool DIRECT>
+static void blk_sweep(const ohm_hier *h, const AmrLevelDev &L, const T *B, long long cs, const T *S, const T *eta,
+                      const double *coef_dev, void *out, const int *active, hipStream_t s, const T *coarse,
+                      long long ccs, const T *Bg, long long gcs, const T *etag)
+{
+#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs, \
+             coarse, ccs, Bg, gcs, etag
+    switch (tile_parts(L.nb)) {
+    case 4: k_blk_sweep<T, MODE, O64, DIRECT, Tile<4, 4>><<<4 * L.nb, Tile<4, 4>::THREADS, 0, s>>>(ARGS); break;
+    case 2: k_blk_sweep<T, MODE, O64, DIRECT, Tile<8, 4>><<<2 * L.nb, Tile<8, 4>::THREADS, 0, s>>>(ARGS); break;
+    default: k_blk_sweep<T, MODE, O64, DIRECT, WholeTile><<<L.nb, WholeTile::THREADS, 0, s>>>(ARGS);
+    }
+#undef ARGS
+}
+
 template <typename T>
 ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long cs, const T *S, const T *eta,
                             const double *coef_dev, T *out, const int *active, hipStream_t s, const T *coarse,
@@ -727,16 +732,14 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
             if (coarse) {
                 if (level != 0 || h->min_level > -1)
                     return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0 and a dense level below it");
-                k_blk_sweep<T, 2, true><<<L.nb, SWEEP_THREADS, 0, s>>>(
-                    L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs,
-                    coarse, ccs, nullptr, 0, nullptr, out64);
+                blk_sweep<T, 2, true, false>(h, L, B, cs, S, eta, coef_dev, out64, active, s, coarse, ccs, nullptr, 0,
+                                             nullptr);
             } else if (level == 0 && L.nmarch > 0 &&
                        ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0) {
                 return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s);
             } else {
-                k_blk_sweep<T, 0, true><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev,
-                                                                       B, cs, S, eta, out, nullptr, nullptr, nullptr,
-                                                                       0, nullptr, 0, nullptr, out64);
+                blk_sweep<T, 0, true, false>(h, L, B, cs, S, eta, coef_dev, out64, active, s, nullptr, 0, nullptr, 0,
+                                             nullptr);
             }
             return check_launch("fused sweep to FP64");
         } else {
@@ -760,29 +763,23 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
             return fail(OHM_ERR_ARG, "level %d: fused sweep needs the ghost arrays and their stride %zu-byte aligned",
                         level, 2 * sizeof(T));
         if (B)
-            k_blk_sweep<T, 3><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S,
-                                                             eta, out, nullptr, nullptr, nullptr, 0, Bg, gcs, etag);
+            blk_sweep<T, 3, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0, Bg, gcs, etag);
         else
-            k_blk_sweep<T, 4><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S,
-                                                             eta, out, nullptr, nullptr, nullptr, 0, nullptr, 0, etag);
+            blk_sweep<T, 4, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0, nullptr, 0, etag);
         return check_launch("fused sweep with ghosts");
     }
     if (coarse) {
         if (level != 0 || h->min_level > -1 || !B)
             return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0, a dense level below it and an input");
-        k_blk_sweep<T, 2><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta,
-                                                         out, L.ijk, h->dense[1].probs, coarse, ccs, nullptr, 0,
-                                                         nullptr);
+        blk_sweep<T, 2, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, coarse, ccs, nullptr, 0, nullptr);
     } else if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
         return launch_march_sweep<T, T>(h, B, cs, S, eta, coef_dev, out, active, s);
     } else if (B) {
         // FP64 tiles go straight from global memory into LDS (16-byte pairs)
-        k_blk_sweep<T, 0, false, std::is_same<T, double>::value><<<L.nb, SWEEP_THREADS, 0, s>>>(
-            L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, nullptr, nullptr, nullptr, 0, nullptr,
-            0, nullptr);
+        blk_sweep<T, 0, false, std::is_same<T, double>::value>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0,
+                                                               nullptr, 0, nullptr);
     } else {
-        k_blk_sweep<T, 1><<<L.nb, SWEEP_THREADS, 0, s>>>(L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta,
-                                                         out, nullptr, nullptr, nullptr, 0, nullptr, 0, nullptr);
+        blk_sweep<T, 1, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0, nullptr, 0, nullptr);
     }
     return check_launch("fused sweep");
 }

@@ -97,26 +97,27 @@ __device__ __forceinline__ DenseAddr dense_tile(const DenseProbDev &q, int t)
 // MODE 0: sweep B -> out; 1: zero input (B not read); 2: sweep of B plus the
 // trilinear prolongation of the next coarser grid's field (coarse, grids
 // clist), B -> out, without storing the corrected input
-template <typename T, int MODE>
-__global__ void __launch_bounds__(SWEEP_THREADS)
+template <typename T, int MODE, typename Tl>
+__global__ void __launch_bounds__(Tl::THREADS)
 k_dense_sweep(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p,
               const T *__restrict__ B, long long cs, const T *__restrict__ S,
               const T *__restrict__ eta, T *__restrict__ out, const T *__restrict__ coarse, long long ccs)
 {
-    __shared__ T sB[3][TC2];
-    __shared__ T sE[TC2];
-    const int pr = list.prob(), t = list.tile();
+    using Coarse = typename std::conditional<MODE == 2, TileCoarse<T, Tl>, NoCoarse<T>>::type;
+    __shared__ T sB[3][Tl::N];
+    __shared__ T sE[Tl::N];
+    __shared__ T sC[MODE == 2 ? 3 * Tl::NCOARSE : 1];
+    const int g = blockIdx.x / Tl::PARTS, part = blockIdx.x % Tl::PARTS;
+    const int pr = list.prob(g), t = list.tile(g);
     if (active && !active[pr]) return;
     const DenseProbDev q = list.grid(pr);
-    const DenseAddr A = dense_tile(q, t);
+    DenseAddr A = dense_tile(q, t);
+    A.oy += Tl::y0(part);
+    A.oz += Tl::z0(part);
     const T cih2 = T(coef_p[pr]) * T(q.inv_h2);
-    if constexpr (MODE == 2) {
-        __shared__ T sC[3 * 512];
-        TileCoarse<T> cor{coarse, ccs, clist.grid(pr), A.ox / 2 - 2, A.oy / 2 - 2, A.oz / 2 - 2, sC, {}};
-        fused_sweep_tile<T, false>(A, B, cs, S, eta, out, cih2, sB, sE, cor);
-    } else {
-        fused_sweep_tile<T, MODE == 1>(A, B, cs, S, eta, out, cih2, sB, sE);
-    }
+    Coarse cor;
+    if constexpr (MODE == 2) cor = {coarse, ccs, clist.grid(pr), A.ox / 2 - 2, A.oy / 2 - 2, A.oz / 2 - 2, sC, {}};
+    fused_sweep_tile<T, MODE == 1, DenseAddr, Coarse, T, Tl>(A, B, cs, S, eta, out, cih2, sB, sE, cor);
 }
 
 // copy (src != nullptr) or zero the cells of the listed 8^3 tiles (3 components)
@@ -161,7 +162,7 @@ k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ 
     constexpr int W = 10;
     __shared__ T sB[3][W * W * W];
     __shared__ T sE[W * W * W];
-    const int pr = list.prob(), tile = list.tile();
+    const int pr = list.prob(blockIdx.x), tile = list.tile(blockIdx.x);
     if (active && !active[pr]) return;
     const DenseProbDev q = list.grid(pr);
     const DenseAddr A = dense_tile(q, tile);
@@ -238,7 +239,7 @@ __global__ void __launch_bounds__(256)
 k_dense_restrict(DenseList clist, DenseList flist, const int *__restrict__ active, const T *__restrict__ fine,
                  long long fcs, T *__restrict__ coarse, long long ccs, int ncomp)
 {
-    const int pr = clist.prob(), start = clist.first_cell();
+    const int pr = clist.prob(blockIdx.x), start = clist.first_cell(blockIdx.x);
     if (active && !active[pr]) return;
     const DenseProbDev c = clist.grid(pr), f = flist.grid(pr);
     const int cell = start + threadIdx.x;
@@ -260,7 +261,7 @@ __global__ void __launch_bounds__(256)
 k_dense_prolong(DenseList flist, DenseList clist, const int *__restrict__ active, const T *__restrict__ coarse,
                 long long ccs, const T *base, T *fine, long long fcs, int ncomp)
 {
-    const int pr = flist.prob(), start = flist.first_cell();
+    const int pr = flist.prob(blockIdx.x), start = flist.first_cell(blockIdx.x);
     if (active && !active[pr]) return;
     const DenseProbDev f = flist.grid(pr), c = clist.grid(pr);
     const int cell = start + threadIdx.x;
@@ -642,6 +643,16 @@ ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T 
 // half-sweep launches; the four-colour ordering takes four class launches per
 // sweep on every problem.  all = every problem present, else the problems that
 // are not coarsest at this level.
+template <typename T, int MODE, typename... Args>
+static void dense_sweep(int nft, hipStream_t s, Args... args)
+{
+    switch (tile_parts(nft)) {
+    case 4: k_dense_sweep<T, MODE, Tile<4, 4>><<<4 * nft, Tile<4, 4>::THREADS, 0, s>>>(args...); break;
+    case 2: k_dense_sweep<T, MODE, Tile<8, 4>><<<2 * nft, Tile<8, 4>::THREADS, 0, s>>>(args...); break;
+    default: k_dense_sweep<T, MODE, WholeTile><<<nft, WholeTile::THREADS, 0, s>>>(args...);
+    }
+}
+
 template <typename T>
 ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const T *S, const T *eta,
                                const double *coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
@@ -694,17 +705,15 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
             T *dst;
             if (k == 0 && zero) {
                 dst = (nsweeps & 1) ? B : tmp;
-                k_dense_sweep<T, 1><<<nft, SWEEP_THREADS, 0, s>>>(list, none, active, coef_dev, nullptr, cs, S, eta,
-                                                                  dst, nullptr, 0);
+                dense_sweep<T, 1>(nft, s, list, none, active, coef_dev, nullptr, cs, S, eta, dst, nullptr, 0);
             } else if (k == 0 && coarse) {
                 dst = cur == B ? tmp : B;
                 const DenseLevelDev &C = h->dense[-level + 1];
-                k_dense_sweep<T, 2><<<nft, SWEEP_THREADS, 0, s>>>(list, dense_list(h, C, C.tiles_all), active, coef_dev,
-                                                                  cur, cs, S, eta, dst, coarse, C.ncells);
+                dense_sweep<T, 2>(nft, s, list, dense_list(h, C, C.tiles_all), active, coef_dev, cur, cs, S, eta, dst,
+                                  coarse, C.ncells);
             } else {
                 dst = cur == B ? tmp : B;
-                k_dense_sweep<T, 0><<<nft, SWEEP_THREADS, 0, s>>>(list, none, active, coef_dev, cur, cs, S, eta, dst,
-                                                                  nullptr, 0);
+                dense_sweep<T, 0>(nft, s, list, none, active, coef_dev, cur, cs, S, eta, dst, nullptr, 0);
             }
             OHM_TRY(check_launch("dense fused sweep"));
             cur = dst;

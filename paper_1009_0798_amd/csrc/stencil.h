@@ -1,11 +1,11 @@
 // Device-side discrete operator of eqs. (8)-(11) and the smoother diagonal of
-// eqs. (21)-(23), on a cube of cells of edge W held in fast memory (LDS tile or
-// registers).
+// eqs. (21)-(23), on a box of cells with rows of W cells and planes of P cells
+// (a cube unless given) held in fast memory (LDS tile or registers).
 #pragma once
 
 namespace ohm {
 
-// All three components at index p of a W^3 cube, every neighbour read once:
+// All three components at index p of the box, every neighbour read once:
 //   dv[c] = 8 h^2 (div F)_c  and  al[c] = 2 h^2 alpha_c / lam_dt.
 // Face fluxes are written without their power-of-two factors: with E the sum of
 // the two cell resistivities at a face (twice the mean of eq. 11), t the
@@ -13,11 +13,11 @@ namespace ohm {
 // normal difference (eq. 9), 8 h F = E (t - 4 n); scaling by 2, 4 or 8 is exact,
 // so the callers fold the factors into their coefficients.  The central
 // difference of B_d along c at p is shared by the +d and -d faces.
-template <typename T, int W>
+template <typename T, int W, int P = W * W>
 __device__ __forceinline__ void divF_all(const T *__restrict__ Bx, const T *__restrict__ By, const T *__restrict__ Bz,
                                          const T *__restrict__ E, int p, T dv[3], T al[3])
 {
-    constexpr int ox = 1, oy = W, oz = W * W;
+    constexpr int ox = 1, oy = W, oz = P;
     const T m4 = T(-4);
     const T e0 = E[p];
     const T Exp = e0 + E[p + ox], Exm = E[p - ox] + e0, Eyp = e0 + E[p + oy], Eym = E[p - oy] + e0,
@@ -159,12 +159,12 @@ __device__ __forceinline__ PlaneEdges<T> plane_edges(const T *c, int u, int ix)
 }
 
 // al[c] = 2 h^2 alpha_c / lam_dt alone (same sums as divF_all)
-template <typename T, int W>
+template <typename T, int W, int P = W * W>
 __device__ __forceinline__ void alpha_all(const T *__restrict__ E, int p, T al[3])
 {
     const T e0 = E[p];
     const T sx = (E[p - 1] + e0) + (e0 + E[p + 1]), sy = (E[p - W] + e0) + (e0 + E[p + W]),
-            sz = (E[p - W * W] + e0) + (e0 + E[p + W * W]);
+            sz = (E[p - P] + e0) + (e0 + E[p + P]);
     al[0] = sy + sz;
     al[1] = sx + sz;
     al[2] = sx + sy;

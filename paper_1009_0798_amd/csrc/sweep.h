@@ -1,4 +1,5 @@
-// One fused red-black sweep (eq. 19 with alpha of eqs. 21-23) of an 8^3 tile.
+// One fused red-black sweep (eq. 19 with alpha of eqs. 21-23) of an 8^3 tile, or
+// of a part of one.
 //
 // The tile and a two-cell halo are staged in LDS.  The red half-sweep is
 // computed on the tile and, redundantly, on the red cells of the first halo
@@ -27,11 +28,74 @@
 
 namespace ohm {
 
-constexpr int SWEEP_THREADS = 512;
-constexpr int TW2 = 8 + 4;               // tile edge with a two-cell halo
-constexpr int TC2 = TW2 * TW2 * TW2;
+// What one group of a sweep updates: a tile of 8 x TY x TZ cells (8^3, or a part
+// of one), staged with its two-cell halo by THREADS threads.
+template <int TY_, int TZ_>
+struct Tile {
+    static constexpr int TY = TY_, TZ = TZ_, PARTS = (8 / TY) * (8 / TZ);
+    static constexpr bool whole = PARTS == 1;
+    static constexpr int THREADS = whole ? 512 : 384;
+    static constexpr int W = 8 + 4, P = W * (TY + 4), N = P * (TZ + 4);   // row, plane and tile with the halo
+    // coarse cells under the tile and its halo, with one more layer around
+    static constexpr int CY = TY / 2 + 4, CZ = TZ / 2 + 4, NCOARSE = 8 * CY * CZ;
+    // part q of an 8^3 tile starts at these cells of it
+    static __device__ __forceinline__ int y0(int q) { return TY * (q % (8 / TY)); }
+    static __device__ __forceinline__ int z0(int q) { return TZ * (q / (8 / TY)); }
+    static __device__ __forceinline__ int at(int x, int y, int z) { return (x + 2) + W * ((y + 2) + (TY + 4) * (z + 2)); }
+    // red cells: HALF of the tile, then those beyond its faces of x, y and z
+    static constexpr int HALF = 4 * TY * TZ, FX = TY * TZ / 2, FY = 4 * TZ, FZ = 4 * TY, NRED = HALF + 2 * (FX + FY + FZ);
+    static __device__ __forceinline__ void red_cell(int u, int &x, int &y, int &z)
+    {
+        if (u < HALF) {
+            z = u / (4 * TY);
+            y = (u >> 2) % TY;
+            x = 2 * (u & 3) + ((y + z) & 1);
+        } else if (whole) {
+            const int w = u - HALF, f = w >> 5, k = w & 31;
+            const int d = f >> 1, s = (f & 1) ? 8 : -1;
+            const int bb = k >> 2, a = 2 * (k & 3) + ((s + bb) & 1);
+            if (d == 0) { x = s; y = a; z = bb; }
+            else if (d == 1) { x = a; y = s; z = bb; }
+            else { x = a; y = bb; z = s; }
+        } else if (int w = u - HALF; w < 2 * FX) {
+            const int k = w % FX;
+            x = w < FX ? -1 : 8;
+            z = k / (TY / 2);
+            y = 2 * (k % (TY / 2)) + ((x + z) & 1);
+        } else if ((w -= 2 * FX) < 2 * FY) {
+            y = w < FY ? -1 : TY;
+            z = (w >> 2) % TZ;
+            x = 2 * (w & 3) + ((y + z) & 1);
+        } else {
+            w -= 2 * FY;
+            z = w < FZ ? -1 : TZ;
+            y = (w >> 2) % TY;
+            x = 2 * (w & 3) + ((y + z) & 1);
+        }
+    }
+};
+using WholeTile = Tile<8, 8>;
 
-__device__ __forceinline__ int tix2(int x, int y, int z) { return (x + 2) + TW2 * ((y + 2) + TW2 * (z + 2)); }
+// Groups a tile is split over in a launch of `tiles`: as many as find a compute
+// unit each.  A group alone on its unit waits out its chain (neighbour list,
+// tile, red cells, black cells, store), of which the updates take longer the
+// more cells it has; with every unit taken the parts' larger share of halo
+// cells costs more than that gives.  FP64 steps with the base level's tiles
+// whole, halved and quartered: 32^3 (64 tiles) 1189, 1147 and 1127 us, 40^3
+// (125) 1332, 1294 and 1330, 48^3 (216) 1977, 2007 and 2119; with the dense
+// levels of a 64^3 box (64, 8 and 1 tiles): 2240, 2119 and 2020.  A quarter's
+// sweep at 32^3 takes 4.9 us where the whole tile's took 6.1.
+constexpr int COMPUTE_UNITS = 256;
+inline int tile_parts(int tiles) { return 4 * tiles <= COMPUTE_UNITS ? 4 : 2 * tiles <= COMPUTE_UNITS ? 2 : 1; }
+
+// The cells of an 8^3 tile as seen from the part at (0, y0, z0)
+template <typename Addr>
+struct PartAddr : Addr {
+    int y0, z0;
+    __device__ __forceinline__ long long at(int x, int y, int z) const { return Addr::at(x, y + y0, z + z0); }
+    __device__ __forceinline__ int entry(int x, int y, int z) const { return Addr::entry(x, y + y0, z + z0); }
+    __device__ __forceinline__ int local(int x, int y, int z) const { return Addr::local(x, y + y0, z + z0); }
+};
 
 __device__ __forceinline__ int wrap_cell(int i, int n)
 {
@@ -79,40 +143,44 @@ __device__ __forceinline__ void store_at(T *base, unsigned off, T v)
 }
 
 // Trilinear correction (27/9/3/1 over 64) from the next coarser grid, a dense
-// grid q, for the tile of fine origin 8 (i, j, k): the 8^3 coarse cells that
-// hold the parents of the tile's cells and their neighbours (origin
-// 4 (i, j, k) - 2, periodic) are staged in LDS; the weights and the order of
-// the sum are those of the stand-alone prolongation kernels.
-template <typename T>
+// grid q, for the tile of fine origin (i, j, k): the coarse cells that hold the
+// parents of the tile's cells and their neighbours (origin (i, j, k) / 2 - 2,
+// periodic) are staged in LDS; the weights and the order of the sum are those
+// of the stand-alone prolongation kernels.
+template <typename T, typename Tl = WholeTile>
 struct TileCoarse {
     static constexpr bool active = true;
+    static constexpr int N = 3 * Tl::NCOARSE, PER = (N + Tl::THREADS - 1) / Tl::THREADS;
     const T *coarse;
     long long ccs;
     DenseProbDev q;
     int i0, j0, k0;
-    T *sC;      // [3][512] in LDS
-    T r[3];
+    T *sC;      // [N] in LDS
+    T r[PER];
     __device__ __forceinline__ void load()
     {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const int t = threadIdx.x + SWEEP_THREADS * k, c = t >> 9, m = t & 511;
-            const int i = wrap_cell(i0 + (m & 7), q.nx), j = wrap_cell(j0 + ((m >> 3) & 7), q.ny),
-                      kk = wrap_cell(k0 + (m >> 6), q.nz);
+        for (int k = 0; k < PER; ++k) {
+            unsigned t = threadIdx.x + Tl::THREADS * k;
+            if (N % Tl::THREADS) t = min(t, (unsigned)N - 1);
+            const unsigned c = t / Tl::NCOARSE, m = t % Tl::NCOARSE;
+            const int i = wrap_cell(i0 + (int)(m & 7), q.nx), j = wrap_cell(j0 + (int)((m >> 3) % Tl::CY), q.ny),
+                      kk = wrap_cell(k0 + (int)(m / (8 * Tl::CY)), q.nz);
             r[k] = coarse[c * ccs + q.off + i + (long long)q.nx * (j + (long long)q.ny * kk)];
         }
     }
     __device__ __forceinline__ void stage()
     {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) sC[threadIdx.x + SWEEP_THREADS * k] = r[k];
+        for (int k = 0; k < PER; ++k)
+            if (N % Tl::THREADS == 0 || (int)threadIdx.x + Tl::THREADS * k < N) sC[threadIdx.x + Tl::THREADS * k] = r[k];
     }
     __device__ __forceinline__ T add(int x, int y, int z, int c, T base) const
     {
         const int i = (x >> 1) + 2, j = (y >> 1) + 2, k = (z >> 1) + 2;
         const int i1 = i + ((x & 1) ? 1 : -1), j1 = j + ((y & 1) ? 1 : -1), k1 = k + ((z & 1) ? 1 : -1);
-        const T *C = sC + 512 * c;
-        auto at = [](int a, int bb, int cc) { return a + 8 * (bb + 8 * cc); };
+        const T *C = sC + Tl::NCOARSE * c;
+        auto at = [](int a, int bb, int cc) { return a + 8 * (bb + Tl::CY * cc); };
         T v = T(27) * C[at(i, j, k)] + T(9) * (C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)]) +
               T(3) * (C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)]) + C[at(i1, j1, k1)];
         v *= T(1.0 / 64.0);
@@ -130,35 +198,81 @@ __device__ __forceinline__ void lds_load16(const void *src, void *dst)
                                      (void __attribute__((address_space(3))) *)dst, 16, 0, 0);
 }
 
-template <typename T, bool ZERO, typename Addr, typename Coarse = NoCoarse<T>, typename TO = T, int TS = TC2,
-          bool DIRECT = false>
+template <typename T, bool ZERO, typename Addr, typename Coarse = NoCoarse<T>, typename TO = T,
+          typename Tl = WholeTile, int TS = Tl::N, bool DIRECT = false>
 __device__ __forceinline__ void fused_sweep_tile(const Addr &A, const T *__restrict__ B, long long cs,
                                                  const T *__restrict__ S, const T *__restrict__ eta,
                                                  TO *__restrict__ out, const T cih2, T (*sB)[TS], T *sE,
                                                  Coarse cor = Coarse())
 {
+    constexpr int TY = Tl::TY, TZ = Tl::TZ, THREADS = Tl::THREADS;
     const int u = threadIdx.x;
     const T *B0 = B, *B1 = ZERO ? B : B + cs, *B2 = ZERO ? B : B + 2 * cs;
     const T *S0 = S, *S1 = S + cs, *S2 = S + 2 * cs;
+    constexpr int HALF = Tl::HALF;
+    const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
+    auto load_s = [&] __device__(T v[3], int x, int y, int z) {
+        const unsigned off = (unsigned)A.at(x, y, z) * (unsigned)sizeof(T);
+        v[0] = load_at(S0, off);
+        v[1] = load_at(S1, off);
+        v[2] = load_at(S2, off);
+    };
+    // This thread's black cell (u < HALF) and its red one (as red_cell) in the
+    // tile (-1: none) with their S.  A part of a tile requests S together with
+    // the tile: a launch of parts has too few groups to hide a cold load
+    // behind another group's updates.
+    T srd[3], sbk[3], red[3];
+    int rp = -1, pb = -1;
+    auto red_start = [&] __device__() {
+        int x, y, z;
+        Tl::red_cell(u, x, y, z);
+        if constexpr (Addr::ghosts)
+            if (u >= HALF && A.entry(x, y, z) < 0) return;
+        rp = Tl::at(x, y, z);
+        load_s(srd, x, y, z);
+    };
+    auto red_update = [&] __device__() {
+        T al[3];
+        if (ZERO) {
+            alpha_all<T, Tl::W, Tl::P>(sE, rp, al);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) red[c] = relax_div(srd[c], fma(c2, al[c], T(1)));
+        } else {
+            T dv[3];
+            divF_all<T, Tl::W, Tl::P>(sB[0], sB[1], sB[2], sE, rp, dv, al);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) red[c] = relax_point(sB[c][rp], srd[c], dv[c], al[c], c8, c2);
+        }
+    };
+    auto black_start = [&] __device__() {
+        const int z = u / (4 * TY), y = (u >> 2) % TY, x = 2 * (u & 3) + (1 - ((y + z) & 1));
+        pb = Tl::at(x, y, z);
+        load_s(sbk, x, y, z);
+    };
+    if constexpr (!Tl::whole) {
+        if (u < Tl::NRED) red_start();
+        if (u < HALF) black_start();
+    }
     if constexpr (DIRECT) {
-        // FP64 tile pairs loaded straight into LDS: pair P = u + 512 k of
-        // the 864 (plane-major, as tix2 lays them out) lands at element 2 P,
-        // which is lane order within each wavefront; the lanes past the last
-        // pair reload pair 863 into 64 elements of padding (TS >= TC2 + 64)
-        static_assert(sizeof(T) == 8 && !ZERO && !Addr::ghosts && !Coarse::active && TS >= TC2 + 64,
+        // FP64 tile pairs loaded straight into LDS: pair P = u + THREADS k of
+        // the NP (plane-major, as the tile lays them out) lands at element 2 P,
+        // which is lane order within each wavefront; lanes past the last pair
+        // (of the 864 of a whole tile) reload it into 64 elements of padding
+        constexpr int NPC = Tl::P / 2, NP = Tl::N / 2;
+        static_assert(sizeof(T) == 8 && !ZERO && !Addr::ghosts && !Coarse::active &&
+                          TS >= Tl::N + (NP % 64 ? 64 : 0),
                       "direct tile loads are for plain FP64 sweeps");
-        constexpr int NPC = (TW2 / 2) * TW2, NP = NPC * TW2;
         const int w = u >> 6;
         // the waves of a group that issues its tile's loads take precedence
         // over the other resident group's updates until the loads are out
         __builtin_amdgcn_s_setprio(3);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int first = SWEEP_THREADS * k + 64 * w;
+        for (int k = 0; k < (NP + THREADS - 1) / THREADS; ++k) {
+            const int first = THREADS * k + 64 * w;
             if (first < NP) {
-                const int P = min(u + SWEEP_THREADS * k, NP - 1);
+                const int P = min(u + THREADS * k, NP - 1);
                 const int pc = P % NPC, z = P / NPC - 2;
-                const int x = 2 * (pc % (TW2 / 2)) - 2, y = pc / (TW2 / 2) - 2;
+                const int x = 2 * (pc % (Tl::W / 2)) - 2, y = pc / (Tl::W / 2) - 2;
                 const unsigned off = (unsigned)A.at(x, y, z) * (unsigned)sizeof(T);
                 lds_load16((const char *)B0 + off, &sB[0][2 * first]);
                 lds_load16((const char *)B1 + off, &sB[1][2 * first]);
@@ -171,19 +285,20 @@ __device__ __forceinline__ void fused_sweep_tile(const Addr &A, const T *__restr
         __syncthreads();
     } else {
     // tile load in pairs of x-neighbours (x even, so a pair never straddles a
-    // block or a periodic wrap and is 2 sizeof(T) aligned): thread u < 432
-    // owns pair column (px, y) = u mod 72 and the planes z = 2 (u / 72) - 2
-    // and the next one; all global loads first, then the LDS stores
-    constexpr int NPC = (TW2 / 2) * TW2;     // pair columns per plane
-    const bool loader = u < 6 * NPC;
+    // block or a periodic wrap and is 2 sizeof(T) aligned): a loader (the
+    // first 432 threads of a whole tile) owns pair column (px, y) = u mod NPC
+    // and EACH planes; all global loads first, then the LDS stores
+    constexpr int NPC = Tl::P / 2;           // pair columns per plane
+    constexpr int EACH = NPC * (TZ + 4) > THREADS ? 2 : 1;
+    const bool loader = u < (TZ + 4) / EACH * NPC;
     const int pc = u % NPC, zq = u / NPC;
-    const int x = 2 * (pc % (TW2 / 2)) - 2, y = pc / (TW2 / 2) - 2;
-    Pair<T> v[2][4];
+    const int x = 2 * (pc % (Tl::W / 2)) - 2, y = pc / (Tl::W / 2) - 2;
+    Pair<T> v[EACH][4];
     if (Coarse::active) cor.load();
     if (loader) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int z = 2 * zq + k - 2;
+        for (int k = 0; k < EACH; ++k) {
+            const int z = EACH * zq + k - 2;
             if constexpr (Addr::ghosts) {
                 const int n = A.entry(x, y, z);
                 const bool g = n < 0;
@@ -212,9 +327,9 @@ __device__ __forceinline__ void fused_sweep_tile(const Addr &A, const T *__restr
     }
     if (loader) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int z = 2 * zq + k - 2;
-            const int t = tix2(x, y, z);
+        for (int k = 0; k < EACH; ++k) {
+            const int z = EACH * zq + k - 2;
+            const int t = Tl::at(x, y, z);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 Pair<T> w;
@@ -227,79 +342,40 @@ __device__ __forceinline__ void fused_sweep_tile(const Addr &A, const T *__restr
     }
     __syncthreads();
     }
-    const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
-    // the black cell of this thread and its S values, loaded before the red
-    // half-sweep so that their latency overlaps it
-    int pb = -1;
-    T sbk[3];
-    if (u < 256) {
-        const int z = u >> 5, y = (u >> 2) & 7, x = 2 * (u & 3) + (1 - ((y + z) & 1));
-        pb = tix2(x, y, z);
-        const unsigned off = (unsigned)A.at(x, y, z) * (unsigned)sizeof(T);
-        sbk[0] = load_at(S0, off);
-        sbk[1] = load_at(S1, off);
-        sbk[2] = load_at(S2, off);
-    }
-    // red half-sweep: thread u < 256 takes tile cell u of the red colour,
-    // 256 <= u < 448 a red first-layer face cell
-    T red[3];
-    int rp = -1;
-    if (u < 448) {
-        int x, y, z;
-        if (u < 256) {
-            z = u >> 5;
-            y = (u >> 2) & 7;
-            x = 2 * (u & 3) + ((y + z) & 1);
-        } else {
-            const int w = u - 256, f = w >> 5, k = w & 31;
-            const int d = f >> 1, s = (f & 1) ? 8 : -1;
-            const int bb = k >> 2, a = 2 * (k & 3) + ((s + bb) & 1);
-            if (d == 0) { x = s; y = a; z = bb; }
-            else if (d == 1) { x = a; y = s; z = bb; }
-            else { x = a; y = bb; z = s; }
+    // red half-sweep; a whole tile requests the black cells' S here, to overlap
+    // with it
+    if constexpr (Tl::whole) {
+        if (u < HALF) black_start();
+        if (u < Tl::NRED) {
+            red_start();
+            if (!Addr::ghosts || rp >= 0) red_update();
         }
-        bool upd = true;
-        if constexpr (Addr::ghosts) upd = u < 256 || A.entry(x, y, z) >= 0;
-        if (upd) {
-            rp = tix2(x, y, z);
-            const unsigned off = (unsigned)A.at(x, y, z) * (unsigned)sizeof(T);
-            const T s3[3] = {load_at(S0, off), load_at(S1, off), load_at(S2, off)};
-            T al[3];
-            if (ZERO) {
-                alpha_all<T, TW2>(sE, rp, al);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) red[c] = relax_div(s3[c], fma(c2, al[c], T(1)));
-            } else {
-                T dv[3];
-                divF_all<T, TW2>(sB[0], sB[1], sB[2], sE, rp, dv, al);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) red[c] = relax_point(sB[c][rp], s3[c], dv[c], al[c], c8, c2);
-            }
-        }
+    } else if (rp >= 0) {
+        red_update();
     }
     __syncthreads();
     if (rp >= 0)
 #pragma unroll
         for (int c = 0; c < 3; ++c) sB[c][rp] = red[c];
     __syncthreads();
-    // black half-sweep on the tile (threads 0..255)
+    // black half-sweep on the tile
     {
         T blk[3];
-        if (u < 256) {
+        if (u < HALF) {
             T dv[3], al[3];
-            divF_all<T, TW2>(sB[0], sB[1], sB[2], sE, pb, dv, al);
+            divF_all<T, Tl::W, Tl::P>(sB[0], sB[1], sB[2], sE, pb, dv, al);
 #pragma unroll
             for (int c = 0; c < 3; ++c) blk[c] = relax_point(sB[c][pb], sbk[c], dv[c], al[c], c8, c2);
         }
         __syncthreads();
-        if (pb >= 0)
+        if (u < HALF)
 #pragma unroll
             for (int c = 0; c < 3; ++c) sB[c][pb] = blk[c];
     }
     __syncthreads();
-    {
-        const int x = u & 7, y = (u >> 3) & 7, z = u >> 6;
-        const int p = tix2(x, y, z);
+    if (Tl::whole || u < 8 * TY * TZ) {
+        const int x = u & 7, y = (u >> 3) % TY, z = u / (8 * TY);
+        const int p = Tl::at(x, y, z);
         const unsigned off = (unsigned)A.at(x, y, z) * (unsigned)sizeof(TO);
         store_at(out, off, TO(sB[0][p]));
         store_at(out + cs, off, TO(sB[1][p]));
