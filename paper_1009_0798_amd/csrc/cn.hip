@@ -854,6 +854,10 @@ struct Solver {
         const int L = nlev();
         for (int k = 0; k < nsteps; ++k) {
             OHM_TRY(composite(P.x, P.p, MODE_APPLY, neg_lam_dt, neg_lam_dt, 0));    // p = x - dt div F(x)
+            if (L == 1) {   // x = (x + p - dt div F(p)) / 2 in one pass (AMR: refluxing comes between)
+                OHM_TRY(composite(P.p, P.x, MODE_MEAN, neg_lam_dt, neg_lam_dt, 0));
+                continue;
+            }
             OHM_TRY(composite(P.p, P.v, MODE_APPLY, neg_lam_dt, neg_lam_dt, 0));    // v = p - dt div F(p)
             OHM_TRY(vmean2((int)P.NBt, mlprob, nullptr, VN, at<double>(P.x), at<double>(P.v), st));
         }

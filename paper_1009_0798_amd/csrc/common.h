@@ -210,7 +210,8 @@ inline DenseList dense_list(const ohm_hier *h, const DenseLevelDev &D, const int
 inline const int *problem_table(const ohm_hier *h, const AmrLevelDev &L) { return h->nprob == 1 ? nullptr : L.prob; }
 
 // launchers implemented in the kernel translation units ----------------------
-enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_SMOOTH = 2, MODE_RESID_RESTRICT = 3 };
+// MODE_MEAN: out = (out + L B) / 2
+enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_SMOOTH = 2, MODE_RESID_RESTRICT = 3, MODE_MEAN = 4 };
 
 // Colour classes of the smoother's orderings, in level-global cell indices
 // (block-local indices have the same parities, block origins being multiples

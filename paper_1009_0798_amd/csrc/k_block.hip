@@ -110,7 +110,7 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
     // values read per cell after the stencil (S, or the other vector of the
     // first fused dot product that has one), loaded with the tile so that
     // their latency overlaps it
-    constexpr bool HAS_S = MODE == MODE_RESID || MODE == MODE_RESID_RESTRICT || MODE == MODE_SMOOTH;
+    constexpr bool HAS_S = MODE != MODE_APPLY;   // MODE_MEAN: the old value of out
     T pS[2][3];
     double pY[2][3];
     int qy = -1;
@@ -118,7 +118,8 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) pS[half][c] = S[c * cs + (long long)b * NC + threadIdx.x + 256 * half];
+            for (int c = 0; c < 3; ++c)
+                pS[half][c] = (MODE == MODE_MEAN ? out : S)[c * cs + (long long)b * NC + threadIdx.x + 256 * half];
     }
     if (MODE == MODE_APPLY) {
         for (int q = dots.ndot - 1; q >= 0; --q)
@@ -151,6 +152,8 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
             if (MODE == MODE_APPLY) {
                 o[half][c] = zero ? T(0) : LB;
                 out[c * cs + gi] = o[half][c];
+            } else if (MODE == MODE_MEAN) {
+                out[c * cs + gi] = T(0.5) * (pS[half][c] + LB);
             } else if (MODE == MODE_RESID_RESTRICT) {
                 o[half][c] = zero ? T(0) : pS[half][c] - LB;
             } else if (MODE == MODE_RESID) {
@@ -678,6 +681,10 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
     case MODE_APPLY: k_blk_stencil<T, MODE_APPLY><<<grid, blk, 0, s>>>(ARGS); break;
     case MODE_RESID: k_blk_stencil<T, MODE_RESID><<<grid, blk, 0, s>>>(ARGS); break;
     case MODE_SMOOTH: k_blk_stencil<T, MODE_SMOOTH><<<grid, blk, 0, s>>>(ARGS); break;
+    case MODE_MEAN:
+        if (cov_zero) return fail(OHM_ERR_ARG, "the mean with an application is for levels without covered cells");
+        k_blk_stencil<T, MODE_MEAN><<<grid, blk, 0, s>>>(ARGS);
+        break;
     default: return fail(OHM_ERR_ARG, "unknown stencil mode %d", mode);
     }
 #undef ARGS
