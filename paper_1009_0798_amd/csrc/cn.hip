@@ -200,8 +200,8 @@ struct Solver {
 
     // y = L x (lam dt) followed by the per-problem dots (xs[q], ys[q]), where
     // every xs[q] or ys[q] is y itself or another vector.  One level: the dot
-    // partials come out of the operator kernel (same summation order as the
-    // dot kernel); AMR: the refluxed operator first, then the dot kernel.
+    // partials come out of the operator kernel; AMR: the refluxed operator
+    // first, then the dot kernel.
     ohm_status apply_dots(size_t xo, size_t yo, const double *const *xs, const double *const *ys, int nq,
                           int stage = -1)
     {

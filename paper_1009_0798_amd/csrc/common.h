@@ -229,8 +229,8 @@ __device__ __forceinline__ bool in_colour(int i, int j, int k, int colour)
 
 // Optional work fused into the block stencil kernel.  MODE_APPLY with ndot > 0
 // also writes per-block partial dot products of the output with dot_y[q]
-// (nullptr: with the output itself) to dot_part[block][ndot], summed in the
-// same order as the stand-alone dot kernel.
+// (nullptr: with the output itself) to dot_part[block][ndot], summed up each
+// column of cells, then over the columns.
 struct StencilDots {
     const double *dot_y[2];
     int ndot;
@@ -262,6 +262,13 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
                             const T *coarse = nullptr, long long ccs = 0, const T *Bg = nullptr, long long gcs = 0,
                             const T *etag = nullptr, double *out64 = nullptr);
 
+// the block stencil (modes APPLY, RESID, MEAN, and RESID_RESTRICT into a coarse
+// field of component stride ccs) of a base level with marching tables; dots: of
+// the vectors in dot_y exactly one is given
+template <typename T>
+ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long long cs, const T *S, const T *eta,
+                                const double *coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
+                                StencilDots dots = StencilDots{{nullptr, nullptr}, 0, nullptr});
 template <typename T, typename TO>
 ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
                               const double *coef_dev, TO *out, const int *active, hipStream_t s);

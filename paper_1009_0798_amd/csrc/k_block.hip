@@ -93,7 +93,7 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
               T *__restrict__ out, int colour, double *__restrict__ partials, StencilDots dots,
               const int *__restrict__ dense_map, const DenseProbDev *__restrict__ dp, long long ccs)
 {
-    __shared__ T sB[3][TC];
+    __shared__ __align__(8) T sB[3][TC];
     __shared__ T sE[1][TC];
     __shared__ int snbr[27];
     __shared__ double sred[6][4];
@@ -170,27 +170,32 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
         }
     }
     if (MODE == MODE_APPLY && dots.ndot > 0) {
-        // the stand-alone dot kernel's order: thread t sums its elements
-        // (component 0, cells t and t + 256), (component 1, ...), (component 2, ...)
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        for (int q = 0; q < dots.ndot; ++q) {
-            double acc = 0.0;
+        // column (x, y) of the block, plane by plane, then the 64 columns (the
+        // order of the marching stencil): a plane's products of each column go
+        // through LDS, where the tile is no longer needed
+        double *col = (double *)sB;
+        __syncthreads();
+        for (int q = 0; q < dots.ndot; ++q)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
+            for (int half = 0; half < 2; ++half) {
+                double acc = 0.0;
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
+                for (int c = 0; c < 3; ++c) {
                     const long long gi = (long long)b * NC + threadIdx.x + 256 * half;
                     const double y = q == qy ? pY[half][c]
                                      : (dots.dot_y[q] ? dots.dot_y[q][c * cs + gi] : (double)o[half][c]);
                     acc += (double)o[half][c] * y;
                 }
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-            if (lane == 0) sred[q][wv] = acc;
-        }
+                col[NC * q + threadIdx.x + 256 * half] = acc;
+            }
         __syncthreads();
-        if (threadIdx.x < dots.ndot) {
-            const int q = threadIdx.x;
-            dots.dot_part[(long long)b * dots.ndot + q] = ((sred[q][0] + sred[q][1]) + sred[q][2]) + sred[q][3];
+        const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        if (q < dots.ndot) {
+            double a = col[NC * q + lane];
+#pragma unroll
+            for (int z = 1; z < NB; ++z) a += col[NC * q + lane + 64 * z];
+            for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+            if (lane == 0) dots.dot_part[(long long)b * dots.ndot + q] = a;
         }
     }
     if (MODE == MODE_RESID_RESTRICT) {
@@ -664,6 +669,15 @@ k_reduce_blocks(int nprob, int nrange, const long long *__restrict__ range, cons
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// Base levels that take the marching sweeps take the marching stencil too, up
+// to the 4 GiB a component that its 32-bit offsets reach.  L B on smaller
+// levels, us, per block / marching in segments of one block: 64^3 9.8 / 10.9,
+// 96^3 18.5 / 16.6, 112^3 25.0 / 23.5 -- too little for tables of its own.
+static bool march_stencil(const AmrLevelDev &L, size_t elem)
+{
+    return L.nmarch > 0 && (unsigned long long)L.nb * NC * elem <= 0xFFFFFFFFull;
+}
+
 template <typename T>
 ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *Bg, long long cs,
                               long long gcs, const T *S, const T *eta, const T *etag, const double *coef_dev,
@@ -674,6 +688,10 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
     if (L.nb == 0) return OHM_OK;
     if (dots.ndot < 0 || dots.ndot > 2 || (dots.ndot > 0 && (mode != MODE_APPLY || !dots.dot_part)))
         return fail(OHM_ERR_ARG, "fused dot products need MODE_APPLY, 1 or 2 products and a partials buffer");
+    const int given = (dots.ndot > 0 && dots.dot_y[0]) + (dots.ndot > 1 && dots.dot_y[1]);
+    if (level == 0 && march_stencil(L, sizeof(T)) && !cov_zero && !partials && out && mode != MODE_SMOOTH &&
+        (dots.ndot == 0 || (given == 1 && std::is_same<T, double>::value)))
+        return launch_march_stencil<T>(h, mode, B, cs, S, eta, coef_dev, out, 0, active, s, dots);
     dim3 grid(L.nb), blk(256);
 #define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, out, colour, \
              partials, dots, nullptr, nullptr, 0
@@ -699,6 +717,8 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     const AmrLevelDev &L = h->amr[0];
     if (L.nb == 0) return OHM_OK;
     if (h->min_level > -1) return fail(OHM_ERR_ARG, "no dense level below level 0");
+    if (march_stencil(L, sizeof(T)))
+        return launch_march_stencil<T>(h, MODE_RESID_RESTRICT, B, cs, S, eta, coef_dev, coarse, ccs, active, s);
     k_blk_stencil<T, MODE_RESID_RESTRICT><<<L.nb, 256, 0, s>>>(
         L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
         nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs);

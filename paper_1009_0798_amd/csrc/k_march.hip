@@ -17,6 +17,8 @@
 // Measured per launch on one box, us, sweep per block -> this kernel: FP64
 // 128^3 56 -> 44, 160x128x192 119 -> 83, 256^3 515 -> 324 (2.6 -> 4.1 TB/s of
 // algorithmic bytes); FP32 35 -> 29, 56 -> 42, 287 -> 193.
+#include <type_traits>
+
 #include "march.h"
 #include "stencil.h"
 #include "sweep.h"
@@ -65,6 +67,16 @@ __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, unsigned of
 {
     typedef unsigned __attribute__((ext_vector_type(2))) u2;
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, 0, 0);
+}
+
+__device__ __forceinline__ void store_one(__amdgpu_buffer_rsrc_t r, unsigned off, double v)
+{
+    typedef unsigned __attribute__((ext_vector_type(2))) u2;
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, off, 0, 0);
+}
+__device__ __forceinline__ void store_one(__amdgpu_buffer_rsrc_t r, unsigned off, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0, 0);
 }
 
 // LDS rings of planes, plane q in slot (q - first plane) mod 4 (mod 2 for the
@@ -317,6 +329,271 @@ k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restr
     }
 }
 
+// ---------------------------------------------------------------------------
+// Plane-marching operator (eqs. 8-11) of the base level: L B, the residual and
+// what the block stencil kernel computes with them, on the same column
+// segments.  At step q plane q of B and eta with a halo of one cell goes to a
+// ring of four in LDS, and plane q - 1 is computed and written: a thread's
+// own column above and below is in its registers, and a z face's flux is
+// formed once for the two planes it separates.  The sums are those of the
+// block stencil kernel on the same values, hence the same bits.
+//
+// A wavefront takes one block's 8 x 8 cells of the plane (its loads and stores
+// are whole runs of 64 cells), plus one array's halo cells around the tile.
+// Rows of 24 elements in LDS: the rows of 8 consecutive cells that a read
+// touches at once start 8 apart modulo 16 (32 in FP32), no bank meets twice.
+//
+// What bounds it: HBM, at the rate of a large copy.  Per cell it asks for 1.1
+// instead of 2.3 lines of each array, two planes ahead.  Per launch on one box,
+// us, per block -> this kernel: FP64 128^3 with two dot products 42.3 -> 38.0
+// (4.9 TB/s of algorithmic bytes), residual + restriction 33.8 -> 26.7,
+// residual 40.7 -> 35.8; 256^3 L B 305 -> 216 (4.4 TB/s); 64 FP32 problems of
+// 16^3 to 64^3, residual + restriction 41.2 -> 34.7.  A dot product adds up per
+// lane over a block's eight planes: one reduction over the lanes per block (one
+// per plane instead: 40.0 us).
+// ---------------------------------------------------------------------------
+constexpr int SW = 24, SP = SW * (MT + 2);   // row and plane of one array in LDS
+
+// the value of lane l ^ 1 (quad permutation 1, 0, 3, 2) or l ^ 8 (rotation of
+// the 16 lanes of a row by 8)
+constexpr int LANES_XOR1 = 0xB1, LANES_XOR8 = 0x128;
+template <int CTRL>
+__device__ __forceinline__ float lanes(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lanes(double v)
+{
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true),
+                   hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
+
+// this thread's cell of a plane, and the z face below it: differences of B_x and
+// B_y across it and along x and y, sum of the resistivity
+template <typename T>
+struct Plane {
+    T b[3], e, fx, fy, Ez;
+};
+
+template <typename T, int MODE, bool DOTS>
+__global__ void __launch_bounds__(MARCH_THREADS, 2)
+k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
+                const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+                const T *__restrict__ B, long long cs, const T *S, const T *__restrict__ eta, T *out, unsigned obytes,
+                StencilDots dots, unsigned pbytes, const int *__restrict__ dense_map,
+                const DenseProbDev *__restrict__ dp, long long ccs)
+{
+    constexpr bool HAS_S = MODE != MODE_APPLY || DOTS, RESTRICT = MODE == MODE_RESID_RESTRICT;
+    constexpr int NID = 16 * (MARCH_MAX_NBZ + 2);
+    __shared__ T sh[4][4][SP];
+    __shared__ int ids[NID];
+    __shared__ int cmap[RESTRICT ? NID : 1];
+    const int w = blockIdx.x, q8 = ntile / NXCD, r8 = ntile % NXCD, xc = w % NXCD;
+    const MarchTile &M = tiles[xc * q8 + min(xc, r8) + w / NXCD];
+    const int pr = M.prob;
+    const int nbx = M.nx, nby = M.ny, nbz = M.nz;
+    const bool on = !(active && !active[pr]);
+    const int ex = min(MT, 8 * (nbx - M.bx)), ey = min(MT, 8 * (nby - M.by));
+    const int z0 = 8 * M.bz, n = 8 * M.nbz;
+    for (int t = threadIdx.x; t < 16 * (M.nbz + 2); t += MARCH_THREADS) {
+        int i = M.bx - 1 + (t & 3), j = M.by - 1 + ((t >> 2) & 3), k = M.bz - 1 + (t >> 4);
+        i = i < 0 ? i + nbx : i % nbx;
+        j = j < 0 ? j + nby : j % nby;
+        k = k < 0 ? k + nbz : k % nbz;
+        const int b = bmap[M.map + i + nbx * (j + nby * k)];
+        ids[t] = b;
+        if (RESTRICT) cmap[t] = dense_map[b];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool in = 8 * (wv & 1) < ex && 8 * (wv >> 1) < ey;   // this wavefront's block is in the box
+    const int x = (in ? 8 * (wv & 1) : 0) + (lane & 7), y = (in ? 8 * (wv >> 1) : 0) + (lane >> 3);
+    if (!on) {   // an inactive problem contributes nothing
+        if (DOTS && in)
+            for (int t = lane; t < M.nbz * dots.ndot; t += 64)
+                dots.dot_part[(long long)ids[((x + 8) >> 3) + 4 * ((y + 8) >> 3) + 16 * (t / dots.ndot + 1)] * dots.ndot +
+                              t % dots.ndot] = 0.0;
+        return;
+    }
+    const T c8 = uniform(T(coef_p[pr]) * T(inv_h2_p[pr]) * T(0.125));
+    // halo cells: the lanes of wavefront k load array k around the tile, four
+    // lanes (of each, for B_x and B_y) the tile's edges
+    const int l = lane & 15;
+    const int hx = lane < 32 ? min(l, ex - 1) : (lane < 48 ? -1 : ex), hy = lane < 32 ? (lane < 16 ? -1 : ey) : min(l, ey - 1);
+    const int cx = (lane & 1) ? ex : -1, cy = (lane & 2) ? ey : -1;
+    const T *H = wv == 3 ? eta : B + wv * cs, *C = B + (wv & 1) * cs;
+    const int u = (x + 1) + SW * (y + 1), uh = (hx + 1) + SW * (hy + 1), uc = (cx + 1) + SW * (cy + 1);
+    const T *B0 = B, *B1 = B + cs, *B2 = B + 2 * cs, *S0 = S, *S1 = S + cs, *S2 = S + 2 * cs;
+    const long long os = RESTRICT ? ccs : cs;
+    const __amdgpu_buffer_rsrc_t O0 = __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)obytes, 0x00027000),
+                                 O1 = __builtin_amdgcn_make_buffer_rsrc(out + os, 0, (int)obytes, 0x00027000),
+                                 O2 = __builtin_amdgcn_make_buffer_rsrc(out + 2 * os, 0, (int)obytes, 0x00027000),
+                                 OP = __builtin_amdgcn_make_buffer_rsrc(dots.dot_part, 0, (int)pbytes, 0x00027000);
+    struct Stage1 {
+        T b[3], e, h, c, s[3];
+    } st[2];
+    struct Off {
+        unsigned own, halo, edge;
+    };
+    const int zs = z0 - 1, zend = z0 + n + 1;                  // planes zs .. zend - 1
+    constexpr unsigned PLANE = 64 * (unsigned)sizeof(T);
+    auto column = [](int a, int b) { return ((a + 8) >> 3) + 4 * ((b + 8) >> 3); };
+    const int io = column(x, y), ih = column(hx, hy), ic = column(cx, cy);
+    auto at = [&](int i, int cell, int P) {
+        return ((unsigned)ids[i + 16 * (((P - z0) >> 3) + 1)] * (unsigned)NC + (unsigned)(cell + 64 * (P & 7))) * (unsigned)sizeof(T);
+    };
+    auto cell = [](int a, int b) { return (a & 7) + 8 * (b & 7); };
+    const int lo = cell(x, y), lh = cell(hx, hy), lc = cell(cx, cy);
+    auto next = [&](Off o, int P) -> Off {                     // offsets on plane P, given those on plane P - 1
+        if ((P & 7) == 0) return {at(io, lo, P), at(ih, lh, P), at(ic, lc, P)};
+        return {o.own + PLANE, o.halo + PLANE, o.edge + PLANE};
+    };
+    auto issue = [&](Stage1 &v, const Off &o, unsigned offs) {
+        v.b[0] = load_at(B0, o.own);
+        v.b[1] = load_at(B1, o.own);
+        v.b[2] = load_at(B2, o.own);
+        v.e = load_at(eta, o.own);
+        v.h = load_at(H, o.halo);
+        v.c = load_at(C, o.edge);
+        if (HAS_S) {
+            v.s[0] = load_at(S0, offs);
+            v.s[1] = load_at(S1, offs);
+            v.s[2] = load_at(S2, offs);
+        }
+    };
+    Off o1 = {at(io, lo, zs), at(ih, lh, zs), at(ic, lc, zs)};
+    unsigned own[4];                                           // offset of the thread's cell by plane mod 4
+    own[0] = o1.own;
+    issue(st[0], o1, own[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    o1 = next(o1, zs + 1);
+    own[1] = o1.own;
+    issue(st[1], o1, own[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    own[2] = own[3] = 0;
+    Plane<T> pl[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) pl[h] = Plane<T>{};
+    double sum[2] = {0.0, 0.0};
+    T acc[3] = {T(0), T(0), T(0)};
+    const int nd = DOTS ? dots.ndot : 0, qy = DOTS && dots.dot_y[0] ? 0 : 1;
+    const int ccell = RESTRICT ? ((lane & 7) >> 1) + dp[pr].nx * (lane >> 4) : 0, cnxy = RESTRICT ? dp[pr].nx * dp[pr].ny : 0;
+    int q0 = zs;
+    do {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            if (h == 2 && q0 + 2 >= zend) break;               // (a segment has 8 n + 2 planes)
+            __builtin_amdgcn_sched_barrier(0);
+            const int q = q0 + h;
+            const int h1 = (h + 3) & 3, h2 = (h + 2) & 3;      // planes q - 1, q - 2
+            Stage1 &v = st[h & 1];
+            T(*L)[SP] = sh[h];
+            Plane<T> &N = pl[h];
+            const Plane<T> &P = pl[h1], &Q = pl[h2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                N.b[c] = v.b[c];
+                L[c][u] = N.b[c];
+            }
+            N.e = v.e;
+            L[3][u] = N.e;
+            L[wv][uh] = v.h;
+            L[wv & 1][uc] = v.c;
+            T s[3];
+            if (HAS_S)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s[c] = v.s[c];
+            if (q + 2 < zend) o1 = next(o1, q + 2);
+            own[h2] = o1.own;                                  // (plane q - 2's slot)
+            issue(v, o1, own[(h + 1) & 3]);
+            lds_barrier();
+            const T m4 = T(-4);
+            const T *Z0 = sh[h][2] + u, *X = sh[h1][0] + u, *Y = sh[h1][1] + u, *Z = sh[h1][2] + u, *E = sh[h1][3] + u;
+            const T Exp = P.e + E[1], Exm = E[-1] + P.e, Eyp = P.e + E[SW], Eym = E[-SW] + P.e;
+            const T z_xp = Z[1], z_xm = Z[-1], z_yp = Z[SW], z_ym = Z[-SW];
+            const T x_yp = X[SW], x_ym = X[-SW], y_xp = Y[1], y_xm = Y[-1];
+            N.fx = fma(m4, N.b[0] - P.b[0], (z_xp - z_xm) + (Z0[1] - Z0[-1]));
+            N.fy = fma(m4, N.b[1] - P.b[1], (z_yp - z_ym) + (Z0[SW] - Z0[-SW]));
+            N.Ez = P.e + N.e;
+            T dv[3];
+            {
+                const T D = y_xp - y_xm;
+                const T tp = D + (Y[SW + 1] - Y[SW - 1]), tm = (Y[-SW + 1] - Y[-SW - 1]) + D;
+                const T gy = Eyp * fma(m4, x_yp - P.b[0], tp) - Eym * fma(m4, P.b[0] - x_ym, tm);
+                dv[0] = gy + fma(N.Ez, N.fx, -(P.Ez * P.fx));
+            }
+            {
+                const T D = x_yp - x_ym;
+                const T tp = D + (X[SW + 1] - X[-SW + 1]), tm = (X[SW - 1] - X[-SW - 1]) + D;
+                const T gx = Exp * fma(m4, y_xp - P.b[1], tp) - Exm * fma(m4, P.b[1] - y_xm, tm);
+                dv[1] = gx + fma(N.Ez, N.fy, -(P.Ez * P.fy));
+            }
+            {
+                const T *X0 = sh[h][0] + u, *X2 = sh[h2][0] + u, *Y0 = sh[h][1] + u, *Y2 = sh[h2][1] + u;
+                const T D = N.b[0] - Q.b[0];
+                const T tp = D + (X0[1] - X2[1]), tm = (X0[-1] - X2[-1]) + D;
+                const T gx = Exp * fma(m4, z_xp - P.b[2], tp) - Exm * fma(m4, P.b[2] - z_xm, tm);
+                const T D2 = N.b[1] - Q.b[1];
+                const T tp2 = D2 + (Y0[SW] - Y2[SW]), tm2 = (Y0[-SW] - Y2[-SW]) + D2;
+                const T gy = Eyp * fma(m4, z_yp - P.b[2], tp2) - Eym * fma(m4, P.b[2] - z_ym, tm2);
+                dv[2] = gx + gy;
+            }
+            const int p = q - 1;
+            const bool mine = in && p >= z0;
+            T r[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T LB = fma(c8, dv[c], P.b[c]);
+                r[c] = MODE == MODE_APPLY ? LB : (MODE == MODE_MEAN ? T(0.5) * (s[c] + LB) : s[c] - LB);
+            }
+            if (RESTRICT) {
+                // the mean of 8 children in the order of the restriction kernel
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const T r8 = lanes<LANES_XOR8>(r[c]);
+                    acc[c] = (h & 1) ? acc[c] + r[c] : r[c];   // plane p is even on even h
+                    acc[c] += lanes<LANES_XOR1>(r[c]);
+                    acc[c] += r8;
+                    acc[c] += lanes<LANES_XOR1>(r8);
+                }
+                if (h & 1) {
+                    const unsigned oc = mine && (lane & 9) == 0
+                                            ? (unsigned)(cmap[io + 16 * (((p - z0) >> 3) + 1)] + ccell + cnxy * ((p & 7) >> 1)) * (unsigned)sizeof(T)
+                                            : 0xFFFFFFF0u;
+                    store_one(O0, oc, acc[0] * T(0.125));
+                    store_one(O1, oc, acc[1] * T(0.125));
+                    store_one(O2, oc, acc[2] * T(0.125));
+                }
+            } else {
+                const unsigned oo = mine ? own[h1] : 0xFFFFFFF0u;
+                store_one(O0, oo, r[0]);
+                store_one(O1, oo, r[1]);
+                store_one(O2, oo, r[2]);
+            }
+            if (DOTS) {
+                // each lane its column of the block, then the 64 lanes
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    if (d >= nd) continue;
+                    double a = 0.0;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) a += (double)r[c] * (d == qy ? (double)s[c] : (double)r[c]);
+                    sum[d] = h == 2 && (p & 7) == 0 ? a : sum[d] + a;   // p = z0 - 2 + h + 4 i
+                    if (h == 1 && (p & 7) == 7) {
+                        double v = sum[d];
+                        for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+                        store_one(OP, mine && lane == 0 ? (own[h1] / PLANE / 8 * nd + d) * 8u : 0xFFFFFFF0u, v);
+                    }
+                }
+            }
+        }
+        q0 += 4;
+    } while (q0 < zend);
+}
+
 }  // namespace
 
 template <typename T, typename TO>
@@ -343,5 +620,40 @@ template ohm_status launch_march_sweep<float, float>(const ohm_hier *, const flo
 template ohm_status launch_march_sweep<float, double>(const ohm_hier *, const float *, long long, const float *,
                                                       const float *, const double *, double *, const int *,
                                                       hipStream_t);
+
+template <typename T>
+ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long long cs, const T *S, const T *eta,
+                                const double *coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
+                                StencilDots dots)
+{
+    const AmrLevelDev &L = h->amr[0];
+    const unsigned obytes = (unsigned)((mode == MODE_RESID_RESTRICT ? (unsigned long long)ccs : (unsigned long long)L.nb * NC) * sizeof(T));
+    const unsigned pbytes = (unsigned)((unsigned long long)L.nb * dots.ndot * sizeof(double));
+    const MarchTile *tiles = (const MarchTile *)L.march;
+#define RUN(mode, d, S) k_march_stencil<T, mode, d><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
+        L.inv_h2, coef_dev, B, cs, S, eta, out, obytes, dots, pbytes, L.dense_map, h->dense[1].probs, ccs)
+    switch (mode) {
+    case MODE_APPLY:
+        if constexpr (std::is_same<T, double>::value)
+            if (dots.ndot > 0) {
+                RUN(MODE_APPLY, true, (dots.dot_y[0] ? dots.dot_y[0] : dots.dot_y[1]));
+                break;
+            }
+        RUN(MODE_APPLY, false, S);
+        break;
+    case MODE_RESID: RUN(MODE_RESID, false, S); break;
+    case MODE_MEAN: RUN(MODE_MEAN, false, out); break;
+    case MODE_RESID_RESTRICT: RUN(MODE_RESID_RESTRICT, false, S); break;
+    default: return fail(OHM_ERR_ARG, "unknown marching mode %d", mode);
+    }
+#undef RUN
+    return check_launch("marching stencil");
+}
+#define INST(T)                                                                                                    \
+    template ohm_status launch_march_stencil<T>(const ohm_hier *, int, const T *, long long, const T *, const T *, \
+                                                const double *, T *, long long, const int *, hipStream_t, StencilDots);
+INST(double)
+INST(float)
+#undef INST
 
 }  // namespace ohm
