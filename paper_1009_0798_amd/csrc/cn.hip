@@ -367,10 +367,16 @@ struct Solver {
         const int d = -lev;
         const int nuc1 = o->nu_coarse > 0 ? o->nu_coarse : nu1, nuc2 = o->nu_coarse > 0 ? o->nu_coarse : nu2;
         const int f1 = zero_guess ? SMOOTH_ZERO : (ecur_of(d) == dv(P.d_tmp, d) ? SMOOTH_FROM_TMP : 0);
-        OHM_TRY(smooth_dense(d, nuc1, active, false, f1));
-        ecur[d] = dv(P.d_e, d);
-        OHM_TRY(launch_dense_resid_restrict<T>(h, -d, dv(P.d_e, d), dv(P.d_rhs, d), dv(P.d_eta, d), lam_dt,
-                                               dv(P.d_res, d), dv(P.d_rhs, d + 1), active, st));
+        if (zero_guess && nuc1 == 1 && o->ordering == 0 && dense_down_fuses(h, -d)) {
+            OHM_TRY(launch_dense_down<T>(h, -d, dv(P.d_e, d), dv(P.d_rhs, d), dv(P.d_eta, d), lam_dt, dv(P.d_rhs, d + 1),
+                                         active, st));
+            ecur[d] = dv(P.d_e, d);
+        } else {
+            OHM_TRY(smooth_dense(d, nuc1, active, false, f1));
+            ecur[d] = dv(P.d_e, d);
+            OHM_TRY(launch_dense_resid_restrict<T>(h, -d, dv(P.d_e, d), dv(P.d_rhs, d), dv(P.d_eta, d), lam_dt,
+                                                   dv(P.d_res, d), dv(P.d_rhs, d + 1), active, st));
+        }
         OHM_TRY(down_dense(d + 1));
         const T *ec = ecur_of(d + 1);
         if (nuc2 > 0 && h->dense[d].nptile == 0 && o->ordering == 0 && (!(nuc2 & 1) || may_end_in_tmp(d))) {

@@ -1,6 +1,7 @@
 // Internal declarations shared by the library's translation units.
 #pragma once
 
+#include <climits>
 #include <hip/hip_runtime.h>
 #include <cstdint>
 #include <cstdio>
@@ -106,6 +107,7 @@ struct DenseLevelDev {
     int nftile = 0, nftile_all = 0, nptile = 0, nptile_all = 0;
     int *ftiles = nullptr, *ftiles_all = nullptr, *ptiles = nullptr, *ptiles_all = nullptr;
     DenseProbDev *probs = nullptr;   // [nprob] (nx = 0 if the problem lacks the level)
+    int edge = INT_MAX;              // smallest edge of the tiled grids
     DenseProbDev one = {};           // the first problem's entry, on the host
 };
 
@@ -331,6 +333,12 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
                                int flags = 0, const T *coarse = nullptr, T **last = nullptr, int ordering = 0);
 // dense level -> next coarser: coarse = restriction of S - L B; res is scratch
 // for handles where some continuing problem is not made of 8^3 tiles
+// from a zero guess: one red-black sweep into e, its residual and restriction
+// (levels for which dense_down_fuses)
+bool dense_down_fuses(const ohm_hier *h, int level);
+template <typename T>
+ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+                             T *coarse, const int *active, hipStream_t s);
 template <typename T>
 ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B, const T *S, const T *eta,
                                        const double *coef_dev, T *res, T *coarse, const int *active, hipStream_t s);

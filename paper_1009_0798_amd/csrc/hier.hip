@@ -574,6 +574,7 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
                     }
                 }
             }
+            if (tiled) D.edge = std::min({D.edge, q.nx, q.ny, q.nz});
             if (tiled)
                 for (int t = 0; t < ntiles; ++t) {
                     ft_all.push_back(p);

@@ -333,6 +333,38 @@ k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ p
                                                                                   sB, sE, cor);
 }
 
+// residual + restriction to the first dense level by parts of the blocks of a
+// complete level 0
+template <typename T, typename Tl>
+__global__ void __launch_bounds__(Tl::THREADS)
+k_blk_down(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of, const int *__restrict__ active,
+           const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, const T *B, long long cs,
+           const T *__restrict__ S, const T *__restrict__ eta, const int *__restrict__ dense_map,
+           const DenseProbDev *__restrict__ dp, T *__restrict__ coarse, long long ccs)
+{
+    using Dn = DownTile<Tl>;
+    __shared__ T sB[3][Dn::N];
+    __shared__ T sE[Dn::N];
+    __shared__ T sR[3][Dn::CELLS];
+    __shared__ int snbr[27];
+    const int w = xcd_block(blockIdx.x, nblk * Tl::PARTS), b = w / Tl::PARTS, part = w % Tl::PARTS;
+    const int mine = load_nbr(nbr_tab, b);
+    const int pr = problem_of(prob_of, b);
+    if (active && !active[pr]) return;
+    if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
+    __syncthreads();
+    PartAddr<BlockAddr> A;
+    static_cast<BlockAddr &>(A) = BlockAddr{snbr, b};
+    A.y0 = Tl::y0(part), A.z0 = Tl::z0(part);
+    down_tile<T, false, Tl>(A, const_cast<T *>(B), cs, S, eta, T(coef_p[pr]) * T(inv_h2_p[pr]), sB, sE, sR);
+    if (threadIdx.x < 3 * Dn::NC8) {
+        const int c = threadIdx.x / Dn::NC8, m = threadIdx.x % Dn::NC8;
+        const int i = m & 3, j = A.y0 / 2 + (m >> 2) % (Tl::TY / 2), k = A.z0 / 2 + m / (2 * Tl::TY);
+        const DenseProbDev q = dp[pr];
+        coarse[c * ccs + dense_map[b] + i + (long long)q.nx * (j + (long long)q.ny * k)] = restrict_part<T, Tl>(sR[c], m);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // restriction: fine block -> the octant of its parent block (AMR levels), and
 // level-0 block -> the first dense level
@@ -719,6 +751,14 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     if (h->min_level > -1) return fail(OHM_ERR_ARG, "no dense level below level 0");
     if (march_stencil(L, sizeof(T)))
         return launch_march_stencil<T>(h, MODE_RESID_RESTRICT, B, cs, S, eta, coef_dev, coarse, ccs, active, s);
+    const int parts = tile_parts(L.nb);
+    if (parts > 1 && L.complete27 && (((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T))) == 0) {
+#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, L.dense_map, h->dense[1].probs, coarse, ccs
+        if (parts == 4) k_blk_down<T, Tile<4, 4>><<<4 * L.nb, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
+        else k_blk_down<T, Tile<8, 4>><<<2 * L.nb, Tile<8, 4>::THREADS, 0, s>>>(ARGS);
+#undef ARGS
+        return check_launch("residual + restriction by parts");
+    }
     k_blk_stencil<T, MODE_RESID_RESTRICT><<<L.nb, 256, 0, s>>>(
         L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
         nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs);

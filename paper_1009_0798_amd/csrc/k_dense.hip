@@ -233,6 +233,35 @@ k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ 
     }
 }
 
+// The way down on parts of the tiles (down_tile)
+template <typename T, bool ZERO, typename Tl>
+__global__ void __launch_bounds__(Tl::THREADS)
+k_dense_down(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p, T *e,
+             const T *__restrict__ S, const T *__restrict__ eta, T *__restrict__ coarse, long long cs, long long ccs)
+{
+    using Dn = DownTile<Tl>;
+    __shared__ T sB[3][Dn::N];
+    __shared__ T sE[Dn::N];
+    __shared__ T sR[3][Dn::CELLS];
+    const int g = blockIdx.x / Tl::PARTS, part = blockIdx.x % Tl::PARTS;
+    const int pr = list.prob(g), t = list.tile(g);
+    if (active && !active[pr]) return;
+    const DenseProbDev q = list.grid(pr);
+    DenseAddr A = dense_tile(q, t);
+    A.oy += Tl::y0(part);
+    A.oz += Tl::z0(part);
+    down_tile<T, ZERO, Tl>(A, e, cs, S, eta, T(coef_p[pr]) * T(q.inv_h2), sB, sE, sR);
+    if (threadIdx.x < 3 * Dn::NC8) {
+        const int c = threadIdx.x / Dn::NC8, m = threadIdx.x % Dn::NC8;
+        const int i = A.ox / 2 + (m & 3), j = A.oy / 2 + (m >> 2) % (Tl::TY / 2), k = A.oz / 2 + m / (2 * Tl::TY);
+        const DenseProbDev cq = clist.grid(pr);
+        // (a coarse cell past the grid's edge belongs to the tile that owns its
+        // children, which are copies here)
+        if (i < cq.nx && j < cq.ny && k < cq.nz)
+            coarse[c * ccs + cq.off + i + (long long)cq.nx * (j + (long long)cq.ny * k)] = restrict_part<T, Tl>(sR[c], m);
+    }
+}
+
 // dense level -d -> -(d+1): mean of 8 children; one thread per coarse cell
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -750,6 +779,39 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
     return OHM_OK;
 }
 
+// parts a tile is split over on the way down from a dense level, as in its
+// sweeps (1: the level takes the kernels of whole tiles); the wrap of the three
+// halo cells is for edges of 4 cells and more
+static int dense_down_parts(const ohm_hier *h, int level)
+{
+    const DenseLevelDev &D = h->dense[-level];
+    const bool ok = D.nptile == 0 && D.nftile > 0 && D.edge >= 4 && (unsigned long long)D.ncells * 8 <= 0xFFFFFFFFull;
+    return ok ? tile_parts(D.nftile) : 1;
+}
+bool dense_down_fuses(const ohm_hier *h, int level) { return dense_down_parts(h, level) > 1; }
+
+template <typename T, bool ZERO>
+static ohm_status dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+                             T *coarse, const int *active, hipStream_t s)
+{
+    const DenseLevelDev &D = h->dense[-level], &C = h->dense[-level + 1];
+#define ARGS dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active, coef_dev, e, S, eta, coarse, D.ncells, C.ncells
+    if (dense_down_parts(h, level) == 4)
+        k_dense_down<T, ZERO, Tile<4, 4>><<<4 * D.nftile, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
+    else
+        k_dense_down<T, ZERO, Tile<8, 4>><<<2 * D.nftile, Tile<8, 4>::THREADS, 0, s>>>(ARGS);
+#undef ARGS
+    return check_launch("dense way down");
+}
+
+template <typename T>
+ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+                             T *coarse, const int *active, hipStream_t s)
+{
+    if (!dense_down_fuses(h, level)) return fail(OHM_ERR_ARG, "dense level %d: too many tiles for the fused way down", level);
+    return dense_down<T, true>(h, level, e, S, eta, coef_dev, coarse, active, s);
+}
+
 template <typename T>
 ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B, const T *S, const T *eta,
                                        const double *coef_dev, T *res, T *coarse, const int *active, hipStream_t s)
@@ -761,6 +823,8 @@ ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B,
         OHM_TRY(launch_dense_stencil<T>(h, level, MODE_RESID, B, S, eta, coef_dev, res, 0, false, active, s));
         return launch_dense_restrict<T>(h, level, res, coarse, 3, active, s);
     }
+    if (dense_down_parts(h, level) > 1)
+        return dense_down<T, false>(h, level, const_cast<T *>(B), S, eta, coef_dev, coarse, active, s);
     k_dense_resid_restrict<T><<<D.nftile, 256, 0, s>>>(dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active,
                                                         coef_dev, B, S, eta, coarse, D.ncells, C.ncells);
     return check_launch("dense residual + restriction");
@@ -944,6 +1008,8 @@ size_t coarse_job_bytes() { return sizeof(CoarseJob); }
                                                  hipStream_t);                                                 \
     template ohm_status launch_dense_resid_restrict<T>(const ohm_hier *, int, const T *, const T *, const T *, \
                                                        const double *, T *, T *, const int *, hipStream_t);    \
+    template ohm_status launch_dense_down<T>(const ohm_hier *, int, T *, const T *, const T *, const double *, T *, \
+                                             const int *, hipStream_t);                                          \
     template ohm_status launch_dense_prolong<T>(const ohm_hier *, int, const T *, T *, int, int, const int *,  \
                                                 hipStream_t, const T *);                                       \
     template ohm_status launch_coarse_apply<T>(const ohm_hier *, int, const void *, int, const double *,       \

@@ -383,4 +383,140 @@ __device__ __forceinline__ void fused_sweep_tile(const Addr &A, const T *__restr
     }
 }
 
+// ---------------------------------------------------------------------------
+// The way down from a level of few tiles, by parts of a tile as the sweeps: the
+// residual S - L e with its restriction, with ZERO behind one sweep from a zero
+// guess (whose result is stored), which computes e one cell around the part.
+// Same operations on the same values as the sweep and the residual kernels.
+//
+// Such a launch is its chain of loads and updates; the sweep's launch, its
+// stores and the reload of e and eta are what putting it in front saves.  FP64
+// levels of 16^3 and 8^3: 4.1 + 6.0 -> 6.7 and 4.0 + 4.6 -> 5.7 us; without the
+// sweep (base level of 32^3) 6.0 -> 3.7 us against the kernel of whole blocks.
+// ---------------------------------------------------------------------------
+template <typename Tl>
+struct DownTile {
+    // tile and halo in LDS: rows of 16 (x from -4), y and z from -3
+    static constexpr int W = 16, P = W * (Tl::TY + 6), N = P * (Tl::TZ + 6), CELLS = 8 * Tl::TY * Tl::TZ,
+                         NC8 = CELLS / 8;   // coarse cells
+    static __device__ __forceinline__ int at(int x, int y, int z) { return (x + 4) + W * ((y + 3) + (Tl::TY + 6) * (z + 3)); }
+};
+
+// the residual goes to sR[component][cell of the part], x fastest
+template <typename T, bool ZERO, typename Tl, typename Addr>
+__device__ __forceinline__ void down_tile(const Addr &A, T *e, long long cs, const T *__restrict__ S,
+                                          const T *__restrict__ eta, const T cih2, T (*sB)[DownTile<Tl>::N], T *sE,
+                                          T (*sR)[DownTile<Tl>::CELLS])
+{
+    using Dn = DownTile<Tl>;
+    constexpr int TY = Tl::TY, TZ = Tl::TZ, THREADS = Tl::THREADS;
+    const int u = threadIdx.x;
+    auto off = [&] __device__(int x, int y, int z) { return (unsigned)A.at(x, y, z) * (unsigned)sizeof(T); };
+    auto load_s = [&] __device__(T v[3], int x, int y, int z) {
+        const unsigned o = off(x, y, z);
+        v[0] = load_at(S, o);
+        v[1] = load_at(S + cs, o);
+        v[2] = load_at(S + 2 * cs, o);
+    };
+    // eta (and e) in pairs of x-neighbours: three cells around the part (one
+    // without the sweep)
+    constexpr int H = ZERO ? 3 : 1, PW = ZERO ? 8 : 6, X0 = ZERO ? -4 : -2;
+    constexpr int NP = PW * (TY + 2 * H) * (TZ + 2 * H), PER = (NP + THREADS - 1) / THREADS;
+    Pair<T> ve[PER], vb[ZERO ? 1 : PER][3];
+    int tp[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int t = min(u + THREADS * k, NP - 1);
+        const int x = X0 + 2 * (t % PW), y = t / PW % (TY + 2 * H) - H, z = t / (PW * (TY + 2 * H)) - H;
+        const unsigned o = off(x, y, z);
+        tp[k] = Dn::at(x, y, z);
+        ve[k] = load_pair(eta, o);
+        if (!ZERO)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vb[k][c] = load_pair(e + c * cs, o);
+    }
+    // S of the cells this thread updates: red cells two around the part, black
+    // ones one around it, then a cell of the part
+    constexpr int NR = ZERO ? 6 * (TY + 4) * (TZ + 4) : 0, RPER = (NR + THREADS - 1) / THREADS, NK = 5 * (TY + 2) * (TZ + 2);
+    static_assert(NK <= THREADS && Dn::CELLS <= THREADS, "one black cell and one cell of the part per thread");
+    T sr[RPER ? RPER : 1][3], sk[3], so[3];
+    int rp[RPER ? RPER : 1], pk = 0;
+    if constexpr (ZERO) {
+#pragma unroll
+        for (int k = 0; k < RPER; ++k) {
+            const int t = min(u + THREADS * k, NR - 1);
+            const int y = t / 6 % (TY + 4) - 2, z = t / (6 * (TY + 4)) - 2, x = -2 + 2 * (t % 6) + ((y + z) & 1);
+            rp[k] = Dn::at(x, y, z);
+            load_s(sr[k], x, y, z);
+        }
+        const int t = min(u, NK - 1);
+        const int y = t / 5 % (TY + 2) - 1, z = t / (5 * (TY + 2)) - 1, x = -1 + 2 * (t % 5) + ((y + z) & 1);
+        pk = Dn::at(x, y, z);
+        load_s(sk, x, y, z);
+    }
+    const int cell = min(u, Dn::CELLS - 1), x = cell & 7, y = (cell >> 3) % TY, z = cell / (8 * TY);
+    const int po = Dn::at(x, y, z);
+    load_s(so, x, y, z);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {   // (threads past the last pair store it again)
+        *(Pair<T> *)&sE[tp[k]] = ve[k];
+        if (!ZERO)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) *(Pair<T> *)&sB[c][tp[k]] = vb[k][c];
+    }
+    const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
+    __syncthreads();
+    if constexpr (ZERO) {
+        // red: S over the diagonal; the other cell of the pair is still zero
+#pragma unroll
+        for (int k = 0; k < RPER; ++k) {
+            T al[3];
+            alpha_all<T, Dn::W, Dn::P>(sE, rp[k], al);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                sB[c][rp[k]] = relax_div(sr[k][c], fma(c2, al[c], T(1)));
+                sB[c][rp[k] ^ 1] = T(0);
+            }
+        }
+        __syncthreads();
+        T blk[3], dv[3], al[3];
+        divF_all<T, Dn::W, Dn::P>(sB[0], sB[1], sB[2], sE, pk, dv, al);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) blk[c] = relax_point(T(0), sk[c], dv[c], al[c], c8, c2);
+        __syncthreads();
+        if (u < NK)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sB[c][pk] = blk[c];
+        __syncthreads();
+    }
+    {
+        T dv[3], al[3];
+        divF_all<T, Dn::W, Dn::P>(sB[0], sB[1], sB[2], sE, po, dv, al);
+        if (u < Dn::CELLS) {
+            const unsigned o = off(x, y, z);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                sR[c][u] = so[c] - fma(c8, dv[c], sB[c][po]);
+                if (ZERO) store_at(e + c * cs, o, sB[c][po]);
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// mean of the residual over the children of coarse cell t of the part
+template <typename T, typename Tl>
+__device__ __forceinline__ T restrict_part(const T *r, int t)
+{
+    const int i = t & 3, j = (t >> 2) % (Tl::TY / 2), k = t / (2 * Tl::TY);
+    T a = T(0);
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 2; ++dx) a += r[(2 * i + dx) + 8 * ((2 * j + dy) + Tl::TY * (2 * k + dz))];
+    return a * T(0.125);
+}
+
 }  // namespace ohm
