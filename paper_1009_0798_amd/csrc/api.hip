@@ -12,9 +12,20 @@ namespace {
 
 constexpr int RING = 64;
 
-// copy per-problem host coefficients into the next device slot
-ohm_status coef_slot(ohm_hier *h, const double *host, hipStream_t s, double **dev, int *slot)
+// The host's per-problem coefficients for the launches of a call: one with the
+// kernels' arguments, more through the next slot of a device ring, which
+// coef_done hands back.
+struct CoefSlot {
+    Coef c{nullptr};
+    int slot = -1;
+};
+
+ohm_status coef_slot(ohm_hier *h, const double *host, hipStream_t s, CoefSlot *out)
 {
+    if (h->nprob == 1) {
+        out->c = Coef(host[0], h->amr[0].inv_h2);
+        return OHM_OK;
+    }
     if (!h->d_ring) {
         OHM_HIP(hipMalloc((void **)&h->d_ring, sizeof(double) * RING * h->nprob));
         for (int i = 0; i < RING; ++i) OHM_HIP(hipEventCreateWithFlags(&h->ring_ev[i], hipEventDisableTiming));
@@ -22,17 +33,18 @@ ohm_status coef_slot(ohm_hier *h, const double *host, hipStream_t s, double **de
     const int k = h->ring_pos;
     h->ring_pos = (k + 1) % RING;
     if (h->ring_live[k]) OHM_HIP(hipEventSynchronize(h->ring_ev[k]));
-    double *d = h->d_ring + (size_t)k * h->nprob;
-    OHM_HIP(hipMemcpyAsync(d, host, sizeof(double) * h->nprob, hipMemcpyHostToDevice, s));
-    *dev = d;
-    *slot = k;
+    const double *d = h->d_ring + (size_t)k * h->nprob;
+    OHM_HIP(hipMemcpyAsync((void *)d, host, sizeof(double) * h->nprob, hipMemcpyHostToDevice, s));
+    out->c = Coef(d);
+    out->slot = k;
     return OHM_OK;
 }
 
-ohm_status coef_done(ohm_hier *h, int slot, hipStream_t s)
+ohm_status coef_done(ohm_hier *h, const CoefSlot &c, hipStream_t s)
 {
-    OHM_HIP(hipEventRecord(h->ring_ev[slot], s));
-    h->ring_live[slot] = true;
+    if (c.slot < 0) return OHM_OK;
+    OHM_HIP(hipEventRecord(h->ring_ev[c.slot], s));
+    h->ring_live[c.slot] = true;
     return OHM_OK;
 }
 
@@ -72,7 +84,7 @@ long long level_cs(const ohm_hier *h, int level)
 
 template <typename T>
 ohm_status stencil(ohm_hier *h, int level, int mode, const void *B, const void *Bg, const void *S, const void *eta,
-                   const void *etag, const double *coef_dev, void *out, int colour, double *partials,
+                   const void *etag, Coef coef_dev, void *out, int colour, double *partials,
                    hipStream_t s)
 {
     if (level >= 0)
@@ -113,14 +125,13 @@ ohm_status ohm_apply(ohm_hier *h, int32_t level, const void *B, const void *B_gh
     if (B == out) return fail(OHM_ERR_ARG, "out must not alias B");
     OHM_TRY(check_coef(h, coef, "coef"));
     OHM_TRY(need_ghosts(h, level, B_ghost, eta_ghost));
-    double *cd;
-    int slot;
-    OHM_TRY(coef_slot(h, coef, stream, &cd, &slot));
+    CoefSlot cf;
+    OHM_TRY(coef_slot(h, coef, stream, &cf));
     ohm_status st = dtype == OHM_F64
-                        ? stencil<double>(h, level, MODE_APPLY, B, B_ghost, nullptr, eta, eta_ghost, cd, out, 0, nullptr, stream)
-                        : stencil<float>(h, level, MODE_APPLY, B, B_ghost, nullptr, eta, eta_ghost, cd, out, 0, nullptr, stream);
+                        ? stencil<double>(h, level, MODE_APPLY, B, B_ghost, nullptr, eta, eta_ghost, cf.c, out, 0, nullptr, stream)
+                        : stencil<float>(h, level, MODE_APPLY, B, B_ghost, nullptr, eta, eta_ghost, cf.c, out, 0, nullptr, stream);
     OHM_TRY(st);
-    return coef_done(h, slot, stream);
+    return coef_done(h, cf, stream);
 }
 
 ohm_status ohm_residual(ohm_hier *h, int32_t level, const void *B, const void *B_ghost, const void *S,
@@ -136,33 +147,23 @@ ohm_status ohm_residual(ohm_hier *h, int32_t level, const void *B, const void *B
     if (level < 0 && !R) return fail(OHM_ERR_ARG, "R is required on multigrid levels");
     OHM_TRY(check_coef(h, lam_dt, "lam_dt"));
     OHM_TRY(need_ghosts(h, level, B_ghost, eta_ghost));
-    double *cd;
-    int slot;
-    OHM_TRY(coef_slot(h, lam_dt, stream, &cd, &slot));
+    CoefSlot cf;
+    OHM_TRY(coef_slot(h, lam_dt, stream, &cf));
     double *part = norms ? h->d_part : nullptr;
     ohm_status st = dtype == OHM_F64
-                        ? stencil<double>(h, level, MODE_RESID, B, B_ghost, S, eta, eta_ghost, cd, R, 0, part, stream)
-                        : stencil<float>(h, level, MODE_RESID, B, B_ghost, S, eta, eta_ghost, cd, R, 0, part, stream);
+                        ? stencil<double>(h, level, MODE_RESID, B, B_ghost, S, eta, eta_ghost, cf.c, R, 0, part, stream)
+                        : stencil<float>(h, level, MODE_RESID, B, B_ghost, S, eta, eta_ghost, cf.c, R, 0, part, stream);
     OHM_TRY(st);
-    OHM_TRY(coef_done(h, slot, stream));
+    OHM_TRY(coef_done(h, cf, stream));
     if (norms) {
-        // one range per problem on this level
-        std::vector<long long> rg(2 * h->nprob);
-        for (int p = 0; p < h->nprob; ++p) {
-            const ohm_prob_host &P = h->probs[p];
-            rg[2 * p] = level < P.nlevels ? P.boff[level] : 0;
-            rg[2 * p + 1] = level < P.nlevels ? P.boff[level] + P.nb[level] : 0;
-        }
-        long long *d_rg = (long long *)(h->d_part + 6 * (size_t)h->nb_host[level]);
-        OHM_HIP(hipMemcpyAsync(d_rg, rg.data(), sizeof(long long) * rg.size(), hipMemcpyHostToDevice, stream));
-        OHM_TRY(launch_reduce_problem(h->nprob, 1, d_rg, h->d_part, 6, 3, h->d_norms, stream));
-        std::vector<double> tmp(6 * h->nprob);
-        OHM_HIP(hipMemcpyAsync(tmp.data(), h->d_norms, sizeof(double) * tmp.size(), hipMemcpyDeviceToHost, stream));
+        // the sums go straight to pinned memory
+        double *sums = h->h_dots + (8 + 2 * ITER_SLOTS + 6) * (size_t)h->nprob;
+        OHM_TRY(launch_reduce_problem(h->nprob, 1, h->amr[level].range, h->d_part, 6, 3, sums, stream));
         OHM_HIP(hipStreamSynchronize(stream));
         for (int p = 0; p < h->nprob; ++p)
             for (int c = 0; c < 3; ++c) {
-                norms[6 * p + 2 * c] = tmp[6 * p + c];
-                norms[6 * p + 2 * c + 1] = tmp[6 * p + 3 + c];
+                norms[6 * p + 2 * c] = sums[6 * p + c];
+                norms[6 * p + 2 * c + 1] = sums[6 * p + 3 + c];
             }
     }
     return OHM_OK;
@@ -181,9 +182,8 @@ ohm_status ohm_smooth(ohm_hier *h, int32_t level, void *B, const void *B_ghost, 
     OHM_TRY(check_coef(h, lam_dt, "lam_dt"));
     OHM_TRY(need_ghosts(h, level, B_ghost, eta_ghost));
     if (nsweeps == 0) return OHM_OK;
-    double *cd;
-    int slot;
-    OHM_TRY(coef_slot(h, lam_dt, stream, &cd, &slot));
+    CoefSlot cf;
+    OHM_TRY(coef_slot(h, lam_dt, stream, &cf));
     // one fused launch per sweep where the level's arrays fit the sweep's
     // 32-bit offsets, else one launch per colour
     const unsigned long long per = (unsigned long long)NC * (dtype == OHM_F64 ? 8 : 4), lim = 0xFFFFFFFFull;
@@ -196,27 +196,27 @@ ohm_status ohm_smooth(ohm_hier *h, int32_t level, void *B, const void *B_ghost, 
             ohm_status st =
                 dtype == OHM_F64
                     ? launch_blk_sweep<double>(h, level, (const double *)src, cs, (const double *)S,
-                                               (const double *)eta, cd, (double *)dst, nullptr, stream, nullptr, 0,
+                                               (const double *)eta, cf.c, (double *)dst, nullptr, stream, nullptr, 0,
                                                (const double *)B_ghost, gcs, (const double *)eta_ghost)
                     : launch_blk_sweep<float>(h, level, (const float *)src, cs, (const float *)S, (const float *)eta,
-                                              cd, (float *)dst, nullptr, stream, nullptr, 0, (const float *)B_ghost,
+                                              cf.c, (float *)dst, nullptr, stream, nullptr, 0, (const float *)B_ghost,
                                               gcs, (const float *)eta_ghost);
             OHM_TRY(st);
         }
         if (nsweeps & 1) OHM_HIP(hipMemcpyAsync(B, tmp, (size_t)(3 * cs) * (dtype == OHM_F64 ? 8 : 4),
                                                 hipMemcpyDeviceToDevice, stream));
-        return coef_done(h, slot, stream);
+        return coef_done(h, cf, stream);
     }
     if (level < 0) {
         ohm_status st = dtype == OHM_F64
                             ? launch_dense_smooth<double>(h, level, (double *)B, (double *)tmp, (const double *)S,
-                                                          (const double *)eta, cd, nsweeps, true, nullptr, stream, 0,
+                                                          (const double *)eta, cf.c, nsweeps, true, nullptr, stream, 0,
                                                           nullptr, nullptr, ordering)
                             : launch_dense_smooth<float>(h, level, (float *)B, (float *)tmp, (const float *)S,
-                                                         (const float *)eta, cd, nsweeps, true, nullptr, stream, 0,
+                                                         (const float *)eta, cf.c, nsweeps, true, nullptr, stream, 0,
                                                          nullptr, nullptr, ordering);
         OHM_TRY(st);
-        return coef_done(h, slot, stream);
+        return coef_done(h, cf, stream);
     }
     // one out-of-place launch per colour class, B -> tmp -> B ...: an even
     // number per sweep, so each sweep ends in B
@@ -227,12 +227,12 @@ ohm_status ohm_smooth(ohm_hier *h, int32_t level, void *B, const void *B_ghost, 
             void *dst = (c & 1) ? B : tmp;
             ohm_status st =
                 dtype == OHM_F64
-                    ? stencil<double>(h, level, MODE_SMOOTH, src, B_ghost, S, eta, eta_ghost, cd, dst, c0 + c, nullptr, stream)
-                    : stencil<float>(h, level, MODE_SMOOTH, src, B_ghost, S, eta, eta_ghost, cd, dst, c0 + c, nullptr, stream);
+                    ? stencil<double>(h, level, MODE_SMOOTH, src, B_ghost, S, eta, eta_ghost, cf.c, dst, c0 + c, nullptr, stream)
+                    : stencil<float>(h, level, MODE_SMOOTH, src, B_ghost, S, eta, eta_ghost, cf.c, dst, c0 + c, nullptr, stream);
             OHM_TRY(st);
         }
     }
-    return coef_done(h, slot, stream);
+    return coef_done(h, cf, stream);
 }
 
 ohm_status ohm_restrict(ohm_hier *h, int32_t fine_level, const void *fine, void *coarse, int32_t ncomp,
@@ -290,22 +290,21 @@ ohm_status ohm_reflux(ohm_hier *h, int32_t level, const void *B_coarse, const vo
     if (!B_coarse || !eta_coarse || !B_fine || !eta_fine || !out) return fail(OHM_ERR_ARG, "NULL field");
     OHM_TRY(need_ghosts(h, level + 1, B_fine_ghost, eta_fine_ghost));
     OHM_TRY(check_coef(h, coef, "coef"));
-    double *cd;
-    int slot;
-    OHM_TRY(coef_slot(h, coef, stream, &cd, &slot));
+    CoefSlot cf;
+    OHM_TRY(coef_slot(h, coef, stream, &cf));
     const long long ccs = level_cs(h, level), fcs = level_cs(h, level + 1), gcs = (long long)h->ng_host[level + 1] * NC;
     ohm_status st;
     if (dtype == OHM_F64)
         st = launch_reflux<double>(h, level, (const double *)B_coarse, ccs, (const double *)eta_coarse,
                                    (const double *)B_fine, fcs, (const double *)B_fine_ghost, gcs,
-                                   (const double *)eta_fine, (const double *)eta_fine_ghost, cd, (double *)out, nullptr,
+                                   (const double *)eta_fine, (const double *)eta_fine_ghost, cf.c, (double *)out, nullptr,
                                    stream);
     else
         st = launch_reflux<float>(h, level, (const float *)B_coarse, ccs, (const float *)eta_coarse,
                                   (const float *)B_fine, fcs, (const float *)B_fine_ghost, gcs, (const float *)eta_fine,
-                                  (const float *)eta_fine_ghost, cd, (float *)out, nullptr, stream);
+                                  (const float *)eta_fine_ghost, cf.c, (float *)out, nullptr, stream);
     OHM_TRY(st);
-    OHM_TRY(coef_done(h, slot, stream));
+    OHM_TRY(coef_done(h, cf, stream));
     if (zero_covered) {
         if (dtype == OHM_F64) return launch_zero_covered<double>(h, level, (double *)out, ccs, 3, stream);
         return launch_zero_covered<float>(h, level, (float *)out, ccs, 3, stream);

@@ -65,6 +65,7 @@ struct AmrLevelDev {
     int *goctant = nullptr;    // [ng] its octant
     int *gprob = nullptr;      // [ng] problem of the ghost block
     uint8_t *cov = nullptr;    // [nb] octants covered by level+1 blocks (bit x+2y+4z)
+    long long *range = nullptr;  // [nprob][2] first block of each problem and the one behind its last
     double *inv_h2 = nullptr;  // [nprob] 1 / h^2 of this level per problem (0 if absent)
     double *inv_h = nullptr;   // [nprob] 1 / h
     int *dense_map = nullptr;  // level 0 only: [nb] cell offset of the block's 4^3 coarse
@@ -162,13 +163,12 @@ struct ohm_hier {
     double *d_scal = nullptr;        // [4 * nprob]
     double *d_part = nullptr;        // reduction partials
     size_t part_cap = 0;
-    double *d_norms = nullptr;       // [nprob * 6]
     size_t table_bytes = 0;          // device bytes of the tables and scratch above
     // pinned host copies of norms: [8 * nprob] of reductions (a step's
     // start: |r|^2, |S|^2 at [0, 2 nprob); the verifying true residual at
     // [2 nprob, 3 nprob); an iteration of eqs. 16-18 at [0, nprob)), then the
     // iteration ring [2 * ITER_SLOTS * nprob], then the final norms of a
-    // step [6 * nprob]
+    // step [6 * nprob] and those of a residual call [6 * nprob]
     double *h_dots = nullptr;
     int bicg_pred = 0;               // iterations the last step's first BiCGStab pass took
     char *h_stage = nullptr;         // pinned staging of a step's host-built tables
@@ -211,6 +211,19 @@ inline DenseList dense_list(const ohm_hier *h, const DenseLevelDev &D, const int
 // block -> problem table of a launch: none for a handle of one problem
 inline const int *problem_table(const ohm_hier *h, const AmrLevelDev &L) { return h->nprob == 1 ? nullptr : L.prob; }
 
+// lambda dt (or the like) of each problem: a device array, or, for a handle of
+// one problem, a value that comes with the kernel's arguments, so that a call
+// uploads nothing (two sweeps of an FP32 40 x 24 x 56 box 19.7 -> 13.6 us).  A
+// kernel reads the array in either case (any of the handle's will do for a
+// value), without a branch; v is not a number when the array counts.
+struct Coef {
+    const double *p;
+    double v;
+    Coef(const double *dev) : p(dev), v(__builtin_nan("")) {}
+    Coef(double value, const double *any) : p(any), v(value) {}
+};
+__device__ __forceinline__ double coef_of(double x, double v) { return v == v ? v : x; }
+
 // launchers implemented in the kernel translation units ----------------------
 // MODE_MEAN: out = (out + L B) / 2
 enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_SMOOTH = 2, MODE_RESID_RESTRICT = 3, MODE_MEAN = 4 };
@@ -242,14 +255,14 @@ struct StencilDots {
 template <typename T>
 ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *Bg,
                               long long cs, long long gcs, const T *S, const T *eta, const T *etag,
-                              const double *coef_dev, T *out, int colour, double *partials,
+                              Coef coef_dev, T *out, int colour, double *partials,
                               const uint8_t *cov_zero, const int *active, hipStream_t s,
                               StencilDots dots = StencilDots{{nullptr, nullptr}, 0, nullptr});
 // level 0 -> first dense level: r = S - L e on the blocks, restricted (mean of
 // the 8 children) straight into coarse; r itself is not stored
 template <typename T>
 ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg, long long cs, long long gcs,
-                                      const T *S, const T *eta, const T *etag, const double *coef_dev, T *coarse,
+                                      const T *S, const T *eta, const T *etag, Coef coef_dev, T *coarse,
                                       long long ccs, const int *active, hipStream_t s);
 // one fused red-black sweep B -> out (levels whose every neighbour entry is a
 // level or ghost block; ghost values Bg / etag, held fixed, on levels that
@@ -260,7 +273,7 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
 // with an input): the result is written as FP64 to out64 instead of out
 template <typename T>
 ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long cs, const T *S, const T *eta,
-                            const double *coef_dev, T *out, const int *active, hipStream_t s,
+                            Coef coef_dev, T *out, const int *active, hipStream_t s,
                             const T *coarse = nullptr, long long ccs = 0, const T *Bg = nullptr, long long gcs = 0,
                             const T *etag = nullptr, double *out64 = nullptr);
 
@@ -269,15 +282,15 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
 // the vectors in dot_y exactly one is given
 template <typename T>
 ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long long cs, const T *S, const T *eta,
-                                const double *coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
+                                Coef coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
                                 StencilDots dots = StencilDots{{nullptr, nullptr}, 0, nullptr});
 template <typename T, typename TO>
 ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
-                              const double *coef_dev, TO *out, const int *active, hipStream_t s);
+                              Coef coef_dev, TO *out, const int *active, hipStream_t s);
 
 template <typename T>
 ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *S,
-                                const T *eta, const double *coef_dev, T *out, int colour,
+                                const T *eta, Coef coef_dev, T *out, int colour,
                                 bool coarsest_too, const int *active, hipStream_t s);
 
 template <typename T>
@@ -295,7 +308,7 @@ ohm_status launch_fill_ghosts(const ohm_hier *h, int level, const T *coarse, lon
 template <typename T>
 ohm_status launch_reflux(const ohm_hier *h, int level, const T *Bc, long long ccs, const T *etac,
                          const T *Bf, long long fcs, const T *Bfg, long long fgcs, const T *etaf,
-                         const T *etafg, const double *coef_dev, T *out, const int *active,
+                         const T *etafg, Coef coef_dev, T *out, const int *active,
                          hipStream_t s);
 template <typename T>
 ohm_status launch_zero_covered(const ohm_hier *h, int level, T *out, long long cs, int ncomp,
@@ -329,7 +342,7 @@ ohm_status launch_prolong_blk(const ohm_hier *h, int coarse_level, const T *coar
 enum { SMOOTH_ZERO = 1, SMOOTH_FROM_TMP = 2 };
 template <typename T>
 ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const T *S, const T *eta,
-                               const double *coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
+                               Coef coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
                                int flags = 0, const T *coarse = nullptr, T **last = nullptr, int ordering = 0);
 // dense level -> next coarser: coarse = restriction of S - L B; res is scratch
 // for handles where some continuing problem is not made of 8^3 tiles
@@ -337,11 +350,11 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
 // (levels for which dense_down_fuses)
 bool dense_down_fuses(const ohm_hier *h, int level);
 template <typename T>
-ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s);
 template <typename T>
 ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B, const T *S, const T *eta,
-                                       const double *coef_dev, T *res, T *coarse, const int *active, hipStream_t s);
+                                       Coef coef_dev, T *res, T *coarse, const int *active, hipStream_t s);
 template <typename T>
 ohm_status launch_dense_restrict(const ohm_hier *h, int fine_level, const T *fine, T *coarse, int ncomp,
                                  const int *active, hipStream_t s);

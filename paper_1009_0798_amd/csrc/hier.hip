@@ -424,6 +424,13 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
             OHM_TRY(upload(&L.goctant, goctant));
             OHM_TRY(upload(&L.gprob, gprob));
         }
+        std::vector<long long> range;
+        for (const ohm_prob_host &P : H->probs) {
+            const bool has = l < P.nlevels;
+            range.push_back(has ? P.boff[l] : 0);
+            range.push_back(has ? P.boff[l] + P.nb[l] : 0);
+        }
+        OHM_TRY(upload(&L.range, range));
         if (l == 0) {
             OHM_TRY(upload(&L.dense_map, dmap));
             OHM_TRY(march_tables(H));
@@ -603,13 +610,12 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
     // ---- scratch ---------------------------------------------------------------
     std::lock_guard<std::mutex> lock(capture_mutex());
     OHM_HIP(hipMalloc((void **)&H->d_scal, sizeof(double) * 4 * nprob));
-    OHM_HIP(hipMalloc((void **)&H->d_norms, sizeof(double) * 8 * nprob));
-    OHM_HIP(hipHostMalloc((void **)&H->h_dots, sizeof(double) * (8 + 2 * ITER_SLOTS + 6) * nprob, hipHostMallocDefault));
+    OHM_HIP(hipHostMalloc((void **)&H->h_dots, sizeof(double) * (8 + 2 * ITER_SLOTS + 12) * nprob, hipHostMallocDefault));
     size_t maxnb = 1;
     for (int l = 0; l < H->nlev; ++l) maxnb = std::max(maxnb, (size_t)H->nb_host[l]);
-    H->part_cap = maxnb * 8 + 2 * (size_t)nprob * OHM_MAX_LEVELS + 64;
+    H->part_cap = maxnb * 8 + 64;
     OHM_HIP(hipMalloc((void **)&H->d_part, sizeof(double) * H->part_cap));
-    H->table_bytes = g_up_bytes + sizeof(double) * (4 * (size_t)nprob + 8 * (size_t)nprob + H->part_cap);
+    H->table_bytes = g_up_bytes + sizeof(double) * (4 * (size_t)nprob + H->part_cap);
     H->cinv_off.assign(nprob, -1);
     H->cinv_n.assign(nprob, 0);
     H->cinv_lamdt.assign(nprob, -1.0);
@@ -622,7 +628,7 @@ static void free_all(ohm_hier *H)
     for (int l = 0; l < OHM_MAX_LEVELS; ++l) {
         AmrLevelDev &L = H->amr[l];
         void *ptrs[] = {L.nbr, L.prob, L.ijk, L.parent, L.octant, L.gparent, L.goctant, L.gprob,
-                        L.cov, L.dense_map, L.bmap, L.march, L.rf, L.rff, L.rfs, L.rfw, L.inv_h2, L.inv_h};
+                        L.cov, L.dense_map, L.bmap, L.march, L.rf, L.rff, L.rfs, L.rfw, L.range, L.inv_h2, L.inv_h};
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
     }
@@ -632,7 +638,7 @@ static void free_all(ohm_hier *H)
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
     }
-    void *ptrs[] = {H->d_scal, H->d_part, H->d_norms, H->d_coarse_inv, H->d_ring, H->d_coarse_eta, H->d_coarse_flags};
+    void *ptrs[] = {H->d_scal, H->d_part, H->d_coarse_inv, H->d_ring, H->d_coarse_eta, H->d_coarse_flags};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (H->h_dots) (void)hipHostFree(H->h_dots);

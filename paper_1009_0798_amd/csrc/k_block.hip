@@ -87,7 +87,7 @@ template <typename T, int MODE>
 __global__ void __launch_bounds__(256)
 k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
               const uint8_t *__restrict__ cov_zero, const int *__restrict__ active,
-              const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+              const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, const T *__restrict__ Bg, long long cs, long long gcs,
               const T *__restrict__ S, const T *__restrict__ eta, const T *__restrict__ etag,
               T *__restrict__ out, int colour, double *__restrict__ partials, StencilDots dots,
@@ -132,7 +132,7 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
                     pY[half][c] = dots.dot_y[qy][c * cs + (long long)b * NC + threadIdx.x + 256 * half];
     }
     __syncthreads();
-    const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
+    const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]);
     const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
     const uint8_t cov = cov_zero ? cov_zero[b] : 0;
     double ss[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
@@ -299,7 +299,7 @@ struct GhostBlockAddr {
 template <typename T, int MODE, bool O64, bool DIRECT, typename Tl>
 __global__ void __launch_bounds__(Tl::THREADS)
 k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
-            const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+            const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
             const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
             void *__restrict__ out, const int *__restrict__ ijk, const DenseProbDev *__restrict__ dp,
             const T *__restrict__ coarse, long long ccs, const T *__restrict__ Bg, long long gcs,
@@ -320,7 +320,7 @@ k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ p
     if (active && !active[pr]) return;
     if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
     __syncthreads();
-    const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
+    const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]);
     Part A;
     if constexpr (MODE >= 3) static_cast<Addr &>(A) = Addr{snbr, Bg, gcs, etag};
     else static_cast<Addr &>(A) = Addr{snbr, b};
@@ -338,7 +338,7 @@ k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ p
 template <typename T, typename Tl>
 __global__ void __launch_bounds__(Tl::THREADS)
 k_blk_down(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of, const int *__restrict__ active,
-           const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, const T *B, long long cs,
+           const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v, const T *B, long long cs,
            const T *__restrict__ S, const T *__restrict__ eta, const int *__restrict__ dense_map,
            const DenseProbDev *__restrict__ dp, T *__restrict__ coarse, long long ccs)
 {
@@ -356,7 +356,7 @@ k_blk_down(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ pr
     PartAddr<BlockAddr> A;
     static_cast<BlockAddr &>(A) = BlockAddr{snbr, b};
     A.y0 = Tl::y0(part), A.z0 = Tl::z0(part);
-    down_tile<T, false, Tl>(A, const_cast<T *>(B), cs, S, eta, T(coef_p[pr]) * T(inv_h2_p[pr]), sB, sE, sR);
+    down_tile<T, false, Tl>(A, const_cast<T *>(B), cs, S, eta, T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]), sB, sE, sR);
     if (threadIdx.x < 3 * Dn::NC8) {
         const int c = threadIdx.x / Dn::NC8, m = threadIdx.x % Dn::NC8;
         const int i = m & 3, j = A.y0 / 2 + (m >> 2) % (Tl::TY / 2), k = A.z0 / 2 + m / (2 * Tl::TY);
@@ -557,7 +557,7 @@ template <typename T>
 __global__ void __launch_bounds__(RF_WG_FACES * 10)
 k_reflux(const int *__restrict__ rfw, const int *__restrict__ rff, const int *__restrict__ rfs,
          const int *__restrict__ rf, const int *__restrict__ active, const int *__restrict__ cnbr,
-         const int *__restrict__ fnbr, const double *__restrict__ inv_h_c, const double *__restrict__ coef_p,
+         const int *__restrict__ fnbr, const double *__restrict__ inv_h_c, const double *__restrict__ coef_p, double coef_v,
          const T *__restrict__ Bc, long long ccs, const T *__restrict__ Ec, const T *__restrict__ Bf,
          long long fcs, const T *__restrict__ Bfg, long long fgcs, const T *__restrict__ Ef,
          const T *__restrict__ Efg, T *__restrict__ out)
@@ -623,7 +623,7 @@ k_reflux(const int *__restrict__ rfw, const int *__restrict__ rff, const int *__
         const int *en = rf + RF_INTS * (long long)e;
         const int pr = en[15];
         if (!(active && !active[pr])) {
-            const T coef = T(coef_p[pr]);
+            const T coef = T(coef_of(coef_p[pr], coef_v));
             const int mask = en[2];
             const long long gi = (long long)en[0] * NC + en[1];
             T a[3] = {T(0), T(0), T(0)};
@@ -712,7 +712,7 @@ static bool march_stencil(const AmrLevelDev &L, size_t elem)
 
 template <typename T>
 ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *Bg, long long cs,
-                              long long gcs, const T *S, const T *eta, const T *etag, const double *coef_dev,
+                              long long gcs, const T *S, const T *eta, const T *etag, Coef coef_dev,
                               T *out, int colour, double *partials, const uint8_t *cov_zero, const int *active,
                               hipStream_t s, StencilDots dots)
 {
@@ -725,7 +725,7 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
         (dots.ndot == 0 || (given == 1 && std::is_same<T, double>::value)))
         return launch_march_stencil<T>(h, mode, B, cs, S, eta, coef_dev, out, 0, active, s, dots);
     dim3 grid(L.nb), blk(256);
-#define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, out, colour, \
+#define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, out, colour, \
              partials, dots, nullptr, nullptr, 0
     switch (mode) {
     case MODE_APPLY: k_blk_stencil<T, MODE_APPLY><<<grid, blk, 0, s>>>(ARGS); break;
@@ -743,7 +743,7 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
 
 template <typename T>
 ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg, long long cs, long long gcs,
-                                      const T *S, const T *eta, const T *etag, const double *coef_dev, T *coarse,
+                                      const T *S, const T *eta, const T *etag, Coef coef_dev, T *coarse,
                                       long long ccs, const int *active, hipStream_t s)
 {
     const AmrLevelDev &L = h->amr[0];
@@ -753,24 +753,24 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
         return launch_march_stencil<T>(h, MODE_RESID_RESTRICT, B, cs, S, eta, coef_dev, coarse, ccs, active, s);
     const int parts = tile_parts(L.nb);
     if (parts > 1 && L.complete27 && (((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T))) == 0) {
-#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, L.dense_map, h->dense[1].probs, coarse, ccs
+#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, L.dense_map, h->dense[1].probs, coarse, ccs
         if (parts == 4) k_blk_down<T, Tile<4, 4>><<<4 * L.nb, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
         else k_blk_down<T, Tile<8, 4>><<<2 * L.nb, Tile<8, 4>::THREADS, 0, s>>>(ARGS);
 #undef ARGS
         return check_launch("residual + restriction by parts");
     }
     k_blk_stencil<T, MODE_RESID_RESTRICT><<<L.nb, 256, 0, s>>>(
-        L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
+        L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
         nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs);
     return check_launch("residual + restriction to dense");
 }
 
 template <typename T, int MODE, bool O64, bool DIRECT>
 static void blk_sweep(const ohm_hier *h, const AmrLevelDev &L, const T *B, long long cs, const T *S, const T *eta,
-                      const double *coef_dev, void *out, const int *active, hipStream_t s, const T *coarse,
+                      Coef coef_dev, void *out, const int *active, hipStream_t s, const T *coarse,
                       long long ccs, const T *Bg, long long gcs, const T *etag)
 {
-#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev, B, cs, S, eta, out, L.ijk, h->dense[1].probs, \
+#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, out, L.ijk, h->dense[1].probs, \
              coarse, ccs, Bg, gcs, etag
     switch (tile_parts(L.nb)) {
     case 4: k_blk_sweep<T, MODE, O64, DIRECT, Tile<4, 4>><<<4 * L.nb, Tile<4, 4>::THREADS, 0, s>>>(ARGS); break;
@@ -782,7 +782,7 @@ static void blk_sweep(const ohm_hier *h, const AmrLevelDev &L, const T *B, long 
 
 template <typename T>
 ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long cs, const T *S, const T *eta,
-                            const double *coef_dev, T *out, const int *active, hipStream_t s, const T *coarse,
+                            Coef coef_dev, T *out, const int *active, hipStream_t s, const T *coarse,
                             long long ccs, const T *Bg, long long gcs, const T *etag, double *out64)
 {
     const AmrLevelDev &L = h->amr[level];
@@ -905,12 +905,12 @@ ohm_status launch_fill_ghosts(const ohm_hier *h, int level, const T *coarse, lon
 template <typename T>
 ohm_status launch_reflux(const ohm_hier *h, int level, const T *Bc, long long ccs, const T *etac, const T *Bf,
                          long long fcs, const T *Bfg, long long fgcs, const T *etaf, const T *etafg,
-                         const double *coef_dev, T *out, const int *active, hipStream_t s)
+                         Coef coef_dev, T *out, const int *active, hipStream_t s)
 {
     const AmrLevelDev &L = h->amr[level];
     if (L.nrf == 0) return OHM_OK;
     k_reflux<T><<<L.nrfw, RF_WG_FACES * 10, 0, s>>>(L.rfw, L.rff, L.rfs, L.rf, active, L.nbr, h->amr[level + 1].nbr,
-                                                   L.inv_h, coef_dev, Bc, ccs, etac, Bf, fcs, Bfg, fgcs, etaf, etafg,
+                                                   L.inv_h, coef_dev.p, coef_dev.v, Bc, ccs, etac, Bf, fcs, Bfg, fgcs, etaf, etafg,
                                                    out);
     return check_launch("reflux");
 }
@@ -933,15 +933,15 @@ ohm_status launch_reduce_problem(int nprob, int nrange, const long long *range_d
 
 #define INST(T)                                                                                                 \
     template ohm_status launch_blk_sweep<T>(const ohm_hier *, int, const T *, long long, const T *, const T *,   \
-                                            const double *, T *, const int *, hipStream_t, const T *, long long, \
+                                            Coef, T *, const int *, hipStream_t, const T *, long long, \
                                             const T *, long long, const T *, double *);                         \
     template ohm_status launch_blk_stencil<T>(const ohm_hier *, int, int, const T *, const T *, long long,      \
-                                              long long, const T *, const T *, const T *, const double *, T *,  \
+                                              long long, const T *, const T *, const T *, Coef, T *,  \
                                               int, double *, const uint8_t *, const int *, hipStream_t,         \
                                               StencilDots);                                                     \
     template ohm_status launch_resid_restrict_blk0<T>(const ohm_hier *, const T *, const T *, long long,       \
                                                       long long, const T *, const T *, const T *,             \
-                                                      const double *, T *, long long, const int *, hipStream_t);        \
+                                                      Coef, T *, long long, const int *, hipStream_t);        \
     template ohm_status launch_restrict_blk<T>(const ohm_hier *, int, const T *, long long, T *, long long, int, \
                                                const int *, hipStream_t);                                       \
     template ohm_status launch_prolong_blk<T>(const ohm_hier *, int, const T *, long long, T *, long long, int,  \
@@ -949,7 +949,7 @@ ohm_status launch_reduce_problem(int nprob, int nrange, const long long *range_d
     template ohm_status launch_fill_ghosts<T>(const ohm_hier *, int, const T *, long long, T *, long long, int,  \
                                               const int *, hipStream_t);                                        \
     template ohm_status launch_reflux<T>(const ohm_hier *, int, const T *, long long, const T *, const T *,      \
-                                         long long, const T *, long long, const T *, const T *, const double *, \
+                                         long long, const T *, long long, const T *, const T *, Coef, \
                                          T *, const int *, hipStream_t);                                        \
     template ohm_status launch_zero_covered<T>(const ohm_hier *, int, T *, long long, int, hipStream_t);
 INST(double)

@@ -35,7 +35,7 @@ __device__ __forceinline__ void gather(const DenseProbDev &q, int i, int j, int 
 template <typename T, int MODE>
 __global__ void __launch_bounds__(256)
 k_dense_stencil(const int *__restrict__ tiles, const DenseProbDev *__restrict__ dp, const int *__restrict__ active,
-                const double *__restrict__ coef_p, const T *__restrict__ B, const T *__restrict__ S,
+                const double *__restrict__ coef_p, double coef_v, const T *__restrict__ B, const T *__restrict__ S,
                 const T *__restrict__ eta, T *__restrict__ out, long long cs, int colour)
 {
     const int pr = tiles[2 * blockIdx.x], start = tiles[2 * blockIdx.x + 1];
@@ -50,7 +50,7 @@ k_dense_stencil(const int *__restrict__ tiles, const DenseProbDev *__restrict__ 
     gather<T>(q, i, j, k, b1, [&](long long x) { return B[cs + x]; });
     gather<T>(q, i, j, k, b2, [&](long long x) { return B[2 * cs + x]; });
     gather<T>(q, i, j, k, e, [&](long long x) { return eta[x]; });
-    const T cih2 = T(coef_p[pr]) * T(q.inv_h2);
+    const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(q.inv_h2);
     const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
     const long long gi = q.off + cell;
     const T *bc[3] = {b0, b1, b2};
@@ -99,7 +99,7 @@ __device__ __forceinline__ DenseAddr dense_tile(const DenseProbDev &q, int t)
 // clist), B -> out, without storing the corrected input
 template <typename T, int MODE, typename Tl>
 __global__ void __launch_bounds__(Tl::THREADS)
-k_dense_sweep(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p,
+k_dense_sweep(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, long long cs, const T *__restrict__ S,
               const T *__restrict__ eta, T *__restrict__ out, const T *__restrict__ coarse, long long ccs)
 {
@@ -114,7 +114,7 @@ k_dense_sweep(DenseList list, DenseList clist, const int *__restrict__ active, c
     DenseAddr A = dense_tile(q, t);
     A.oy += Tl::y0(part);
     A.oz += Tl::z0(part);
-    const T cih2 = T(coef_p[pr]) * T(q.inv_h2);
+    const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(q.inv_h2);
     Coarse cor;
     if constexpr (MODE == 2) cor = {coarse, ccs, clist.grid(pr), A.ox / 2 - 2, A.oy / 2 - 2, A.oz / 2 - 2, sC, {}};
     fused_sweep_tile<T, MODE == 1, DenseAddr, Coarse, T, Tl>(A, B, cs, S, eta, out, cih2, sB, sE, cor);
@@ -156,7 +156,7 @@ k_dense_run_copy(const int *__restrict__ runs, const DenseProbDev *__restrict__ 
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ active,
-                       const double *__restrict__ coef_p, const T *__restrict__ B, const T *__restrict__ S,
+                       const double *__restrict__ coef_p, double coef_v, const T *__restrict__ B, const T *__restrict__ S,
                        const T *__restrict__ eta, T *__restrict__ coarse, long long cs, long long ccs)
 {
     constexpr int W = 10;
@@ -198,7 +198,7 @@ k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ 
         for (int c = 0; c < 3; ++c) s2[half][c] = S[c * cs + gi];
     }
     __syncthreads();
-    const T c8 = T(coef_p[pr]) * T(q.inv_h2) * T(0.125);
+    const T c8 = T(coef_of(coef_p[pr], coef_v)) * T(q.inv_h2) * T(0.125);
     T r[2][3];
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
@@ -236,7 +236,7 @@ k_dense_resid_restrict(DenseList list, DenseList clist, const int *__restrict__ 
 // The way down on parts of the tiles (down_tile)
 template <typename T, bool ZERO, typename Tl>
 __global__ void __launch_bounds__(Tl::THREADS)
-k_dense_down(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p, T *e,
+k_dense_down(DenseList list, DenseList clist, const int *__restrict__ active, const double *__restrict__ coef_p, double coef_v, T *e,
              const T *__restrict__ S, const T *__restrict__ eta, T *__restrict__ coarse, long long cs, long long ccs)
 {
     using Dn = DownTile<Tl>;
@@ -250,7 +250,7 @@ k_dense_down(DenseList list, DenseList clist, const int *__restrict__ active, co
     DenseAddr A = dense_tile(q, t);
     A.oy += Tl::y0(part);
     A.oz += Tl::z0(part);
-    down_tile<T, ZERO, Tl>(A, e, cs, S, eta, T(coef_p[pr]) * T(q.inv_h2), sB, sE, sR);
+    down_tile<T, ZERO, Tl>(A, e, cs, S, eta, T(coef_of(coef_p[pr], coef_v)) * T(q.inv_h2), sB, sE, sR);
     if (threadIdx.x < 3 * Dn::NC8) {
         const int c = threadIdx.x / Dn::NC8, m = threadIdx.x % Dn::NC8;
         const int i = A.ox / 2 + (m & 3), j = A.oy / 2 + (m >> 2) % (Tl::TY / 2), k = A.oz / 2 + m / (2 * Tl::TY);
@@ -645,7 +645,7 @@ k_coarse_apply(const CoarseJob *__restrict__ jobs, const int *__restrict__ activ
 // ---------------------------------------------------------------------------
 template <typename T>
 ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *S, const T *eta,
-                                const double *coef_dev, T *out, int colour, bool coarsest_too, const int *active,
+                                Coef coef_dev, T *out, int colour, bool coarsest_too, const int *active,
                                 hipStream_t s)
 {
     const DenseLevelDev &D = h->dense[-level];
@@ -655,13 +655,13 @@ ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T 
     const long long cs = D.ncells;
     switch (mode) {
     case MODE_APPLY:
-        k_dense_stencil<T, MODE_APPLY><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev, B, S, eta, out, cs, colour);
+        k_dense_stencil<T, MODE_APPLY><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev.p, coef_dev.v, B, S, eta, out, cs, colour);
         break;
     case MODE_RESID:
-        k_dense_stencil<T, MODE_RESID><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev, B, S, eta, out, cs, colour);
+        k_dense_stencil<T, MODE_RESID><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev.p, coef_dev.v, B, S, eta, out, cs, colour);
         break;
     default:
-        k_dense_stencil<T, MODE_SMOOTH><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev, B, S, eta, out, cs, colour);
+        k_dense_stencil<T, MODE_SMOOTH><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev.p, coef_dev.v, B, S, eta, out, cs, colour);
     }
     return check_launch("dense stencil");
 }
@@ -684,7 +684,7 @@ static void dense_sweep(int nft, hipStream_t s, Args... args)
 
 template <typename T>
 ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const T *S, const T *eta,
-                               const double *coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
+                               Coef coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
                                int flags, const T *coarse, T **last, int ordering)
 {
     const DenseLevelDev &D = h->dense[-level];
@@ -709,7 +709,7 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
         }
         for (int k = 0; k < nsweeps; ++k)
             for (int m = 0; m < 4; ++m) {
-                k_dense_stencil<T, MODE_SMOOTH><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev, (m & 1) ? oth : cur,
+                k_dense_stencil<T, MODE_SMOOTH><<<nt, 256, 0, s>>>(tl, D.probs, active, coef_dev.p, coef_dev.v, (m & 1) ? oth : cur,
                                                                    S, eta, (m & 1) ? cur : oth, cs, 2 + m);
                 OHM_TRY(check_launch("dense colour-class update"));
             }
@@ -734,15 +734,15 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
             T *dst;
             if (k == 0 && zero) {
                 dst = (nsweeps & 1) ? B : tmp;
-                dense_sweep<T, 1>(nft, s, list, none, active, coef_dev, nullptr, cs, S, eta, dst, nullptr, 0);
+                dense_sweep<T, 1>(nft, s, list, none, active, coef_dev.p, coef_dev.v, nullptr, cs, S, eta, dst, nullptr, 0);
             } else if (k == 0 && coarse) {
                 dst = cur == B ? tmp : B;
                 const DenseLevelDev &C = h->dense[-level + 1];
-                dense_sweep<T, 2>(nft, s, list, dense_list(h, C, C.tiles_all), active, coef_dev, cur, cs, S, eta, dst,
+                dense_sweep<T, 2>(nft, s, list, dense_list(h, C, C.tiles_all), active, coef_dev.p, coef_dev.v, cur, cs, S, eta, dst,
                                   coarse, C.ncells);
             } else {
                 dst = cur == B ? tmp : B;
-                dense_sweep<T, 0>(nft, s, list, none, active, coef_dev, cur, cs, S, eta, dst, nullptr, 0);
+                dense_sweep<T, 0>(nft, s, list, none, active, coef_dev.p, coef_dev.v, cur, cs, S, eta, dst, nullptr, 0);
             }
             OHM_TRY(check_launch("dense fused sweep"));
             cur = dst;
@@ -766,9 +766,9 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
             OHM_TRY(check_launch("dense run zero"));
         }
         for (int k = 0; k < nsweeps; ++k) {
-            k_dense_stencil<T, MODE_SMOOTH><<<npt, 256, 0, s>>>(pt, D.probs, active, coef_dev, cur, S, eta, oth, cs, 0);
+            k_dense_stencil<T, MODE_SMOOTH><<<npt, 256, 0, s>>>(pt, D.probs, active, coef_dev.p, coef_dev.v, cur, S, eta, oth, cs, 0);
             OHM_TRY(check_launch("dense half-sweep"));
-            k_dense_stencil<T, MODE_SMOOTH><<<npt, 256, 0, s>>>(pt, D.probs, active, coef_dev, oth, S, eta, cur, cs, 1);
+            k_dense_stencil<T, MODE_SMOOTH><<<npt, 256, 0, s>>>(pt, D.probs, active, coef_dev.p, coef_dev.v, oth, S, eta, cur, cs, 1);
             OHM_TRY(check_launch("dense half-sweep"));
         }
         if (cur != B) {
@@ -791,11 +791,11 @@ static int dense_down_parts(const ohm_hier *h, int level)
 bool dense_down_fuses(const ohm_hier *h, int level) { return dense_down_parts(h, level) > 1; }
 
 template <typename T, bool ZERO>
-static ohm_status dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+static ohm_status dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s)
 {
     const DenseLevelDev &D = h->dense[-level], &C = h->dense[-level + 1];
-#define ARGS dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active, coef_dev, e, S, eta, coarse, D.ncells, C.ncells
+#define ARGS dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active, coef_dev.p, coef_dev.v, e, S, eta, coarse, D.ncells, C.ncells
     if (dense_down_parts(h, level) == 4)
         k_dense_down<T, ZERO, Tile<4, 4>><<<4 * D.nftile, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
     else
@@ -805,7 +805,7 @@ static ohm_status dense_down(const ohm_hier *h, int level, T *e, const T *S, con
 }
 
 template <typename T>
-ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, const double *coef_dev,
+ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s)
 {
     if (!dense_down_fuses(h, level)) return fail(OHM_ERR_ARG, "dense level %d: too many tiles for the fused way down", level);
@@ -814,7 +814,7 @@ ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, con
 
 template <typename T>
 ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B, const T *S, const T *eta,
-                                       const double *coef_dev, T *res, T *coarse, const int *active, hipStream_t s)
+                                       Coef coef_dev, T *res, T *coarse, const int *active, hipStream_t s)
 {
     const DenseLevelDev &D = h->dense[-level], &C = h->dense[-level + 1];
     if (D.ntile == 0) return OHM_OK;
@@ -826,7 +826,7 @@ ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B,
     if (dense_down_parts(h, level) > 1)
         return dense_down<T, false>(h, level, const_cast<T *>(B), S, eta, coef_dev, coarse, active, s);
     k_dense_resid_restrict<T><<<D.nftile, 256, 0, s>>>(dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active,
-                                                        coef_dev, B, S, eta, coarse, D.ncells, C.ncells);
+                                                        coef_dev.p, coef_dev.v, B, S, eta, coarse, D.ncells, C.ncells);
     return check_launch("dense residual + restriction");
 }
 
@@ -1000,15 +1000,15 @@ size_t coarse_job_bytes() { return sizeof(CoarseJob); }
 
 #define INST(T)                                                                                                \
     template ohm_status launch_dense_smooth<T>(const ohm_hier *, int, T *, T *, const T *, const T *,           \
-                                               const double *, int, bool, const int *, hipStream_t, int,       \
+                                               Coef, int, bool, const int *, hipStream_t, int,       \
                                                const T *, T **, int);                                          \
     template ohm_status launch_dense_stencil<T>(const ohm_hier *, int, int, const T *, const T *, const T *,   \
-                                                const double *, T *, int, bool, const int *, hipStream_t);     \
+                                                Coef, T *, int, bool, const int *, hipStream_t);     \
     template ohm_status launch_dense_restrict<T>(const ohm_hier *, int, const T *, T *, int, const int *,      \
                                                  hipStream_t);                                                 \
     template ohm_status launch_dense_resid_restrict<T>(const ohm_hier *, int, const T *, const T *, const T *, \
-                                                       const double *, T *, T *, const int *, hipStream_t);    \
-    template ohm_status launch_dense_down<T>(const ohm_hier *, int, T *, const T *, const T *, const double *, T *, \
+                                                       Coef, T *, T *, const int *, hipStream_t);    \
+    template ohm_status launch_dense_down<T>(const ohm_hier *, int, T *, const T *, const T *, Coef, T *, \
                                              const int *, hipStream_t);                                          \
     template ohm_status launch_dense_prolong<T>(const ohm_hier *, int, const T *, T *, int, int, const int *,  \
                                                 hipStream_t, const T *);                                       \

@@ -273,7 +273,7 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
 template <typename T, typename TO, bool ZERO>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
 k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
-              const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+              const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
               TO *__restrict__ out, unsigned obytes)
 {
@@ -284,7 +284,7 @@ k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restr
     const MarchTile &M = tiles[xc * q8 + min(xc, r8) + w / NXCD];
     const int pr = M.prob;
     if (active && !active[pr]) return;
-    const T cih2 = T(coef_p[pr]) * T(inv_h2_p[pr]);
+    const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]);
     const int nbx = M.nx, nby = M.ny, nbz = M.nz;
     const int ex = min(MT, 8 * (nbx - M.bx)), ey = min(MT, 8 * (nby - M.by));   // cells of the tile inside the box
     const int z0 = 8 * M.bz, n = 8 * M.nbz;
@@ -381,7 +381,7 @@ struct Plane {
 template <typename T, int MODE, bool DOTS>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
 k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
-                const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p,
+                const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
                 const T *__restrict__ B, long long cs, const T *S, const T *__restrict__ eta, T *out, unsigned obytes,
                 StencilDots dots, unsigned pbytes, const int *__restrict__ dense_map,
                 const DenseProbDev *__restrict__ dp, long long ccs)
@@ -418,7 +418,7 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
                               t % dots.ndot] = 0.0;
         return;
     }
-    const T c8 = uniform(T(coef_p[pr]) * T(inv_h2_p[pr]) * T(0.125));
+    const T c8 = uniform(T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]) * T(0.125));
     // halo cells: the lanes of wavefront k load array k around the tile, four
     // lanes (of each, for B_x and B_y) the tile's edges
     const int l = lane & 15;
@@ -598,32 +598,30 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
 
 template <typename T, typename TO>
 ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
-                              const double *coef_dev, TO *out, const int *active, hipStream_t s)
+                              Coef coef_dev, TO *out, const int *active, hipStream_t s)
 {
     const AmrLevelDev &L = h->amr[0];
     const unsigned obytes = (unsigned)((unsigned long long)L.nb * NC * sizeof(TO));   // (the callers allow 4 GiB)
     const MarchTile *tiles = (const MarchTile *)L.march;
     if (B)
         k_march_sweep<T, TO, false><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
-                                                                       coef_dev, B, cs, S, eta, out, obytes);
+                                                                       coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes);
     else
         k_march_sweep<T, TO, true><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
-                                                                      coef_dev, B, cs, S, eta, out, obytes);
+                                                                      coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes);
     return check_launch("marching sweep");
 }
-template ohm_status launch_march_sweep<double, double>(const ohm_hier *, const double *, long long, const double *,
-                                                       const double *, const double *, double *, const int *,
-                                                       hipStream_t);
-template ohm_status launch_march_sweep<float, float>(const ohm_hier *, const float *, long long, const float *,
-                                                     const float *, const double *, float *, const int *,
-                                                     hipStream_t);
-template ohm_status launch_march_sweep<float, double>(const ohm_hier *, const float *, long long, const float *,
-                                                      const float *, const double *, double *, const int *,
-                                                      hipStream_t);
+#define INST(T, TO)                                                                                              \
+    template ohm_status launch_march_sweep<T, TO>(const ohm_hier *, const T *, long long, const T *, const T *, \
+                                                  Coef, TO *, const int *, hipStream_t);
+INST(double, double)
+INST(float, float)
+INST(float, double)
+#undef INST
 
 template <typename T>
 ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long long cs, const T *S, const T *eta,
-                                const double *coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
+                                Coef coef_dev, T *out, long long ccs, const int *active, hipStream_t s,
                                 StencilDots dots)
 {
     const AmrLevelDev &L = h->amr[0];
@@ -631,7 +629,7 @@ ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long lo
     const unsigned pbytes = (unsigned)((unsigned long long)L.nb * dots.ndot * sizeof(double));
     const MarchTile *tiles = (const MarchTile *)L.march;
 #define RUN(mode, d, S) k_march_stencil<T, mode, d><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
-        L.inv_h2, coef_dev, B, cs, S, eta, out, obytes, dots, pbytes, L.dense_map, h->dense[1].probs, ccs)
+        L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes, dots, pbytes, L.dense_map, h->dense[1].probs, ccs)
     switch (mode) {
     case MODE_APPLY:
         if constexpr (std::is_same<T, double>::value)
@@ -651,7 +649,7 @@ ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long lo
 }
 #define INST(T)                                                                                                    \
     template ohm_status launch_march_stencil<T>(const ohm_hier *, int, const T *, long long, const T *, const T *, \
-                                                const double *, T *, long long, const int *, hipStream_t, StencilDots);
+                                                Coef, T *, long long, const int *, hipStream_t, StencilDots);
 INST(double)
 INST(float)
 #undef INST
