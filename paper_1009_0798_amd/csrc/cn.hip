@@ -505,7 +505,9 @@ struct Solver {
             rhs_b = (T *)at<double>(ro);
             e_b = (T *)at<double>(zo);
         } else {
-            rhs_b = e_b = nullptr;
+            // an FP64 cycle over several levels leaves its correction in z, too
+            rhs_b = nullptr;
+            e_b = P.T32 ? nullptr : (T *)at<double>(zo);
             if (!rhs_ready) OHM_TRY(vconvert<double, T>(at<double>(ro), at<T>(P.rhs), n, st));
         }
         // one FP32 level: the last post-sweep writes the FP64 result directly
@@ -514,7 +516,7 @@ struct Solver {
                                 ? at<double>(zo)
                                 : nullptr;
         OHM_TRY(amr_vcycle(L - 1, o64));
-        if (!alias && !wrote64_) OHM_TRY(vconvert<T, double>(at<T>(P.e), at<double>(zo), n, st));
+        if (P.T32 && !wrote64_) OHM_TRY(vconvert<T, double>(at<T>(P.e), at<double>(zo), n, st));
         rhs_b = e_b = nullptr;
         return OHM_OK;
     }

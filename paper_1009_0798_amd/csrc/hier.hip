@@ -522,19 +522,25 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
         // face list and workgroup partition: whole entries per workgroup, at
         // most RF_WG_FACES faces
         std::vector<int> rff, rfs(nrf), rfw;
-        int w_e0 = 0, w_f0 = 0;
+        int w_e0 = 0, w_f0 = 0, nface = 0;
         for (int e = 0; e <= nrf; ++e) {
             const int nf = e < nrf ? __builtin_popcount(rf[RF_INTS * e + 2]) : 0;
-            const int cur = (int)rff.size() - w_f0;
+            const int cur = nface - w_f0;
             if (e == nrf || cur + nf > RF_WG_FACES) {
                 if (e > w_e0) rfw.insert(rfw.end(), {w_e0, e - w_e0, w_f0, cur});
                 w_e0 = e;
-                w_f0 = (int)rff.size();
+                w_f0 = nface;
             }
             if (e == nrf) break;
-            rfs[e] = (int)rff.size();
+            rfs[e] = nface;
+            const int *ent = &rf[(size_t)RF_INTS * e];
             for (int f = 0; f < 6; ++f)
-                if ((rf[RF_INTS * e + 2] >> f) & 1) rff.push_back(8 * e + f);
+                if ((ent[2] >> f) & 1) {
+                    const RfFace r = {ent[0], ent[1], ent[3 + f], ent[9 + f], f, ent[15], {}};
+                    const int *v = (const int *)&r;
+                    rff.insert(rff.end(), v, v + sizeof r / sizeof(int));
+                    ++nface;
+                }
         }
         H->amr[l].nrfw = (int)(rfw.size() / 4);
         OHM_TRY(upload(&H->amr[l].rff, rff));
