@@ -347,7 +347,7 @@ ohm_status launch_prolong_blk(const ohm_hier *h, int coarse_level, const T *coar
 // it loads (coarse and last need a level of whole tiles, an input and a sweep).
 // ordering 1: four-colour sweeps (four class launches each, see in_colour)
 // instead of red-black; coarse and last are then not accepted.
-enum { SMOOTH_ZERO = 1, SMOOTH_FROM_TMP = 2 };
+enum { SMOOTH_ZERO = 1, SMOOTH_FROM_TMP = 2, SMOOTH_TO_TMP = 4 };
 template <typename T>
 ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const T *S, const T *eta,
                                Coef coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
