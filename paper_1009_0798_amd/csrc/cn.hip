@@ -351,11 +351,9 @@ struct Solver {
         if (lev == 0) {
             const bool fz = h->amr[0].complete27 && fused_blk(0);
             // the first of an odd number of sweeps can add the correction as it
-            // loads, too, where the sweeps before can end in tmp.  Not on a
-            // marching level, whose sweeps take no correction: 128^3 FP64 24 us
-            // of prolongation and 40 a sweep, against 56 of the sweep per block
-            // and the correction; on a 32^3 level 5.4 + 5.1 against 7.0.
-            const bool in_tmp = fz && (nu2 & 1) && zero_guess && nu1 > 0 && h->amr[0].nmarch == 0;
+            // loads, too, where the sweeps before can end in tmp: a 32^3 FP64
+            // level 5.4 + 5.1 us -> 7.3, a marching 128^3 one 24.2 + 39.5 -> 51.7
+            const bool in_tmp = fz && (nu2 & 1) && zero_guess && nu1 > 0;
             OHM_TRY(smooth_blk(0, nu1, zf | (in_tmp ? SMOOTH_TO_TMP : 0)));
             OHM_TRY(launch_resid_restrict_blk0<T>(h, mg(in_tmp ? P.tmp : P.e, 0), at<T>(P.mg_g) + P.LG[0] * NC, VN, GN, mg(P.rhs, 0),
                                                   etaT(0), etagT(0), lam_dt, dv(P.d_rhs, 1), h->dense_cells[1],

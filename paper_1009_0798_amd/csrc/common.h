@@ -294,7 +294,8 @@ ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long lo
                                 StencilDots dots = StencilDots{{nullptr, nullptr}, 0, nullptr});
 template <typename T, typename TO>
 ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
-                              Coef coef_dev, TO *out, const int *active, hipStream_t s);
+                              Coef coef_dev, TO *out, const int *active, hipStream_t s,
+                              const T *coarse = nullptr, long long ccs = 0);
 
 template <typename T>
 ohm_status launch_dense_stencil(const ohm_hier *h, int level, int mode, const T *B, const T *S,

@@ -796,18 +796,17 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
             if (((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T)) != 0)
                 return fail(OHM_ERR_ARG, "level %d: fused sweep needs B, eta and the component stride %zu-byte "
                                          "aligned", level, 2 * sizeof(T));
-            if (coarse) {
-                if (level != 0 || h->min_level > -1)
-                    return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0 and a dense level below it");
+            if (coarse && (level != 0 || h->min_level > -1))
+                return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0 and a dense level below it");
+            if (level == 0 && L.nmarch > 0 &&
+                ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0)
+                return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s, coarse, ccs);
+            if (coarse)
                 blk_sweep<T, 2, true, false>(h, L, B, cs, S, eta, coef_dev, out64, active, s, coarse, ccs, nullptr, 0,
                                              nullptr);
-            } else if (level == 0 && L.nmarch > 0 &&
-                       ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0) {
-                return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s);
-            } else {
+            else
                 blk_sweep<T, 0, true, false>(h, L, B, cs, S, eta, coef_dev, out64, active, s, nullptr, 0, nullptr, 0,
                                              nullptr);
-            }
             return check_launch("fused sweep to FP64");
         } else {
             return fail(OHM_ERR_ARG, "an FP64 result is for FP32 sweeps");
@@ -835,12 +834,12 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
             blk_sweep<T, 4, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0, nullptr, 0, etag);
         return check_launch("fused sweep with ghosts");
     }
-    if (coarse) {
-        if (level != 0 || h->min_level > -1 || !B)
-            return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0, a dense level below it and an input");
+    if (coarse && (level != 0 || h->min_level > -1 || !B))
+        return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0, a dense level below it and an input");
+    if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
+        return launch_march_sweep<T, T>(h, B, cs, S, eta, coef_dev, out, active, s, coarse, ccs);
+    } else if (coarse) {
         blk_sweep<T, 2, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, coarse, ccs, nullptr, 0, nullptr);
-    } else if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
-        return launch_march_sweep<T, T>(h, B, cs, S, eta, coef_dev, out, active, s);
     } else if (B) {
         // FP64 tiles go straight from global memory into LDS (16-byte pairs)
         blk_sweep<T, 0, false, std::is_same<T, double>::value>(h, L, B, cs, S, eta, coef_dev, out, active, s, nullptr, 0,

@@ -32,6 +32,7 @@ namespace {
 template <typename T>
 struct Stage {
     Pair<T> b[3], e, s[3];
+    T co;   // a coarse value (see CoarseRing)
 };
 
 // a value every lane holds, kept in scalar registers
@@ -86,6 +87,32 @@ constexpr int RB = MNP;                               // elements per ring row (
 constexpr int O_ER = 0, O_EK = O_ER + 4 * RB, O_R1 = O_EK + 4 * RB, O_R0 = O_R1 + 2 * 3 * RB, O_K0 = O_R0 + 4 * 3 * RB,
               N_ZERO = O_R0, N_FULL = O_K0 + 4 * 3 * RB;
 
+// With a coarse correction the tile's values are B + P(coarse): the coarse cells
+// under the tile and its halo, with one more layer around (12 x 12 cells from
+// half the tile's origin less 2), of the planes K = q/2 - 1 to q/2 + 2 are kept
+// in a ring in LDS.  At step q every thread requests one of the 216 values of
+// half (q mod 2) of plane q/2 + 3, and stores it two steps later: plane K is
+// complete at step 2 K - 3 and first read at step 2 K - 1.  (36 LDS reads and 54
+// operations a pair; us against the prolongation's launch and a sweep, FP64
+// 128^3 24.2 + 39.5 -> 51.7, FP32 160x128x192 29.9 + 39.9 -> 53.8; against a
+// sweep per block with the correction, 64 FP32 problems, 82 -> 73.)
+constexpr int CW = MT / 2 + 4, CP = 3 * CW * CW;      // edge, and elements of a plane
+template <typename T>
+struct CoarseRing {
+    T *lds;                  // [4][CP]
+    const T *src;
+    unsigned off[2];         // this thread's value of each half on plane 0: byte offset ...
+    int at[2];               // ... and place in the plane
+    unsigned plane;          // bytes from plane to plane
+    int nz;
+    __device__ __forceinline__ T load(int half, int K) const
+    {
+        K = K < 0 ? K + nz : (K >= nz ? K - nz : K);
+        return load_at(src, off[half] + (unsigned)K * plane);
+    }
+    __device__ __forceinline__ T *slot(int K) const { return lds + (K & 3) * CP; }
+};
+
 // hardware placement of a wavefront: bits 0-3 its slot on the SIMD, 4-5 the SIMD
 constexpr int HWREG_PLACE = 4 | (5 << 11);
 
@@ -94,10 +121,11 @@ constexpr int HWREG_PLACE = 4 | (5 << 11);
 // the first halo layer that face the tile, one only loads the rest of the halo
 enum { ROLE_INNER = 0, ROLE_RING = 1, ROLE_LOAD = 2 };
 
-template <typename T, typename TO, int ROLE, bool ZERO>
+template <typename T, typename TO, int ROLE, bool ZERO, bool CO>
 __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__restrict__ B, long long cs,
                                            const T *__restrict__ S, const T *__restrict__ eta, TO *__restrict__ out,
-                                           unsigned obytes, T cih2, int x, int y, int z0, int n, bool in)
+                                           unsigned obytes, T cih2, int x, int y, int z0, int n, bool in,
+                                           const CoarseRing<T> &co)
 {
     constexpr bool RED = ROLE != ROLE_LOAD, BLACK = ROLE == ROLE_INNER;
     const T c8 = uniform(cih2 * T(0.125)), c2 = uniform(cih2 * T(0.5));
@@ -121,7 +149,8 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
         constexpr unsigned PLANE = 64 * (unsigned)sizeof(T);
         return (P & 7) == 0 ? block(P) * 8u * PLANE + before % PLANE : before + PLANE;
     };
-    auto issue = [&](Stage<T> &v, unsigned off, unsigned offs) {
+    auto issue = [&](Stage<T> &v, unsigned off, unsigned offs, int half, int K) {
+        if (CO) v.co = co.load(half, K);
         if (!ZERO) {
             v.b[0] = load_pair(B0, off);
             v.b[1] = load_pair(B1, off);
@@ -142,7 +171,7 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
     const Pair<TO> none = {TO(0), TO(0)};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        issue(st[h], h ? o_p1 : o_p0, o_p0);
+        issue(st[h], h ? o_p1 : o_p0, o_p0, h, (zs >> 1) + 2);
         __builtin_amdgcn_sched_barrier(0);
         if (BLACK) {
             store_pair(O0, 0xFFFFFFF0u, none);
@@ -175,6 +204,23 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
             const bool par = ((y + h) & 1) != 0;                // red is the pair's second cell on plane q (zs is even)
             // plane q (and S of plane q - 1) arrive
             Stage<T> &v = st[h & 1];
+            if constexpr (CO) {
+                co.slot((q >> 1) + 2)[co.at[h & 1]] = v.co;
+                // the prolongation kernels' weights and order of the sum
+                const T *ck = co.slot(q >> 1), *c1 = co.slot((q >> 1) + ((h & 1) ? 1 : -1));
+                const int row = ((y + 2) >> 1) + 1, A = CW * row + ((x + 2) >> 1) + 1, A1 = A + ((y & 1) ? CW : -CW);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const T *a0 = ck + CW * CW * c + A, *a1 = ck + CW * CW * c + A1, *b0 = c1 + CW * CW * c + A,
+                            *b1 = c1 + CW * CW * c + A1;
+                    T va = T(27) * a0[0] + T(9) * (a0[-1] + a1[0] + b0[0]) + T(3) * (a1[-1] + b0[-1] + b1[0]) + b1[-1];
+                    T vb = T(27) * a0[0] + T(9) * (a0[1] + a1[0] + b0[0]) + T(3) * (a1[1] + b0[1] + b1[0]) + b1[1];
+                    va *= T(1.0 / 64.0);
+                    vb *= T(1.0 / 64.0);
+                    v.b[c].a = v.b[c].a + va;
+                    v.b[c].b = v.b[c].b + vb;
+                }
+            }
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 if (ZERO) continue;
@@ -195,7 +241,7 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
             }
             const unsigned o_m2 = off[h2];
             off[h2] = q + 2 < zend ? offset(q + 2, off[h3]) : off[h3];   // plane q + 2
-            issue(v, off[h2], off[h3]);                         // ... and S of q + 1
+            issue(v, off[h2], off[h3], h & 1, (q >> 1) + 3);    // ... and S of q + 1
             lds_barrier();
             // x-neighbours: of the red cell at q - 1 and of the black cell at
             // q - 2 alike, the same-row (and row +-1, plane +-1) partner on
@@ -270,14 +316,16 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
     } while (q0 < zend);
 }
 
-template <typename T, typename TO, bool ZERO>
+template <typename T, typename TO, bool ZERO, bool CO>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
 k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
               const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
-              TO *__restrict__ out, unsigned obytes)
+              TO *__restrict__ out, unsigned obytes, const DenseProbDev *__restrict__ dp,
+              const T *__restrict__ coarse, long long ccs)
 {
     __shared__ T sh[ZERO ? N_ZERO : N_FULL];
+    __shared__ T sco[CO ? 4 * CP : 1];
     __shared__ int place[MARCH_THREADS / 64];
     __shared__ int ids[16 * (MARCH_MAX_NBZ + 2)];
     const int w = blockIdx.x, q8 = ntile / NXCD, r8 = ntile % NXCD, xc = w % NXCD;
@@ -297,6 +345,31 @@ k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restr
         k = k < 0 ? k + nbz : k % nbz;
         ids[t] = bmap[M.map + i + nbx * (j + nby * k)];
     }
+    CoarseRing<T> co{};
+    if constexpr (CO) {
+        const DenseProbDev g = dp[pr];
+        auto wrap = [](int i, int n) { return i < 0 ? i + n : (i >= n ? i % n : i); };
+        auto place_of = [&](int e) {     // element e of a plane: component, row, cell
+            const int c = e / (CW * CW), m = e % (CW * CW);
+            return (unsigned)(c * ccs + g.off + wrap(4 * M.bx - 2 + m % CW, g.nx) +
+                              (long long)g.nx * wrap(4 * M.by - 2 + m / CW, g.ny)) * (unsigned)sizeof(T);
+        };
+        co.lds = sco;
+        co.src = coarse;
+        co.plane = (unsigned)(g.nx * g.ny) * (unsigned)sizeof(T);
+        co.nz = g.nz;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            co.at[h] = CP / 2 * h + min((int)threadIdx.x, CP / 2 - 1);
+            co.off[h] = place_of(co.at[h]);
+        }
+        // planes z0/2 - 2 to z0/2
+        T first[6];
+#pragma unroll
+        for (int m = 0; m < 6; ++m) first[m] = co.load(m & 1, z0 / 2 - 2 + m / 2);
+#pragma unroll
+        for (int m = 0; m < 6; ++m) co.slot(z0 / 2 - 2 + m / 2)[co.at[m & 1]] = first[m];
+    }
     if ((threadIdx.x & 63) == 0) place[threadIdx.x >> 6] = __builtin_amdgcn_s_getreg(HWREG_PLACE);
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -312,20 +385,20 @@ k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restr
         // reads of a plane meet no bank twice (rows 0 to 7 and 8 to 15
         // instead: FP32 sweep of 128^3 34.9 instead of 29.2 us)
         const int r = 2 * role + (lane >> 5) + 4 * ((lane >> 3) & 3), x = 2 * (lane & 7);
-        march_loop<T, TO, ROLE_INNER, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, min(x, ex - 2), min(r, ey - 1), z0, n,
-                                      x < ex && r < ey);
+        march_loop<T, TO, ROLE_INNER, ZERO, CO>(sh, ids, B, cs, S, eta, out, obytes, cih2, min(x, ex - 2), min(r, ey - 1), z0, n,
+                                      x < ex && r < ey, co);
     } else if (__builtin_amdgcn_readfirstlane(role) == 2) {
         // red cells of the first halo layer that face the tile
         const int l = min(lane, 47);
         const int x = l < 16 ? min(2 * (l & 7), ex - 2) : (l < 32 ? -2 : ex),
                   y = l < 16 ? (l < 8 ? -1 : ey) : min(l & 15, ey - 1);
-        march_loop<T, TO, ROLE_RING, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false);
+        march_loop<T, TO, ROLE_RING, ZERO, CO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false, co);
     } else {
         // the rest of the halo: rows -2 and ey + 1, the corners of rows -1 and ey
         const int l = min(lane, 23);
         const int x = l < 20 ? min(2 * (l % 10) - 2, ex) : ((l & 1) ? ex : -2),
                   y = l < 20 ? (l < 10 ? -2 : ey + 1) : (l < 22 ? -1 : ey);
-        march_loop<T, TO, ROLE_LOAD, ZERO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false);
+        march_loop<T, TO, ROLE_LOAD, ZERO, CO>(sh, ids, B, cs, S, eta, out, obytes, cih2, x, y, z0, n, false, co);
     }
 }
 
@@ -598,22 +671,23 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
 
 template <typename T, typename TO>
 ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const T *S, const T *eta,
-                              Coef coef_dev, TO *out, const int *active, hipStream_t s)
+                              Coef coef_dev, TO *out, const int *active, hipStream_t s, const T *coarse,
+                              long long ccs)
 {
     const AmrLevelDev &L = h->amr[0];
     const unsigned obytes = (unsigned)((unsigned long long)L.nb * NC * sizeof(TO));   // (the callers allow 4 GiB)
     const MarchTile *tiles = (const MarchTile *)L.march;
-    if (B)
-        k_march_sweep<T, TO, false><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
-                                                                       coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes);
-    else
-        k_march_sweep<T, TO, true><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, L.inv_h2,
-                                                                      coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes);
+#define RUN(zero, co) k_march_sweep<T, TO, zero, co><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
+        L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes, h->dense[1].probs, coarse, ccs)
+    if (!B) RUN(true, false);
+    else if (coarse) RUN(false, true);
+    else RUN(false, false);
+#undef RUN
     return check_launch("marching sweep");
 }
 #define INST(T, TO)                                                                                              \
     template ohm_status launch_march_sweep<T, TO>(const ohm_hier *, const T *, long long, const T *, const T *, \
-                                                  Coef, TO *, const int *, hipStream_t);
+                                                  Coef, TO *, const int *, hipStream_t, const T *, long long);
 INST(double, double)
 INST(float, float)
 INST(float, double)
