@@ -36,25 +36,26 @@ __device__ __forceinline__ int load_nbr(const int *nbr_tab, int b)
 
 __device__ __forceinline__ int side(int c) { return c < 0 ? -1 : (c >= NB ? 1 : 0); }
 
-// B (3 components) and eta of block b plus the one-cell halo into LDS: thread
-// u < 200 owns tile column (x, y) = u mod 100 and five consecutive z, issues
-// all its global loads, then stores them (ghost blocks for negative
-// neighbour entries, zeros for absent corner blocks)
-template <typename T>
+// B (3 components) and eta of block b plus the one-cell halo into LDS: each of
+// the first 200 (500) of 256 (512) threads owns a tile column (x, y) and five
+// (two) consecutive z, issues all its global loads, then stores them (ghost
+// blocks for negative neighbour entries, zeros for absent corner blocks)
+template <typename T, int THREADS>
 __device__ __forceinline__ void load_tile_b_eta(T (*sB)[TC], T *sE, const T *f, const T *g, long long cs,
                                                 long long gcs, const T *eta, const T *etag, const int *nbr)
 {
+    constexpr int EACH = THREADS == 512 ? 2 : 5;
     const int u = threadIdx.x;
-    if (u >= 2 * TW * TW) return;
+    if (u >= TW / EACH * TW * TW) return;
     const int col = u % (TW * TW), zh = u / (TW * TW);
     const int x = col % TW - 1, y = col / TW - 1;
     const int sx = side(x), sy = side(y);
     const int lxy = (x - NB * sx) + NB * (y - NB * sy);
     const int sxy = (sx + 1) + 3 * (sy + 1);
-    T v[5][4];
+    T v[EACH][4];
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int z = 5 * zh + k - 1, sz = side(z);
+    for (int k = 0; k < EACH; ++k) {
+        const int z = EACH * zh + k - 1, sz = side(z);
         const int n = nbr[sxy + 9 * (sz + 1)];
         const int li = lxy + NB * NB * (z - NB * sz);
         if (n >= 0) {
@@ -74,8 +75,8 @@ __device__ __forceinline__ void load_tile_b_eta(T (*sB)[TC], T *sE, const T *f, 
         }
     }
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const int t = col + TW * TW * (5 * zh + k);
+    for (int k = 0; k < EACH; ++k) {
+        const int t = col + TW * TW * (EACH * zh + k);
         sB[0][t] = v[k][0];
         sB[1][t] = v[k][1];
         sB[2][t] = v[k][2];
@@ -83,8 +84,9 @@ __device__ __forceinline__ void load_tile_b_eta(T (*sB)[TC], T *sE, const T *f, 
     }
 }
 
-template <typename T, int MODE>
-__global__ void __launch_bounds__(256)
+// THREADS 256 or 512: two cells or one a thread (see launch_blk_stencil)
+template <typename T, int MODE, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
               const uint8_t *__restrict__ cov_zero, const int *__restrict__ active,
               const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
@@ -96,7 +98,7 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
     __shared__ __align__(8) T sB[3][TC];
     __shared__ T sE[1][TC];
     __shared__ int snbr[27];
-    __shared__ double sred[6][4];
+    __shared__ double sred[6][8];
     const int b = xcd_block(blockIdx.x, nblk);
     const int mine = load_nbr(nbr_tab, b);
     const int pr = problem_of(prob_of, b);
@@ -106,65 +108,63 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
     }
     if (threadIdx.x < 27) snbr[threadIdx.x] = mine;
     __syncthreads();
-    load_tile_b_eta<T>(sB, sE[0], B, Bg, cs, gcs, eta, etag, snbr);
+    load_tile_b_eta<T, THREADS>(sB, sE[0], B, Bg, cs, gcs, eta, etag, snbr);
     // values read per cell after the stencil (S, or the other vector of the
     // first fused dot product that has one), loaded with the tile so that
     // their latency overlaps it
     constexpr bool HAS_S = MODE != MODE_APPLY;   // MODE_MEAN: the old value of out
-    T pS[2][3];
-    double pY[2][3];
+    constexpr int H = NC / THREADS;
+    T pS[H][3];
+    double pY[H][3];
+    const long long g0 = (long long)b * NC + threadIdx.x;
     int qy = -1;
     if (HAS_S) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                pS[half][c] = (MODE == MODE_MEAN ? out : S)[c * cs + (long long)b * NC + threadIdx.x + 256 * half];
+            for (int c = 0; c < 3; ++c) pS[h][c] = (MODE == MODE_MEAN ? out : S)[c * cs + g0 + THREADS * h];
     }
     if (MODE == MODE_APPLY) {
         for (int q = dots.ndot - 1; q >= 0; --q)
             if (dots.dot_y[q]) qy = q;
         if (qy >= 0)
 #pragma unroll
-            for (int half = 0; half < 2; ++half)
+            for (int h = 0; h < H; ++h)
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    pY[half][c] = dots.dot_y[qy][c * cs + (long long)b * NC + threadIdx.x + 256 * half];
+                for (int c = 0; c < 3; ++c) pY[h][c] = dots.dot_y[qy][c * cs + g0 + THREADS * h];
     }
     __syncthreads();
     const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]);
     const T c8 = cih2 * T(0.125), c2 = cih2 * T(0.5);
     const uint8_t cov = cov_zero ? cov_zero[b] : 0;
-    double ss[3] = {0, 0, 0}, mx[3] = {0, 0, 0};
-    T o[2][3];   // outputs kept for the fused dot products / restriction
+    double rd[H][3] = {};
+    T o[H][3];   // outputs kept for the fused dot products / restriction
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int cell = threadIdx.x + 256 * half;
+    for (int h = 0; h < H; ++h) {
+        const int cell = threadIdx.x + THREADS * h;
         const int x = cell & 7, y = (cell >> 3) & 7, z = cell >> 6;
         const int p = (x + 1) + TW * ((y + 1) + TW * (z + 1));
         const bool zero = (cov >> ((x >> 2) + 2 * (y >> 2) + 4 * (z >> 2))) & 1;
-        const long long gi = (long long)b * NC + cell;
+        const long long gi = g0 + THREADS * h;
         T dvs[3], als[3];
         divF_all<T, TW>(sB[0], sB[1], sB[2], sE[0], p, dvs, als);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const T LB = fma(c8, dvs[c], sB[c][p]);
             if (MODE == MODE_APPLY) {
-                o[half][c] = zero ? T(0) : LB;
-                out[c * cs + gi] = o[half][c];
+                o[h][c] = zero ? T(0) : LB;
+                out[c * cs + gi] = o[h][c];
             } else if (MODE == MODE_MEAN) {
-                out[c * cs + gi] = T(0.5) * (pS[half][c] + LB);
+                out[c * cs + gi] = T(0.5) * (pS[h][c] + LB);
             } else if (MODE == MODE_RESID_RESTRICT) {
-                o[half][c] = zero ? T(0) : pS[half][c] - LB;
+                o[h][c] = zero ? T(0) : pS[h][c] - LB;
             } else if (MODE == MODE_RESID) {
-                T r = zero ? T(0) : pS[half][c] - LB;
+                T r = zero ? T(0) : pS[h][c] - LB;
                 if (out) out[c * cs + gi] = r;
-                double rd = (double)r;
-                ss[c] += rd * rd;
-                mx[c] = fmax(mx[c], fabs(rd));
+                rd[h][c] = (double)r;
             } else {  // smoother half-sweep
                 T v = sB[c][p];
-                if (in_colour(x, y, z, colour)) v = relax_point(v, pS[half][c], dvs[c], als[c], c8, c2);
+                if (in_colour(x, y, z, colour)) v = relax_point(v, pS[h][c], dvs[c], als[c], c8, c2);
                 out[c * cs + gi] = v;
             }
         }
@@ -177,16 +177,15 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
         __syncthreads();
         for (int q = 0; q < dots.ndot; ++q)
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
+            for (int h = 0; h < H; ++h) {
                 double acc = 0.0;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    const long long gi = (long long)b * NC + threadIdx.x + 256 * half;
-                    const double y = q == qy ? pY[half][c]
-                                     : (dots.dot_y[q] ? dots.dot_y[q][c * cs + gi] : (double)o[half][c]);
-                    acc += (double)o[half][c] * y;
+                    const double y = q == qy ? pY[h][c]
+                                     : (dots.dot_y[q] ? dots.dot_y[q][c * cs + g0 + THREADS * h] : (double)o[h][c]);
+                    acc = fma((double)o[h][c], y, acc);
                 }
-                col[NC * q + threadIdx.x + 256 * half] = acc;
+                col[NC * q + threadIdx.x + THREADS * h] = acc;
             }
         __syncthreads();
         const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -203,9 +202,9 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
         // children of each coarse cell in the order of the restriction kernel
         __syncthreads();
 #pragma unroll
-        for (int half = 0; half < 2; ++half)
+        for (int h = 0; h < H; ++h)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) sB[c][threadIdx.x + 256 * half] = o[half][c];
+            for (int c = 0; c < 3; ++c) sB[c][threadIdx.x + THREADS * h] = o[h][c];
         __syncthreads();
         if (threadIdx.x < 64) {
             const int t = threadIdx.x;
@@ -226,25 +225,27 @@ k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__
         }
     }
     if (MODE == MODE_RESID && partials) {
-        // wavefront reduction, then across the 4 wavefronts in fixed order
+        // the 64 lanes of each plane, then the planes in order
         const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double a = ss[c], m = mx[c];
-            for (int o = 32; o > 0; o >>= 1) {
-                a += __shfl_down(a, o, 64);
-                m = fmax(m, __shfl_down(m, o, 64));
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                double a = rd[h][c] * rd[h][c], m = fabs(rd[h][c]);
+                for (int o = 32; o > 0; o >>= 1) {
+                    a += __shfl_down(a, o, 64);
+                    m = fmax(m, __shfl_down(m, o, 64));
+                }
+                if (lane == 0) {
+                    sred[c][wv + THREADS / 64 * h] = a;
+                    sred[3 + c][wv + THREADS / 64 * h] = m;
+                }
             }
-            if (lane == 0) {
-                sred[c][wv] = a;
-                sred[3 + c][wv] = m;
-            }
-        }
         __syncthreads();
         if (threadIdx.x < 6) {
             int k = threadIdx.x;
             double v = sred[k][0];
-            for (int w = 1; w < 4; ++w) v = (k < 3) ? v + sred[k][w] : fmax(v, sred[k][w]);
+            for (int w = 1; w < 8; ++w) v = (k < 3) ? v + sred[k][w] : fmax(v, sred[k][w]);
             partials[6 * (long long)b + k] = v;
         }
     }
@@ -472,9 +473,8 @@ k_prolong_blk(int nfine, const int *__restrict__ parent, const int *__restrict__
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const T *C = sc[c];
-            T v = T(27) * C[p0] + T(9) * (C[p0 + qx] + C[p0 + qy] + C[p0 + qz]) +
-                  T(3) * (C[p0 + qx + qy] + C[p0 + qx + qz] + C[p0 + qy + qz]) + C[p0 + qx + qy + qz];
-            v *= T(1.0 / 64.0);
+            const T v = trilinear<T>(C[p0], C[p0 + qx] + C[p0 + qy] + C[p0 + qz],
+                               C[p0 + qx + qy] + C[p0 + qx + qz] + C[p0 + qy + qz], C[p0 + qx + qy + qz]);
             if (c < ncomp) fine[c * fcs + (long long)b * NC + cell] = accumulate ? old[h][c] + v : v;
         }
     }
@@ -510,9 +510,8 @@ k_prolong_dense_blk0(int nblk, const int *__restrict__ ijk, const int *__restric
         auto at = [](int a, int bb, int cc) { return a + 6 * (bb + 6 * cc); };
         for (int c = 0; c < ncomp; ++c) {
             const T *C = sc[c];
-            T v = T(27) * C[at(i, j, k)] + T(9) * (C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)]) +
-                  T(3) * (C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)]) + C[at(i1, j1, k1)];
-            v *= T(1.0 / 64.0);
+            const T v = trilinear<T>(C[at(i, j, k)], C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)],
+                               C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)], C[at(i1, j1, k1)]);
             const long long gi = c * fcs + (long long)b * NC + cell;
             fine[gi] = base ? base[gi] + v : v;
         }
@@ -701,6 +700,12 @@ k_reduce_blocks(int nprob, int nrange, const long long *__restrict__ range, cons
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// The block stencil takes a thread per cell (8 instead of 20 tile loads in front
+// of one instead of two applications) while all groups of 512 threads are
+// resident at once, four to a compute unit.  FP64, us, two cells a thread / one:
+// 512 blocks 8.4 / 7.6, with the mean 9.4 / 8.6, 1,232 blocks 14.2 / 14.7.
+static bool one_cell_a_thread(const AmrLevelDev &L) { return L.nb <= 4 * COMPUTE_UNITS; }
+
 // Base levels that take the marching sweeps take the marching stencil too, up
 // to the 4 GiB a component that its 32-bit offsets reach.  L B on smaller
 // levels, us, per block / marching in segments of one block: 64^3 9.8 / 10.9,
@@ -724,19 +729,23 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
     if (level == 0 && march_stencil(L, sizeof(T)) && !cov_zero && !partials && out && mode != MODE_SMOOTH &&
         (dots.ndot == 0 || (given == 1 && std::is_same<T, double>::value)))
         return launch_march_stencil<T>(h, mode, B, cs, S, eta, coef_dev, out, 0, active, s, dots);
-    dim3 grid(L.nb), blk(256);
+    const bool one = one_cell_a_thread(L);
 #define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, out, colour, \
              partials, dots, nullptr, nullptr, 0
+#define RUN(mode)                                                              \
+    if (one) k_blk_stencil<T, mode, 512><<<L.nb, 512, 0, s>>>(ARGS);           \
+    else k_blk_stencil<T, mode, 256><<<L.nb, 256, 0, s>>>(ARGS)
     switch (mode) {
-    case MODE_APPLY: k_blk_stencil<T, MODE_APPLY><<<grid, blk, 0, s>>>(ARGS); break;
-    case MODE_RESID: k_blk_stencil<T, MODE_RESID><<<grid, blk, 0, s>>>(ARGS); break;
-    case MODE_SMOOTH: k_blk_stencil<T, MODE_SMOOTH><<<grid, blk, 0, s>>>(ARGS); break;
+    case MODE_APPLY: RUN(MODE_APPLY); break;
+    case MODE_RESID: RUN(MODE_RESID); break;
+    case MODE_SMOOTH: RUN(MODE_SMOOTH); break;
     case MODE_MEAN:
         if (cov_zero) return fail(OHM_ERR_ARG, "the mean with an application is for levels without covered cells");
-        k_blk_stencil<T, MODE_MEAN><<<grid, blk, 0, s>>>(ARGS);
+        RUN(MODE_MEAN);
         break;
     default: return fail(OHM_ERR_ARG, "unknown stencil mode %d", mode);
     }
+#undef RUN
 #undef ARGS
     return check_launch("block stencil");
 }
@@ -759,9 +768,11 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
 #undef ARGS
         return check_launch("residual + restriction by parts");
     }
-    k_blk_stencil<T, MODE_RESID_RESTRICT><<<L.nb, 256, 0, s>>>(
-        L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, coarse, 0,
-        nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs);
+#define ARGS L.nb, L.nbr, problem_table(h, L), nullptr, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, \
+             coarse, 0, nullptr, StencilDots{{nullptr, nullptr}, 0, nullptr}, L.dense_map, h->dense[1].probs, ccs
+    if (one_cell_a_thread(L)) k_blk_stencil<T, MODE_RESID_RESTRICT, 512><<<L.nb, 512, 0, s>>>(ARGS);
+    else k_blk_stencil<T, MODE_RESID_RESTRICT, 256><<<L.nb, 256, 0, s>>>(ARGS);
+#undef ARGS
     return check_launch("residual + restriction to dense");
 }
 

@@ -302,9 +302,8 @@ k_dense_prolong(DenseList flist, DenseList clist, const int *__restrict__ active
     auto at = [&](int a, int b, int d) { return c.off + a + (long long)c.nx * (b + (long long)c.ny * d); };
     for (int m = 0; m < ncomp; ++m) {
         const T *C = coarse + m * ccs;
-        T v = T(27) * C[at(i, j, k)] + T(9) * (C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)]) +
-              T(3) * (C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)]) + C[at(i1, j1, k1)];
-        v *= T(1.0 / 64.0);
+        const T v = trilinear<T>(C[at(i, j, k)], C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)],
+                           C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)], C[at(i1, j1, k1)]);
         const long long gi = m * fcs + f.off + cell;
         fine[gi] = base ? base[gi] + v : v;
     }

@@ -213,10 +213,8 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
                 for (int c = 0; c < 3; ++c) {
                     const T *a0 = ck + CW * CW * c + A, *a1 = ck + CW * CW * c + A1, *b0 = c1 + CW * CW * c + A,
                             *b1 = c1 + CW * CW * c + A1;
-                    T va = T(27) * a0[0] + T(9) * (a0[-1] + a1[0] + b0[0]) + T(3) * (a1[-1] + b0[-1] + b1[0]) + b1[-1];
-                    T vb = T(27) * a0[0] + T(9) * (a0[1] + a1[0] + b0[0]) + T(3) * (a1[1] + b0[1] + b1[0]) + b1[1];
-                    va *= T(1.0 / 64.0);
-                    vb *= T(1.0 / 64.0);
+                    const T va = trilinear<T>(a0[0], a0[-1] + a1[0] + b0[0], a1[-1] + b0[-1] + b1[0], b1[-1]);
+                    const T vb = trilinear<T>(a0[0], a0[1] + a1[0] + b0[0], a1[1] + b0[1] + b1[0], b1[1]);
                     v.b[c].a = v.b[c].a + va;
                     v.b[c].b = v.b[c].b + vb;
                 }
@@ -595,23 +593,23 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
             {
                 const T D = y_xp - y_xm;
                 const T tp = D + (Y[SW + 1] - Y[SW - 1]), tm = (Y[-SW + 1] - Y[-SW - 1]) + D;
-                const T gy = Eyp * fma(m4, x_yp - P.b[0], tp) - Eym * fma(m4, P.b[0] - x_ym, tm);
+                const T gy = fma(Eyp, fma(m4, x_yp - P.b[0], tp), -(Eym * fma(m4, P.b[0] - x_ym, tm)));
                 dv[0] = gy + fma(N.Ez, N.fx, -(P.Ez * P.fx));
             }
             {
                 const T D = x_yp - x_ym;
                 const T tp = D + (X[SW + 1] - X[-SW + 1]), tm = (X[SW - 1] - X[-SW - 1]) + D;
-                const T gx = Exp * fma(m4, y_xp - P.b[1], tp) - Exm * fma(m4, P.b[1] - y_xm, tm);
+                const T gx = fma(Exp, fma(m4, y_xp - P.b[1], tp), -(Exm * fma(m4, P.b[1] - y_xm, tm)));
                 dv[1] = gx + fma(N.Ez, N.fy, -(P.Ez * P.fy));
             }
             {
                 const T *X0 = sh[h][0] + u, *X2 = sh[h2][0] + u, *Y0 = sh[h][1] + u, *Y2 = sh[h2][1] + u;
                 const T D = N.b[0] - Q.b[0];
                 const T tp = D + (X0[1] - X2[1]), tm = (X0[-1] - X2[-1]) + D;
-                const T gx = Exp * fma(m4, z_xp - P.b[2], tp) - Exm * fma(m4, P.b[2] - z_xm, tm);
+                const T gx = fma(Exp, fma(m4, z_xp - P.b[2], tp), -(Exm * fma(m4, P.b[2] - z_xm, tm)));
                 const T D2 = N.b[1] - Q.b[1];
                 const T tp2 = D2 + (Y0[SW] - Y2[SW]), tm2 = (Y0[-SW] - Y2[-SW]) + D2;
-                const T gy = Eyp * fma(m4, z_yp - P.b[2], tp2) - Eym * fma(m4, P.b[2] - z_ym, tm2);
+                const T gy = fma(Eyp, fma(m4, z_yp - P.b[2], tp2), -(Eym * fma(m4, P.b[2] - z_ym, tm2)));
                 dv[2] = gx + gy;
             }
             const int p = q - 1;
@@ -653,7 +651,7 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
                     if (d >= nd) continue;
                     double a = 0.0;
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) a += (double)r[c] * (d == qy ? (double)s[c] : (double)r[c]);
+                    for (int c = 0; c < 3; ++c) a = fma((double)r[c], d == qy ? (double)s[c] : (double)r[c], a);
                     sum[d] = h == 2 && (p & 7) == 0 ? a : sum[d] + a;   // p = z0 - 2 + h + 4 i
                     if (h == 1 && (p & 7) == 7) {
                         double v = sum[d];

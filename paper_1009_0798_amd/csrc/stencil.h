@@ -11,7 +11,9 @@ namespace ohm {
 // the two cell resistivities at a face (twice the mean of eq. 11), t the
 // transverse four-point sum (four times the difference of eq. 10) and n the
 // normal difference (eq. 9), 8 h F = E (t - 4 n); scaling by 2, 4 or 8 is exact,
-// so the callers fold the factors into their coefficients.  The central
+// so the callers fold the factors into their coefficients.  (The sums are
+// spelled out in fused operations where a compiler could choose which product
+// to fuse: every kernel's values are the same.)  The central
 // difference of B_d along c at p is shared by the +d and -d faces.
 template <typename T, int W, int P = W * W>
 __device__ __forceinline__ void divF_all(const T *__restrict__ Bx, const T *__restrict__ By, const T *__restrict__ Bz,
@@ -29,28 +31,28 @@ __device__ __forceinline__ void divF_all(const T *__restrict__ Bx, const T *__re
     {   // component x: faces +-y (transverse d_x B_y) and +-z (d_x B_z)
         const T D = y_xp - y_xm;
         const T tp = D + (By[p + oy + ox] - By[p + oy - ox]), tm = (By[p - oy + ox] - By[p - oy - ox]) + D;
-        const T gy = Eyp * fma(m4, x_yp - x0, tp) - Eym * fma(m4, x0 - x_ym, tm);
+        const T gy = fma(Eyp, fma(m4, x_yp - x0, tp), -(Eym * fma(m4, x0 - x_ym, tm)));
         const T D2 = z_xp - z_xm;
         const T tp2 = D2 + (Bz[p + oz + ox] - Bz[p + oz - ox]), tm2 = (Bz[p - oz + ox] - Bz[p - oz - ox]) + D2;
-        const T gz = Ezp * fma(m4, x_zp - x0, tp2) - Ezm * fma(m4, x0 - x_zm, tm2);
+        const T gz = fma(Ezp, fma(m4, x_zp - x0, tp2), -(Ezm * fma(m4, x0 - x_zm, tm2)));
         dv[0] = gy + gz;
     }
     {   // component y: faces +-x (d_y B_x) and +-z (d_y B_z)
         const T D = x_yp - x_ym;
         const T tp = D + (Bx[p + ox + oy] - Bx[p + ox - oy]), tm = (Bx[p - ox + oy] - Bx[p - ox - oy]) + D;
-        const T gx = Exp * fma(m4, y_xp - y0, tp) - Exm * fma(m4, y0 - y_xm, tm);
+        const T gx = fma(Exp, fma(m4, y_xp - y0, tp), -(Exm * fma(m4, y0 - y_xm, tm)));
         const T D2 = z_yp - z_ym;
         const T tp2 = D2 + (Bz[p + oz + oy] - Bz[p + oz - oy]), tm2 = (Bz[p - oz + oy] - Bz[p - oz - oy]) + D2;
-        const T gz = Ezp * fma(m4, y_zp - y0, tp2) - Ezm * fma(m4, y0 - y_zm, tm2);
+        const T gz = fma(Ezp, fma(m4, y_zp - y0, tp2), -(Ezm * fma(m4, y0 - y_zm, tm2)));
         dv[1] = gx + gz;
     }
     {   // component z: faces +-x (d_z B_x) and +-y (d_z B_y)
         const T D = x_zp - x_zm;
         const T tp = D + (Bx[p + ox + oz] - Bx[p + ox - oz]), tm = (Bx[p - ox + oz] - Bx[p - ox - oz]) + D;
-        const T gx = Exp * fma(m4, z_xp - z0, tp) - Exm * fma(m4, z0 - z_xm, tm);
+        const T gx = fma(Exp, fma(m4, z_xp - z0, tp), -(Exm * fma(m4, z0 - z_xm, tm)));
         const T D2 = y_zp - y_zm;
         const T tp2 = D2 + (By[p + oy + oz] - By[p + oy - oz]), tm2 = (By[p - oy + oz] - By[p - oy - oz]) + D2;
-        const T gy = Eyp * fma(m4, z_yp - z0, tp2) - Eym * fma(m4, z0 - z_ym, tm2);
+        const T gy = fma(Eyp, fma(m4, z_yp - z0, tp2), -(Eym * fma(m4, z0 - z_ym, tm2)));
         dv[2] = gx + gy;
     }
     const T sx = Exm + Exp, sy = Eym + Eyp, sz = Ezm + Ezp;
@@ -100,28 +102,28 @@ __device__ __forceinline__ void divF_core(const Nbr<T> &n, T dv[3], T al[3])
     {   // component x: faces +-y (transverse d_x B_y) and +-z (d_x B_z)
         const T D = n.y_xp - n.y_xm;
         const T tp = D + (n.y_xpyp - n.y_xmyp), tm = (n.y_xpym - n.y_xmym) + D;
-        const T gy = Eyp * fma(m4, n.x_yp - n.x0, tp) - Eym * fma(m4, n.x0 - n.x_ym, tm);
+        const T gy = fma(Eyp, fma(m4, n.x_yp - n.x0, tp), -(Eym * fma(m4, n.x0 - n.x_ym, tm)));
         const T D2 = n.z_xp - n.z_xm;
         const T tp2 = D2 + n.p.zx, tm2 = n.m.zx + D2;
-        const T gz = Ezp * fma(m4, n.x_zp - n.x0, tp2) - Ezm * fma(m4, n.x0 - n.x_zm, tm2);
+        const T gz = fma(Ezp, fma(m4, n.x_zp - n.x0, tp2), -(Ezm * fma(m4, n.x0 - n.x_zm, tm2)));
         dv[0] = gy + gz;
     }
     {   // component y: faces +-x (d_y B_x) and +-z (d_y B_z)
         const T D = n.x_yp - n.x_ym;
         const T tp = D + (n.x_xpyp - n.x_xpym), tm = (n.x_xmyp - n.x_xmym) + D;
-        const T gx = Exp * fma(m4, n.y_xp - n.y0, tp) - Exm * fma(m4, n.y0 - n.y_xm, tm);
+        const T gx = fma(Exp, fma(m4, n.y_xp - n.y0, tp), -(Exm * fma(m4, n.y0 - n.y_xm, tm)));
         const T D2 = n.z_yp - n.z_ym;
         const T tp2 = D2 + n.p.zy, tm2 = n.m.zy + D2;
-        const T gz = Ezp * fma(m4, n.y_zp - n.y0, tp2) - Ezm * fma(m4, n.y0 - n.y_zm, tm2);
+        const T gz = fma(Ezp, fma(m4, n.y_zp - n.y0, tp2), -(Ezm * fma(m4, n.y0 - n.y_zm, tm2)));
         dv[1] = gx + gz;
     }
     {   // component z: faces +-x (d_z B_x) and +-y (d_z B_y)
         const T D = n.x_zp - n.x_zm;
         const T tp = D + (n.p.x_xp - n.m.x_xp), tm = (n.p.x_xm - n.m.x_xm) + D;
-        const T gx = Exp * fma(m4, n.z_xp - n.z0, tp) - Exm * fma(m4, n.z0 - n.z_xm, tm);
+        const T gx = fma(Exp, fma(m4, n.z_xp - n.z0, tp), -(Exm * fma(m4, n.z0 - n.z_xm, tm)));
         const T D2 = n.y_zp - n.y_zm;
         const T tp2 = D2 + (n.p.y_yp - n.m.y_yp), tm2 = (n.p.y_ym - n.m.y_ym) + D2;
-        const T gy = Eyp * fma(m4, n.z_yp - n.z0, tp2) - Eym * fma(m4, n.z0 - n.z_ym, tm2);
+        const T gy = fma(Eyp, fma(m4, n.z_yp - n.z0, tp2), -(Eym * fma(m4, n.z0 - n.z_ym, tm2)));
         dv[2] = gx + gy;
     }
     const T sx = Exm + Exp, sy = Eym + Eyp, sz = Ezm + Ezp;
@@ -195,6 +197,14 @@ template <typename T>
 __device__ __forceinline__ T relax_point(T b, T s, T dv, T al, T c8, T c2)
 {
     return b + relax_div(s - fma(c8, dv, b), fma(c2, al, T(1)));
+}
+
+// Trilinear prolongation: c the parent, s1, s2 and c3 the sums of its
+// neighbours on the child's side across one, two and three axes.
+template <typename T>
+__device__ __forceinline__ T trilinear(T c, T s1, T s2, T c3)
+{
+    return (fma(T(3), s2, fma(T(9), s1, T(27) * c)) + c3) * T(1.0 / 64.0);
 }
 
 }  // namespace ohm

@@ -181,9 +181,8 @@ struct TileCoarse {
         const int i1 = i + ((x & 1) ? 1 : -1), j1 = j + ((y & 1) ? 1 : -1), k1 = k + ((z & 1) ? 1 : -1);
         const T *C = sC + Tl::NCOARSE * c;
         auto at = [](int a, int bb, int cc) { return a + 8 * (bb + Tl::CY * cc); };
-        T v = T(27) * C[at(i, j, k)] + T(9) * (C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)]) +
-              T(3) * (C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)]) + C[at(i1, j1, k1)];
-        v *= T(1.0 / 64.0);
+        const T v = trilinear<T>(C[at(i, j, k)], C[at(i1, j, k)] + C[at(i, j1, k)] + C[at(i, j, k1)],
+                           C[at(i1, j1, k)] + C[at(i1, j, k1)] + C[at(i, j1, k1)], C[at(i1, j1, k1)]);
         return base + v;
     }
 };
