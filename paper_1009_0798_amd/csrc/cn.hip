@@ -376,7 +376,7 @@ struct Solver {
         const int d = -lev;
         const int nuc1 = o->nu_coarse > 0 ? o->nu_coarse : nu1, nuc2 = o->nu_coarse > 0 ? o->nu_coarse : nu2;
         const int f1 = zero_guess ? SMOOTH_ZERO : (ecur_of(d) == dv(P.d_tmp, d) ? SMOOTH_FROM_TMP : 0);
-        if (zero_guess && nuc1 == 1 && o->ordering == 0 && dense_down_fuses(h, -d)) {
+        if (zero_guess && nuc1 == 1 && o->ordering == 0 && dense_down_fuses<T>(h, -d)) {
             OHM_TRY(launch_dense_down<T>(h, -d, dv(P.d_e, d), dv(P.d_rhs, d), dv(P.d_eta, d), lam_dt, dv(P.d_rhs, d + 1),
                                          active, st));
             ecur[d] = dv(P.d_e, d);

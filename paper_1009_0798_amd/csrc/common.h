@@ -357,6 +357,7 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
 // for handles where some continuing problem is not made of 8^3 tiles
 // from a zero guess: one red-black sweep into e, its residual and restriction
 // (levels for which dense_down_fuses)
+template <typename T>
 bool dense_down_fuses(const ohm_hier *h, int level);
 template <typename T>
 ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,

@@ -1,6 +1,8 @@
 // Kernels on the dense multigrid levels below the base grid (one thread per
 // cell, 256-cell tiles that never straddle two problems) and the coarsest-grid
 // solve (per-problem dense FP64 inverse built on the device).
+#include <algorithm>
+
 #include "common.h"
 #include "stencil.h"
 #include "sweep.h"
@@ -778,24 +780,31 @@ ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const
     return OHM_OK;
 }
 
-// parts a tile is split over on the way down from a dense level, as in its
-// sweeps (1: the level takes the kernels of whole tiles); the wrap of the three
-// halo cells is for edges of 4 cells and more
+// parts a tile is split over on the way down from a dense level (1: the level
+// takes the kernels of whole tiles): as in its sweeps; but in FP32, whose parts
+// run five or four to a compute unit, the launch with the sweep stays ahead of
+// the two of whole tiles at any size (halves: 233 tiles 12.2 -> 9.1 us, 960
+// tiles 27.2 -> 25.6, 1,359 31.1 -> 29.4; FP64, 512 tiles: 21.7 -> 30.7).  The
+// wrap of the three halo cells is for edges of 4 cells and more.
+template <typename T, bool ZERO>
 static int dense_down_parts(const ohm_hier *h, int level)
 {
     const DenseLevelDev &D = h->dense[-level];
-    const bool ok = D.nptile == 0 && D.nftile > 0 && D.edge >= 4 && (unsigned long long)D.ncells * 8 <= 0xFFFFFFFFull;
-    return ok ? tile_parts(D.nftile) : 1;
+    if (D.nptile > 0 || D.nftile == 0 || D.edge < 4 || (unsigned long long)D.ncells * 8 > 0xFFFFFFFFull) return 1;
+    const int parts = tile_parts(D.nftile);
+    return ZERO && sizeof(T) == 4 ? std::max(parts, 2) : parts;
 }
-bool dense_down_fuses(const ohm_hier *h, int level) { return dense_down_parts(h, level) > 1; }
+template <typename T>
+bool dense_down_fuses(const ohm_hier *h, int level) { return dense_down_parts<T, true>(h, level) > 1; }
 
 template <typename T, bool ZERO>
 static ohm_status dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s)
 {
     const DenseLevelDev &D = h->dense[-level], &C = h->dense[-level + 1];
-#define ARGS dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active, coef_dev.p, coef_dev.v, e, S, eta, coarse, D.ncells, C.ncells
-    if (dense_down_parts(h, level) == 4)
+#define ARGS dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active, coef_dev.p, coef_dev.v, e, S, eta, coarse, \
+             D.ncells, C.ncells
+    if (dense_down_parts<T, ZERO>(h, level) == 4)
         k_dense_down<T, ZERO, Tile<4, 4>><<<4 * D.nftile, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
     else
         k_dense_down<T, ZERO, Tile<8, 4>><<<2 * D.nftile, Tile<8, 4>::THREADS, 0, s>>>(ARGS);
@@ -807,7 +816,7 @@ template <typename T>
 ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s)
 {
-    if (!dense_down_fuses(h, level)) return fail(OHM_ERR_ARG, "dense level %d: too many tiles for the fused way down", level);
+    if (!dense_down_fuses<T>(h, level)) return fail(OHM_ERR_ARG, "dense level %d: too many tiles for the fused way down", level);
     return dense_down<T, true>(h, level, e, S, eta, coef_dev, coarse, active, s);
 }
 
@@ -822,7 +831,7 @@ ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B,
         OHM_TRY(launch_dense_stencil<T>(h, level, MODE_RESID, B, S, eta, coef_dev, res, 0, false, active, s));
         return launch_dense_restrict<T>(h, level, res, coarse, 3, active, s);
     }
-    if (dense_down_parts(h, level) > 1)
+    if (dense_down_parts<T, false>(h, level) > 1)
         return dense_down<T, false>(h, level, const_cast<T *>(B), S, eta, coef_dev, coarse, active, s);
     k_dense_resid_restrict<T><<<D.nftile, 256, 0, s>>>(dense_list(h, D, D.ftiles), dense_list(h, C, C.tiles_all), active,
                                                         coef_dev.p, coef_dev.v, B, S, eta, coarse, D.ncells, C.ncells);
@@ -1007,6 +1016,7 @@ size_t coarse_job_bytes() { return sizeof(CoarseJob); }
                                                  hipStream_t);                                                 \
     template ohm_status launch_dense_resid_restrict<T>(const ohm_hier *, int, const T *, const T *, const T *, \
                                                        Coef, T *, T *, const int *, hipStream_t);    \
+    template bool dense_down_fuses<T>(const ohm_hier *, int);                                                  \
     template ohm_status launch_dense_down<T>(const ohm_hier *, int, T *, const T *, const T *, Coef, T *, \
                                              const int *, hipStream_t);                                          \
     template ohm_status launch_dense_prolong<T>(const ohm_hier *, int, const T *, T *, int, int, const int *,  \
