@@ -31,12 +31,12 @@ SERVE_SCHEDULE = (2, 2, 0)   # (pre, post, below the base grid; 0 = as the base 
 
 
 def kernel_source_hash() -> str:
-    """Hash of the sources of the block-level stencil kernels (the block
-    kernels, the sweep body and the stencil they use); the counter traffic
+    """Hash of the sources of the level-0 stencil kernels (marching and per
+    block, the sweep body and the stencil they use); the counter traffic
     recorded under profiles/ is valid only for that source."""
     import hashlib
     csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1009_0798_amd", "csrc")
-    body = "".join(open(os.path.join(csrc, f)).read() for f in ("k_block.hip", "sweep.h", "stencil.h"))
+    body = "".join(open(os.path.join(csrc, f)).read() for f in ("k_march.hip", "march.h", "k_block.hip", "sweep.h", "stencil.h"))
     return hashlib.sha256(body.encode()).hexdigest()[:16]
 
 
@@ -44,11 +44,11 @@ def kernel_source_hash() -> str:
 # --roofline-only: tag -> (kernel name prefix, algorithmic bytes per cell,
 # dispatches to average: the first k of that name, or all when None)
 COUNTED = {
-    "sweep_f64": ("k_blk_sweep<double, 0, false, true>", 80, 12),
-    "sweep_f32": ("k_blk_sweep<float, 0, false, false>", 40, 12),
-    "apply_f64": ("k_blk_stencil<double, 0>", 56, 12),
-    "resid_f64": ("k_blk_stencil<double, 1>", 80, 12),
-    "resid_restrict_f64": ("k_blk_stencil<double, 3>", 59, None),
+    "sweep_f64": ("k_march_sweep<double, double, false, false>", 80, 12),
+    "sweep_f32": ("k_march_sweep<float, float, false, false>", 40, 12),
+    "apply_f64": ("k_march_stencil<double, 0, false>", 56, 12),
+    "resid_f64": ("k_march_stencil<double, 1, false>", 80, 12),
+    "resid_restrict_f64": ("k_march_stencil<double, 3, false>", 59, None),
 }
 
 
@@ -755,7 +755,7 @@ def main():
                    "cells": cells, "outer": "BiCGStab",
                    "cycle": f"V{SCHEDULE[0]} (FP64) / V{SCHEDULE[1]} (mixed), {NU_COARSE} sweep below the base grid",
                    "iterations_per_step": f64["iters"]},
-        "roofline": {"kernel": "k_blk_sweep<double> (one fused red-black sweep, level 0)",
+        "roofline": {"kernel": "k_march_sweep<double> (one fused red-black sweep, level 0)",
                      "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": counter_traffic("sweep_f64", n),
                      "us_per_launch": t_sw * 1e6, "bytes_per_launch": bytes_sw,
@@ -768,7 +768,7 @@ def main():
         _, Hh, Bh, Sh, Eh, dth = random_level(nh)
         ch = nh ** 3
         t_h = smoother_rate(ohm, Hh, Bh, Sh, Eh, 0.5 * dth, torch.float64)
-        leg = {"kernel": "k_blk_sweep<double> (one fused red-black sweep, level 0)", "bound": "hbm",
+        leg = {"kernel": "k_march_sweep<double> (one fused red-black sweep, level 0)", "bound": "hbm",
                "achieved": ch * 80 / t_h / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                "frac": ch * 80 / t_h / 1e9 / HBM_PEAK_GBS, "traffic": counter_traffic("sweep_f64", nh),
                "us_per_launch": t_h * 1e6, "bytes_per_launch": ch * 80,

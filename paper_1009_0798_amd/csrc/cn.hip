@@ -355,9 +355,9 @@ struct Solver {
             // level 5.4 + 5.1 us -> 7.3, a marching 128^3 one 24.2 + 39.5 -> 51.7
             const bool in_tmp = fz && (nu2 & 1) && zero_guess && nu1 > 0;
             OHM_TRY(smooth_blk(0, nu1, zf | (in_tmp ? SMOOTH_TO_TMP : 0)));
-            OHM_TRY(launch_resid_restrict_blk0<T>(h, mg(in_tmp ? P.tmp : P.e, 0), at<T>(P.mg_g) + P.LG[0] * NC, VN, GN, mg(P.rhs, 0),
-                                                  etaT(0), etagT(0), lam_dt, dv(P.d_rhs, 1), h->dense_cells[1],
-                                                  active, st));
+            OHM_TRY(launch_resid_restrict_blk0<T>(h, mg(in_tmp ? P.tmp : P.e, 0), at<T>(P.mg_g) + P.LG[0] * NC, VN, GN,
+                                                  mg(P.rhs, 0), etaT(0), etagT(0), lam_dt, dv(P.d_rhs, 1),
+                                                  h->dense_cells[1], active, st));
             OHM_TRY(down_dense(1));
             const T *e1 = ecur_of(1);
             if (fz && nu2 > 0 && (!(nu2 & 1) || in_tmp)) {

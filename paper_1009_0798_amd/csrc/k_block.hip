@@ -89,7 +89,8 @@ template <typename T, int MODE, int THREADS>
 __global__ void __launch_bounds__(THREADS)
 k_blk_stencil(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
               const uint8_t *__restrict__ cov_zero, const int *__restrict__ active,
-              const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
+              const double *__restrict__ inv_h2_p,
+            const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, const T *__restrict__ Bg, long long cs, long long gcs,
               const T *__restrict__ S, const T *__restrict__ eta, const T *__restrict__ etag,
               T *__restrict__ out, int colour, double *__restrict__ partials, StencilDots dots,
@@ -300,7 +301,8 @@ struct GhostBlockAddr {
 template <typename T, int MODE, bool O64, bool DIRECT, typename Tl>
 __global__ void __launch_bounds__(Tl::THREADS)
 k_blk_sweep(int nblk, const int *__restrict__ nbr_tab, const int *__restrict__ prob_of,
-            const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
+            const int *__restrict__ active, const double *__restrict__ inv_h2_p,
+            const double *__restrict__ coef_p, double coef_v,
             const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
             void *__restrict__ out, const int *__restrict__ ijk, const DenseProbDev *__restrict__ dp,
             const T *__restrict__ coarse, long long ccs, const T *__restrict__ Bg, long long gcs,
@@ -730,8 +732,8 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
         (dots.ndot == 0 || (given == 1 && std::is_same<T, double>::value)))
         return launch_march_stencil<T>(h, mode, B, cs, S, eta, coef_dev, out, 0, active, s, dots);
     const bool one = one_cell_a_thread(L);
-#define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, etag, out, colour, \
-             partials, dots, nullptr, nullptr, 0
+#define ARGS L.nb, L.nbr, problem_table(h, L), cov_zero, active, L.inv_h2, coef_dev.p, coef_dev.v, B, Bg, cs, gcs, S, eta, \
+             etag, out, colour, partials, dots, nullptr, nullptr, 0
 #define RUN(mode)                                                              \
     if (one) k_blk_stencil<T, mode, 512><<<L.nb, 512, 0, s>>>(ARGS);           \
     else k_blk_stencil<T, mode, 256><<<L.nb, 256, 0, s>>>(ARGS)
@@ -761,8 +763,10 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     if (march_stencil(L, sizeof(T)))
         return launch_march_stencil<T>(h, MODE_RESID_RESTRICT, B, cs, S, eta, coef_dev, coarse, ccs, active, s);
     const int parts = tile_parts(L.nb);
-    if (parts > 1 && L.complete27 && (((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T))) == 0) {
-#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, L.dense_map, h->dense[1].probs, coarse, ccs
+    const bool pairs = ((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T)) == 0;
+    if (parts > 1 && L.complete27 && pairs) {
+#define ARGS L.nb, L.nbr, problem_table(h, L), active, L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, L.dense_map, \
+             h->dense[1].probs, coarse, ccs
         if (parts == 4) k_blk_down<T, Tile<4, 4>><<<4 * L.nb, Tile<4, 4>::THREADS, 0, s>>>(ARGS);
         else k_blk_down<T, Tile<8, 4>><<<2 * L.nb, Tile<8, 4>::THREADS, 0, s>>>(ARGS);
 #undef ARGS

@@ -317,7 +317,8 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
 template <typename T, typename TO, bool ZERO, bool CO>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
 k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
-              const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
+              const int *__restrict__ active, const double *__restrict__ inv_h2_p,
+              const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
               TO *__restrict__ out, unsigned obytes, const DenseProbDev *__restrict__ dp,
               const T *__restrict__ coarse, long long ccs)
@@ -452,7 +453,8 @@ struct Plane {
 template <typename T, int MODE, bool DOTS>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
 k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
-                const int *__restrict__ active, const double *__restrict__ inv_h2_p, const double *__restrict__ coef_p, double coef_v,
+                const int *__restrict__ active, const double *__restrict__ inv_h2_p,
+              const double *__restrict__ coef_p, double coef_v,
                 const T *__restrict__ B, long long cs, const T *S, const T *__restrict__ eta, T *out, unsigned obytes,
                 StencilDots dots, unsigned pbytes, const int *__restrict__ dense_map,
                 const DenseProbDev *__restrict__ dp, long long ccs)
@@ -514,7 +516,8 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
     auto column = [](int a, int b) { return ((a + 8) >> 3) + 4 * ((b + 8) >> 3); };
     const int io = column(x, y), ih = column(hx, hy), ic = column(cx, cy);
     auto at = [&](int i, int cell, int P) {
-        return ((unsigned)ids[i + 16 * (((P - z0) >> 3) + 1)] * (unsigned)NC + (unsigned)(cell + 64 * (P & 7))) * (unsigned)sizeof(T);
+        const unsigned b = (unsigned)ids[i + 16 * (((P - z0) >> 3) + 1)];
+        return (b * (unsigned)NC + (unsigned)(cell + 64 * (P & 7))) * (unsigned)sizeof(T);
     };
     auto cell = [](int a, int b) { return (a & 7) + 8 * (b & 7); };
     const int lo = cell(x, y), lh = cell(hx, hy), lc = cell(cx, cy);
@@ -631,9 +634,8 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
                     acc[c] += lanes<LANES_XOR1>(r8);
                 }
                 if (h & 1) {
-                    const unsigned oc = mine && (lane & 9) == 0
-                                            ? (unsigned)(cmap[io + 16 * (((p - z0) >> 3) + 1)] + ccell + cnxy * ((p & 7) >> 1)) * (unsigned)sizeof(T)
-                                            : 0xFFFFFFF0u;
+                    const int cell = cmap[io + 16 * (((p - z0) >> 3) + 1)] + ccell + cnxy * ((p & 7) >> 1);
+                    const unsigned oc = mine && (lane & 9) == 0 ? (unsigned)cell * (unsigned)sizeof(T) : 0xFFFFFFF0u;
                     store_one(O0, oc, acc[0] * T(0.125));
                     store_one(O1, oc, acc[1] * T(0.125));
                     store_one(O2, oc, acc[2] * T(0.125));
@@ -697,7 +699,8 @@ ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long lo
                                 StencilDots dots)
 {
     const AmrLevelDev &L = h->amr[0];
-    const unsigned obytes = (unsigned)((mode == MODE_RESID_RESTRICT ? (unsigned long long)ccs : (unsigned long long)L.nb * NC) * sizeof(T));
+    const unsigned long long cells = mode == MODE_RESID_RESTRICT ? ccs : (long long)L.nb * NC;
+    const unsigned obytes = (unsigned)(cells * sizeof(T));
     const unsigned pbytes = (unsigned)((unsigned long long)L.nb * dots.ndot * sizeof(double));
     const MarchTile *tiles = (const MarchTile *)L.march;
 #define RUN(mode, d, S) k_march_stencil<T, mode, d><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
