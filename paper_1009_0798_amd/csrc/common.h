@@ -51,6 +51,13 @@ std::mutex &capture_mutex();
 // interpolation would need missing coarse cells).
 constexpr int NBR_NONE = -(1 << 30);
 
+// segments of each XCD's groups: XCD x takes entries first[x] to first[x + 1]
+// of the list, one after the other; the longest list has `longest`
+struct MarchLists {
+    int first[NXCD + 1];
+    int longest;
+};
+
 struct AmrLevelDev {
     int nb = 0;                // blocks
     int ng = 0;                // coarse-fine ghost blocks
@@ -73,8 +80,9 @@ struct AmrLevelDev {
     // level 0 only: block at each position of the problems' boxes (x fastest,
     // problem after problem) and the column segments of the marching kernels
     int *bmap = nullptr;
-    int nmarch = 0;
+    int nmarch = 0;            // (0: the level does not march)
     int *march = nullptr;
+    MarchLists mlists = {};
     // refluxing: coarse cells of this level with faces next to covered cells
     int nrf = 0;
     int *rf = nullptr;         // [nrf][RF_INTS]

@@ -124,39 +124,70 @@ ohm_status upload(V **dptr, const std::vector<V> &h)
     return OHM_OK;
 }
 
-// The marching kernels' work on a base level cut into segments of sb blocks, in
-// planes one after the other on the busiest of the 512 places (two groups on
-// each of the 256 compute units): a segment of n planes costs its n planes,
-// four of halo and about as much again to start; groups that have a compute
-// unit each march about a third faster.
-static double march_cost(const ohm_hier *H, int sb)
+// A part of one layer of a problem's column segments: columns c0 to c1 (x
+// fastest) of the segments that start at block z
+struct MarchPart {
+    int prob, z, c0, c1, planes;
+};
+
+// Segments of sb blocks, problem after problem, layer after layer, cut into one
+// run of equal work for each XCD (columns side by side share halos on its L2).
+// Returns the planes one after the other on the busiest of an XCD's 64 places
+// (two groups on each of its 32 compute units): a segment of n planes costs its
+// n planes, four of halo and about as much again to start; groups that have a
+// compute unit each march about a third faster.
+static double march_plan(const ohm_hier *H, int sb, std::vector<MarchPart> out[NXCD])
 {
-    constexpr int PLACES = 512;
-    double total = 0.0;
-    long long w = 0;
-    for (const ohm_prob_host &P : H->probs) {
-        const long long cols = (long long)((P.bb[0] + 1) / 2) * ((P.bb[1] + 1) / 2), segs = (P.bb[2] + sb - 1) / sb;
-        w += cols * segs;
-        total += (double)cols * (NB * P.bb[2] + 8.0 * segs);
+    constexpr int PLACES = 64;
+    std::vector<MarchPart> all;
+    double total = 0.0, done = 0.0;
+    for (size_t p = 0; p < H->probs.size(); ++p) {
+        const ohm_prob_host &P = H->probs[p];
+        const int cols = ((P.bb[0] + 1) / 2) * ((P.bb[1] + 1) / 2);
+        for (int z = 0; z < P.bb[2]; z += sb) {
+            all.push_back({(int)p, z, 0, cols, NB * std::min(sb, P.bb[2] - z) + 8});
+            total += (double)cols * all.back().planes;
+        }
     }
-    if (w > 8 * PLACES) return total / PLACES;   // evenly spread
-    std::vector<double> place(PLACES, 0.0);
-    for (const ohm_prob_host &P : H->probs) {
-        const long long cols = (long long)((P.bb[0] + 1) / 2) * ((P.bb[1] + 1) / 2);
-        for (int z = 0; z < P.bb[2]; z += sb)
-            for (long long c = 0; c < cols; ++c) {
+    double load[NXCD] = {}, longest = 0.0;
+    int count[NXCD] = {}, x = 0;
+    for (int k = 0; k < NXCD; ++k) out[k].clear();
+    for (MarchPart m : all)
+        while (m.c0 < m.c1) {
+            // columns up to where this XCD's share of the work ends (rounded)
+            const double left = total * (x + 1) / NXCD - done;
+            const int n = x == NXCD - 1 ? m.c1 - m.c0 : std::min(m.c1 - m.c0, std::max(0, (int)(left / m.planes + 0.5)));
+            if (n > 0) {
+                out[x].push_back({m.prob, m.z, m.c0, m.c0 + n, m.planes});
+                load[x] += (double)n * m.planes;
+                done += (double)n * m.planes;
+                count[x] += n;
+                m.c0 += n;
+            }
+            if (m.c0 < m.c1) ++x;
+        }
+    bool alone = true;
+    for (x = 0; x < NXCD; ++x) {
+        alone = alone && count[x] <= PLACES / 2;
+        if (count[x] > 8 * PLACES) {   // evenly spread
+            longest = std::max(longest, load[x] / PLACES);
+            continue;
+        }
+        std::vector<double> place(PLACES, 0.0);
+        for (const MarchPart &m : out[x])
+            for (int c = m.c0; c < m.c1; ++c) {
                 std::pop_heap(place.begin(), place.end(), std::greater<double>());
-                place.back() += NB * std::min(sb, P.bb[2] - z) + 8;
+                place.back() += m.planes;
                 std::push_heap(place.begin(), place.end(), std::greater<double>());
             }
+        longest = std::max(longest, *std::max_element(place.begin(), place.end()));
     }
-    const double longest = *std::max_element(place.begin(), place.end());
-    return w <= PLACES / 2 ? 0.65 * longest : longest;
+    return alone ? 0.65 * longest : longest;
 }
 
 // Tables of the marching kernels of the base level, where they are the faster
 // ones: a sweep per block takes 7.0 us (FP64; FP32 4.2) for every 512 blocks,
-// a marching sweep 1.85 us (1.2) for every plane of march_cost, so that it
+// a marching sweep 1.85 us (1.2) for every plane of march_plan, so that it
 // takes over where the blocks are more than 140 times the planes: 128^3 (4,096
 // blocks, 24 planes: FP64 56 -> 44 us), 64 problems of 32^3 (the same counts:
 // 56 -> 46), 160 x 128 x 192 (119 -> 83), but not 112^3 (2,744 blocks, 24
@@ -164,36 +195,43 @@ static double march_cost(const ohm_hier *H, int sb)
 static ohm_status march_tables(ohm_hier *H)
 {
     AmrLevelDev &L = H->amr[0];
+    std::vector<MarchPart> plan[NXCD], best_plan[NXCD];
     int sb = 0;
     double best = L.nb / 140.0;
     if (best > 16)   // no segment costs less
         for (int s = 1; s <= MARCH_MAX_NBZ; ++s) {
-            const double c = march_cost(H, s);
+            const double c = march_plan(H, s, plan);
             if (c < best) {
                 best = c;
                 sb = s;
+                for (int x = 0; x < NXCD; ++x) best_plan[x].swap(plan[x]);
             }
         }
     if (sb == 0) return OHM_OK;
     std::vector<int> bmap(L.nb), march;
-    for (size_t p = 0; p < H->probs.size(); ++p) {
-        const ohm_prob_host &P = H->probs[p];
-        const int off = (int)P.boff[0], nx = P.bb[0], ny = P.bb[1], nz = P.bb[2];
+    for (const ohm_prob_host &P : H->probs) {
+        const int off = (int)P.boff[0], nx = P.bb[0], ny = P.bb[1];
         for (int b = 0; b < P.nb[0]; ++b) {
             const int32_t *q = &P.blocks[0][3 * b];
             bmap[off + q[0] + nx * (q[1] + ny * q[2])] = off + b;
         }
-        // x fastest: each XCD takes a contiguous part of the list, groups that
-        // share halos in x and y march side by side on one L2
-        for (int z = 0; z < nz; z += sb)
-            for (int y = 0; y < ny; y += MT / NB)
-                for (int x = 0; x < nx; x += MT / NB) {
-                    const MarchTile M = {(int)p, x, y, z, std::min(sb, nz - z), nx, ny, nz, off, {}};
-                    const int *m = (const int *)&M;
-                    march.insert(march.end(), m, m + sizeof M / sizeof(int));
-                }
     }
-    L.nmarch = (int)(march.size() / (sizeof(MarchTile) / sizeof(int)));
+    constexpr int INTS = sizeof(MarchTile) / sizeof(int);
+    for (int x = 0; x < NXCD; ++x) {
+        L.mlists.first[x] = (int)march.size() / INTS;
+        for (const MarchPart &m : best_plan[x]) {
+            const ohm_prob_host &P = H->probs[m.prob];
+            const int nx = P.bb[0], ny = P.bb[1], nz = P.bb[2], cx = (nx + 1) / 2;
+            for (int c = m.c0; c < m.c1; ++c) {
+                const MarchTile M = {m.prob, 2 * (c % cx), 2 * (c / cx), m.z, std::min(sb, nz - m.z), nx, ny, nz,
+                                     (int)P.boff[0], {}};
+                const int *v = (const int *)&M;
+                march.insert(march.end(), v, v + INTS);
+            }
+        }
+        L.mlists.longest = std::max(L.mlists.longest, (int)march.size() / INTS - L.mlists.first[x]);
+    }
+    L.nmarch = L.mlists.first[NXCD] = (int)march.size() / INTS;
     OHM_TRY(upload(&L.bmap, bmap));
     return upload(&L.march, march);
 }

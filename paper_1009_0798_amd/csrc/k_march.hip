@@ -316,7 +316,7 @@ __device__ __forceinline__ void march_loop(T *sh, const int *ids, const T *__res
 
 template <typename T, typename TO, bool ZERO, bool CO>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
-k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
+k_march_sweep(MarchLists lists, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
               const int *__restrict__ active, const double *__restrict__ inv_h2_p,
               const double *__restrict__ coef_p, double coef_v,
               const T *__restrict__ B, long long cs, const T *__restrict__ S, const T *__restrict__ eta,
@@ -327,8 +327,9 @@ k_march_sweep(int ntile, const MarchTile *__restrict__ tiles, const int *__restr
     __shared__ T sco[CO ? 4 * CP : 1];
     __shared__ int place[MARCH_THREADS / 64];
     __shared__ int ids[16 * (MARCH_MAX_NBZ + 2)];
-    const int w = blockIdx.x, q8 = ntile / NXCD, r8 = ntile % NXCD, xc = w % NXCD;
-    const MarchTile &M = tiles[xc * q8 + min(xc, r8) + w / NXCD];
+    const int xc = blockIdx.x % NXCD, seg = lists.first[xc] + (int)blockIdx.x / NXCD;
+    if (seg >= lists.first[xc + 1]) return;
+    const MarchTile &M = tiles[seg];
     const int pr = M.prob;
     if (active && !active[pr]) return;
     const T cih2 = T(coef_of(coef_p[pr], coef_v)) * T(inv_h2_p[pr]);
@@ -452,7 +453,7 @@ struct Plane {
 
 template <typename T, int MODE, bool DOTS>
 __global__ void __launch_bounds__(MARCH_THREADS, 2)
-k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
+k_march_stencil(MarchLists lists, const MarchTile *__restrict__ tiles, const int *__restrict__ bmap,
                 const int *__restrict__ active, const double *__restrict__ inv_h2_p,
               const double *__restrict__ coef_p, double coef_v,
                 const T *__restrict__ B, long long cs, const T *S, const T *__restrict__ eta, T *out, unsigned obytes,
@@ -464,8 +465,9 @@ k_march_stencil(int ntile, const MarchTile *__restrict__ tiles, const int *__res
     __shared__ T sh[4][4][SP];
     __shared__ int ids[NID];
     __shared__ int cmap[RESTRICT ? NID : 1];
-    const int w = blockIdx.x, q8 = ntile / NXCD, r8 = ntile % NXCD, xc = w % NXCD;
-    const MarchTile &M = tiles[xc * q8 + min(xc, r8) + w / NXCD];
+    const int xc = blockIdx.x % NXCD, seg = lists.first[xc] + (int)blockIdx.x / NXCD;
+    if (seg >= lists.first[xc + 1]) return;
+    const MarchTile &M = tiles[seg];
     const int pr = M.prob;
     const int nbx = M.nx, nby = M.ny, nbz = M.nz;
     const bool on = !(active && !active[pr]);
@@ -677,7 +679,7 @@ ohm_status launch_march_sweep(const ohm_hier *h, const T *B, long long cs, const
     const AmrLevelDev &L = h->amr[0];
     const unsigned obytes = (unsigned)((unsigned long long)L.nb * NC * sizeof(TO));   // (the callers allow 4 GiB)
     const MarchTile *tiles = (const MarchTile *)L.march;
-#define RUN(zero, co) k_march_sweep<T, TO, zero, co><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
+#define RUN(zero, co) k_march_sweep<T, TO, zero, co><<<NXCD * L.mlists.longest, MARCH_THREADS, 0, s>>>(L.mlists, tiles, L.bmap, active, \
         L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes, h->dense[1].probs, coarse, ccs)
     if (!B) RUN(true, false);
     else if (coarse) RUN(false, true);
@@ -703,7 +705,7 @@ ohm_status launch_march_stencil(const ohm_hier *h, int mode, const T *B, long lo
     const unsigned obytes = (unsigned)(cells * sizeof(T));
     const unsigned pbytes = (unsigned)((unsigned long long)L.nb * dots.ndot * sizeof(double));
     const MarchTile *tiles = (const MarchTile *)L.march;
-#define RUN(mode, d, S) k_march_stencil<T, mode, d><<<L.nmarch, MARCH_THREADS, 0, s>>>(L.nmarch, tiles, L.bmap, active, \
+#define RUN(mode, d, S) k_march_stencil<T, mode, d><<<NXCD * L.mlists.longest, MARCH_THREADS, 0, s>>>(L.mlists, tiles, L.bmap, active, \
         L.inv_h2, coef_dev.p, coef_dev.v, B, cs, S, eta, out, obytes, dots, pbytes, L.dense_map, h->dense[1].probs, ccs)
     switch (mode) {
     case MODE_APPLY:
