@@ -2,6 +2,7 @@
 // (neighbours, coarse-fine ghost blocks, parents, covered octants, refluxing
 // faces, dense multigrid levels).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
@@ -129,6 +130,7 @@ ohm_status upload(V **dptr, const std::vector<V> &h)
 struct MarchPart {
     int prob, z, c0, c1, planes;
 };
+using Box3 = std::array<int, 3>;   // blocks of a problem's box per axis
 
 // Segments of sb blocks, problem after problem, layer after layer, cut into one
 // run of equal work for each XCD (columns side by side share halos on its L2).
@@ -136,16 +138,16 @@ struct MarchPart {
 // (two groups on each of its 32 compute units): a segment of n planes costs its
 // n planes, four of halo and about as much again to start; groups that have a
 // compute unit each march about a third faster.
-static double march_plan(const ohm_hier *H, int sb, std::vector<MarchPart> out[NXCD])
+double march_cost(const std::vector<Box3> &boxes, int sb, std::vector<MarchPart> out[NXCD])
 {
     constexpr int PLACES = 64;
     std::vector<MarchPart> all;
     double total = 0.0, done = 0.0;
-    for (size_t p = 0; p < H->probs.size(); ++p) {
-        const ohm_prob_host &P = H->probs[p];
-        const int cols = ((P.bb[0] + 1) / 2) * ((P.bb[1] + 1) / 2);
-        for (int z = 0; z < P.bb[2]; z += sb) {
-            all.push_back({(int)p, z, 0, cols, NB * std::min(sb, P.bb[2] - z) + 8});
+    for (size_t p = 0; p < boxes.size(); ++p) {
+        const Box3 &bb = boxes[p];
+        const int cols = ((bb[0] + 1) / 2) * ((bb[1] + 1) / 2);
+        for (int z = 0; z < bb[2]; z += sb) {
+            all.push_back({(int)p, z, 0, cols, NB * std::min(sb, bb[2] - z) + 8});
             total += (double)cols * all.back().planes;
         }
     }
@@ -185,29 +187,46 @@ static double march_plan(const ohm_hier *H, int sb, std::vector<MarchPart> out[N
     return alone ? 0.65 * longest : longest;
 }
 
-// Tables of the marching kernels of the base level, where they are the faster
-// ones: a sweep per block takes 7.0 us (FP64; FP32 4.2) for every 512 blocks,
-// a marching sweep 1.85 us (1.2) for every plane of march_plan, so that it
+// The segments of the marching kernels for a base level of these boxes, in each
+// XCD's run, where those kernels are the faster ones (else sb = 0 and no runs):
+// a sweep per block takes 7.0 us (FP64; FP32 4.2) for every 512 blocks,
+// a marching sweep 1.85 us (1.2) for every plane of march_cost, so that it
 // takes over where the blocks are more than 140 times the planes: 128^3 (4,096
 // blocks, 24 planes: FP64 56 -> 44 us), 64 problems of 32^3 (the same counts:
 // 56 -> 46), 160 x 128 x 192 (119 -> 83), but not 112^3 (2,744 blocks, 24
 // planes: 39.5 against 40.7 us) or 96^3 (28 against 30).
-static ohm_status march_tables(ohm_hier *H)
+struct MarchPlan {
+    int sb = 0;                        // blocks of a segment along z (fewer in a column's last)
+    std::vector<MarchPart> run[NXCD];
+};
+
+MarchPlan march_plan(const std::vector<Box3> &boxes)
 {
-    AmrLevelDev &L = H->amr[0];
-    std::vector<MarchPart> plan[NXCD], best_plan[NXCD];
-    int sb = 0;
-    double best = L.nb / 140.0;
+    MarchPlan P;
+    double blocks = 0.0;
+    for (const Box3 &b : boxes) blocks += (double)b[0] * b[1] * b[2];
+    std::vector<MarchPart> run[NXCD];
+    double best = blocks / 140.0;
     if (best > 16)   // no segment costs less
         for (int s = 1; s <= MARCH_MAX_NBZ; ++s) {
-            const double c = march_plan(H, s, plan);
+            const double c = march_cost(boxes, s, run);
             if (c < best) {
                 best = c;
-                sb = s;
-                for (int x = 0; x < NXCD; ++x) best_plan[x].swap(plan[x]);
+                P.sb = s;
+                for (int x = 0; x < NXCD; ++x) P.run[x].swap(run[x]);
             }
         }
-    if (sb == 0) return OHM_OK;
+    return P;
+}
+
+// Tables of the marching kernels of the base level, where it marches.
+ohm_status march_tables(ohm_hier *H)
+{
+    AmrLevelDev &L = H->amr[0];
+    std::vector<Box3> boxes;
+    for (const ohm_prob_host &P : H->probs) boxes.push_back({P.bb[0], P.bb[1], P.bb[2]});
+    const MarchPlan plan = march_plan(boxes);
+    if (plan.sb == 0) return OHM_OK;
     std::vector<int> bmap(L.nb), march;
     for (const ohm_prob_host &P : H->probs) {
         const int off = (int)P.boff[0], nx = P.bb[0], ny = P.bb[1];
@@ -219,11 +238,11 @@ static ohm_status march_tables(ohm_hier *H)
     constexpr int INTS = sizeof(MarchTile) / sizeof(int);
     for (int x = 0; x < NXCD; ++x) {
         L.mlists.first[x] = (int)march.size() / INTS;
-        for (const MarchPart &m : best_plan[x]) {
+        for (const MarchPart &m : plan.run[x]) {
             const ohm_prob_host &P = H->probs[m.prob];
             const int nx = P.bb[0], ny = P.bb[1], nz = P.bb[2], cx = (nx + 1) / 2;
             for (int c = m.c0; c < m.c1; ++c) {
-                const MarchTile M = {m.prob, 2 * (c % cx), 2 * (c / cx), m.z, std::min(sb, nz - m.z), nx, ny, nz,
+                const MarchTile M = {m.prob, 2 * (c % cx), 2 * (c / cx), m.z, std::min(plan.sb, nz - m.z), nx, ny, nz,
                                      (int)P.boff[0], {}};
                 const int *v = (const int *)&M;
                 march.insert(march.end(), v, v + INTS);
@@ -788,6 +807,29 @@ ohm_status ohm_hier_problem_info(const ohm_hier *h, int32_t prob, int32_t level,
     if (cell_offset) *cell_offset = off;
     if (dims) memcpy(dims, d3, sizeof d3);
     return OHM_OK;
+}
+
+// The marching plan of a handle over nprob boxes of these block counts, for
+// tests (host only; not part of the API): returns the number of segments (0:
+// the base level does not march) and writes the first cap of them, one XCD's
+// after the other's, as {XCD, problem, first block x, y, z, blocks along z}.
+// kernels: 1 (FP64 sweeps) + 2 (FP32 sweeps) + 4 (operator and residual) of
+// those that march.
+int32_t ohm_march_plan(const int32_t *base_blocks, int32_t nprob, int32_t (*segments)[6], int32_t cap, int32_t *kernels)
+{
+    std::vector<Box3> boxes(nprob);
+    for (int p = 0; p < nprob; ++p) boxes[p] = {base_blocks[3 * p], base_blocks[3 * p + 1], base_blocks[3 * p + 2]};
+    const MarchPlan plan = march_plan(boxes);
+    *kernels = plan.sb > 0 ? 1 + 2 + 4 : 0;
+    int32_t n = 0;
+    for (int x = 0; x < NXCD; ++x)
+        for (const MarchPart &m : plan.run[x])
+            for (int c = m.c0; c < m.c1; ++c, ++n) {
+                const int cx = (boxes[m.prob][0] + 1) / 2, nz = boxes[m.prob][2];
+                const int32_t seg[6] = {x, m.prob, 2 * (c % cx), 2 * (c / cx), m.z, std::min(plan.sb, nz - m.z)};
+                if (n < cap) memcpy(segments[n], seg, sizeof seg);
+            }
+    return n;
 }
 
 }  // extern "C"
