@@ -82,6 +82,7 @@ struct AmrLevelDev {
     int *bmap = nullptr;
     int nmarch = 0;            // (0: the level does not march)
     int *march = nullptr;
+    bool march_sweep64 = false, march_sweep32 = false, march_resid64 = false;   // kernels that march (see hier.hip)
     MarchLists mlists = {};
     // refluxing: coarse cells of this level with faces next to covered cells
     int nrf = 0;

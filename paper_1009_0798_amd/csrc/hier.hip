@@ -126,78 +126,103 @@ ohm_status upload(V **dptr, const std::vector<V> &h)
 }
 
 // A part of one layer of a problem's column segments: columns c0 to c1 (x
-// fastest) of the segments that start at block z
+// fastest) of the segments of `planes` planes that start at block z
 struct MarchPart {
     int prob, z, c0, c1, planes;
 };
 using Box3 = std::array<int, 3>;   // blocks of a problem's box per axis
 
 // Segments of sb blocks, problem after problem, layer after layer, cut into one
-// run of equal work for each XCD (columns side by side share halos on its L2).
-// Returns the planes one after the other on the busiest of an XCD's 64 places
-// (two groups on each of its 32 compute units): a segment of n planes costs its
-// n planes, four of halo and about as much again to start; groups that have a
-// compute unit each march about a third faster.
-double march_cost(const std::vector<Box3> &boxes, int sb, std::vector<MarchPart> out[NXCD])
+// run of equal work for each XCD (columns side by side share halos on its L2):
+// a segment of n planes costs its n planes, four of halo and about as much
+// again to start.
+void march_runs(const std::vector<Box3> &boxes, int sb, std::vector<MarchPart> out[NXCD])
 {
-    constexpr int PLACES = 64;
     std::vector<MarchPart> all;
     double total = 0.0, done = 0.0;
     for (size_t p = 0; p < boxes.size(); ++p) {
         const Box3 &bb = boxes[p];
         const int cols = ((bb[0] + 1) / 2) * ((bb[1] + 1) / 2);
         for (int z = 0; z < bb[2]; z += sb) {
-            all.push_back({(int)p, z, 0, cols, NB * std::min(sb, bb[2] - z) + 8});
-            total += (double)cols * all.back().planes;
+            all.push_back({(int)p, z, 0, cols, NB * std::min(sb, bb[2] - z)});
+            total += (double)cols * (all.back().planes + 8);
         }
     }
-    double load[NXCD] = {}, longest = 0.0;
-    int count[NXCD] = {}, x = 0;
+    int x = 0;
     for (int k = 0; k < NXCD; ++k) out[k].clear();
     for (MarchPart m : all)
         while (m.c0 < m.c1) {
             // columns up to where this XCD's share of the work ends (rounded)
+            const int cost = m.planes + 8;
             const double left = total * (x + 1) / NXCD - done;
-            const int n = x == NXCD - 1 ? m.c1 - m.c0 : std::min(m.c1 - m.c0, std::max(0, (int)(left / m.planes + 0.5)));
+            const int n = x == NXCD - 1 ? m.c1 - m.c0 : std::min(m.c1 - m.c0, std::max(0, (int)(left / cost + 0.5)));
             if (n > 0) {
                 out[x].push_back({m.prob, m.z, m.c0, m.c0 + n, m.planes});
-                load[x] += (double)n * m.planes;
-                done += (double)n * m.planes;
-                count[x] += n;
+                done += (double)n * cost;
                 m.c0 += n;
             }
             if (m.c0 < m.c1) ++x;
         }
-    bool alone = true;
-    for (x = 0; x < NXCD; ++x) {
-        alone = alone && count[x] <= PLACES / 2;
-        if (count[x] > 8 * PLACES) {   // evenly spread
-            longest = std::max(longest, load[x] / PLACES);
+}
+
+// Planes one after the other on the busiest of an XCD's 64 places (two groups on
+// each of its 32 compute units), each segment `start` planes more; where every
+// group has a compute unit of its own, times what a plane then takes (alone).
+double march_planes(const std::vector<MarchPart> run[NXCD], int start, double alone)
+{
+    constexpr int PLACES = 64;
+    double longest = 0.0;
+    bool all_alone = true;
+    for (int x = 0; x < NXCD; ++x) {
+        double load = 0.0;
+        int count = 0;
+        for (const MarchPart &m : run[x]) {
+            load += (double)(m.c1 - m.c0) * (m.planes + start);
+            count += m.c1 - m.c0;
+        }
+        all_alone = all_alone && count <= PLACES / 2;
+        if (count > 8 * PLACES) {   // evenly spread
+            longest = std::max(longest, load / PLACES);
             continue;
         }
         std::vector<double> place(PLACES, 0.0);
-        for (const MarchPart &m : out[x])
+        for (const MarchPart &m : run[x])
             for (int c = m.c0; c < m.c1; ++c) {
                 std::pop_heap(place.begin(), place.end(), std::greater<double>());
-                place.back() += m.planes;
+                place.back() += m.planes + start;
                 std::push_heap(place.begin(), place.end(), std::greater<double>());
             }
         longest = std::max(longest, *std::max_element(place.begin(), place.end()));
     }
-    return alone ? 0.65 * longest : longest;
+    return all_alone ? alone * longest : longest;
 }
 
 // The segments of the marching kernels for a base level of these boxes, in each
-// XCD's run, where those kernels are the faster ones (else sb = 0 and no runs):
-// a sweep per block takes 7.0 us (FP64; FP32 4.2) for every 512 blocks,
-// a marching sweep 1.85 us (1.2) for every plane of march_cost, so that it
-// takes over where the blocks are more than 140 times the planes: 128^3 (4,096
-// blocks, 24 planes: FP64 56 -> 44 us), 64 problems of 32^3 (the same counts:
-// 56 -> 46), 160 x 128 x 192 (119 -> 83), but not 112^3 (2,744 blocks, 24
-// planes: 39.5 against 40.7 us) or 96^3 (28 against 30).
+// XCD's run (sb = 0: the level does not march), and which of the kernels are the
+// faster ones there.  Timed on 130 handles (boxes of 2,700 to 24,000 blocks,
+// batches of boxes of 2^3 to 16^3 blocks), us:
+//
+// FP64 sweep: 5.4 to 6.2 for every 512 blocks per block, 1.55 to 1.67 a plane
+// marching (with eight to start a segment), 1.1 to 1.2 where segments are alone on
+// their unit; with fields beyond the last-level cache both take a third more.  So
+// it marches from 140 blocks a plane on: 128^3 (24 planes) 47.7 -> 39.8, 160 x 128
+// x 192 110 -> 79, but not 112^3 (24 planes: 39.5 against 40.7) or 23 x 40 x 5
+// blocks (48, alone: 52.7 against 53.5).
+// FP32 sweep: 3.0 to 3.6 per block, 0.93 to 1.0 a plane marching (with the four of
+// a segment's halo), 0.8 alone, so from 171 blocks a plane: 128^3 28.4 -> 24.2, 160 x
+// 128 x 192 48 -> 39, but not 152^3 (44.1 against 45.6), 176^3 (alone: 65.8 against
+// 76.1) or 96 problems of 32^3 (37.2 against 38.8).  Beyond the last-level cache
+// 3.8 to 4.4 against 1.0 to 1.3, so 140 (192^3 103 -> 83).
+// Operator and residual: from 140 blocks a plane on, 0.65 for a plane alone.  L B
+// is 1.1 to 1.5 times as fast there in either type, the residual 1.0 to 1.25 times
+// (FP32 1.05 to 1.4); except the FP64 residual of several problems, whose calls
+// upload coefficients in between: per block a call takes 14 and 6.2 for every 1,000
+// blocks while the cache holds the fields, marching 1.37 a plane (16 problems of
+// 48^3 42.6 against 43.9, 3 of 96^3 49.3 -> 46.9).
 struct MarchPlan {
     int sb = 0;                        // blocks of a segment along z (fewer in a column's last)
     std::vector<MarchPart> run[NXCD];
+    bool sweep64 = false, sweep32 = false, resid64 = false;
 };
 
 MarchPlan march_plan(const std::vector<Box3> &boxes)
@@ -207,15 +232,22 @@ MarchPlan march_plan(const std::vector<Box3> &boxes)
     for (const Box3 &b : boxes) blocks += (double)b[0] * b[1] * b[2];
     std::vector<MarchPart> run[NXCD];
     double best = blocks / 140.0;
-    if (best > 16)   // no segment costs less
+    if (best > 16)   // too few blocks for a plan that short
         for (int s = 1; s <= MARCH_MAX_NBZ; ++s) {
-            const double c = march_cost(boxes, s, run);
+            march_runs(boxes, s, run);
+            const double c = march_planes(run, 8, 0.65);
             if (c < best) {
                 best = c;
                 P.sb = s;
                 for (int x = 0; x < NXCD; ++x) P.run[x].swap(run[x]);
             }
         }
+    if (P.sb == 0) return P;
+    // B, S, eta and the result of a sweep against the 256 MB last-level cache
+    auto cached = [&](int elem) { return 10.0 * NC * elem * blocks <= (256 << 20); };
+    P.sweep64 = march_planes(P.run, 8, 0.69) < blocks / 140.0;
+    P.sweep32 = march_planes(P.run, 4, 0.83) < blocks / (cached(4) ? 171.0 : 140.0);
+    P.resid64 = boxes.size() == 1 || !cached(8) || best < 10.0 + blocks / 222.0;
     return P;
 }
 
@@ -227,6 +259,9 @@ ohm_status march_tables(ohm_hier *H)
     for (const ohm_prob_host &P : H->probs) boxes.push_back({P.bb[0], P.bb[1], P.bb[2]});
     const MarchPlan plan = march_plan(boxes);
     if (plan.sb == 0) return OHM_OK;
+    L.march_sweep64 = plan.sweep64;
+    L.march_sweep32 = plan.sweep32;
+    L.march_resid64 = plan.resid64;
     std::vector<int> bmap(L.nb), march;
     for (const ohm_prob_host &P : H->probs) {
         const int off = (int)P.boff[0], nx = P.bb[0], ny = P.bb[1];
@@ -813,14 +848,14 @@ ohm_status ohm_hier_problem_info(const ohm_hier *h, int32_t prob, int32_t level,
 // tests (host only; not part of the API): returns the number of segments (0:
 // the base level does not march) and writes the first cap of them, one XCD's
 // after the other's, as {XCD, problem, first block x, y, z, blocks along z}.
-// kernels: 1 (FP64 sweeps) + 2 (FP32 sweeps) + 4 (operator and residual) of
-// those that march.
+// kernels: 1 (FP64 sweeps) + 2 (FP32 sweeps) + 4 (operator, and residual unless
+// FP64) + 8 (FP64 residual) of those that march.
 int32_t ohm_march_plan(const int32_t *base_blocks, int32_t nprob, int32_t (*segments)[6], int32_t cap, int32_t *kernels)
 {
     std::vector<Box3> boxes(nprob);
     for (int p = 0; p < nprob; ++p) boxes[p] = {base_blocks[3 * p], base_blocks[3 * p + 1], base_blocks[3 * p + 2]};
     const MarchPlan plan = march_plan(boxes);
-    *kernels = plan.sb > 0 ? 1 + 2 + 4 : 0;
+    *kernels = plan.sb > 0 ? plan.sweep64 + 2 * plan.sweep32 + 4 + 8 * plan.resid64 : 0;
     int32_t n = 0;
     for (int x = 0; x < NXCD; ++x)
         for (const MarchPart &m : plan.run[x])

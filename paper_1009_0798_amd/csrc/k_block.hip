@@ -709,13 +709,20 @@ k_reduce_blocks(int nprob, int nrange, const long long *__restrict__ range, cons
 // 512 blocks 8.4 / 7.6, with the mean 9.4 / 8.6, 1,232 blocks 14.2 / 14.7.
 static bool one_cell_a_thread(const AmrLevelDev &L) { return L.nb <= 4 * COMPUTE_UNITS; }
 
-// Base levels that take the marching sweeps take the marching stencil too, up
-// to the 4 GiB a component that its 32-bit offsets reach.  L B on smaller
-// levels, us, per block / marching in segments of one block: 64^3 9.8 / 10.9,
-// 96^3 18.5 / 16.6, 112^3 25.0 / 23.5 -- too little for tables of its own.
-static bool march_stencil(const AmrLevelDev &L, size_t elem)
+// Base levels with marching tables take the marching stencil (but see the FP64
+// residual in hier.hip), up to the 4 GiB a component that its 32-bit offsets
+// reach.  L B on smaller levels, us, per block / marching in segments of one
+// block: 64^3 9.8 / 10.9, 96^3 18.5 / 16.6, 112^3 25.0 / 23.5 -- too little for
+// tables of its own.
+static bool march_stencil(const AmrLevelDev &L, int mode, size_t elem)
 {
-    return L.nmarch > 0 && (unsigned long long)L.nb * NC * elem <= 0xFFFFFFFFull;
+    return L.nmarch > 0 && (mode != MODE_RESID || elem == 4 || L.march_resid64) &&
+           (unsigned long long)L.nb * NC * elem <= 0xFFFFFFFFull;
+}
+template <typename T>
+static bool march_sweep(const AmrLevelDev &L)
+{
+    return sizeof(T) == 8 ? L.march_sweep64 : L.march_sweep32;
 }
 
 template <typename T>
@@ -729,7 +736,7 @@ ohm_status launch_blk_stencil(const ohm_hier *h, int level, int mode, const T *B
     if (dots.ndot < 0 || dots.ndot > 2 || (dots.ndot > 0 && (mode != MODE_APPLY || !dots.dot_part)))
         return fail(OHM_ERR_ARG, "fused dot products need MODE_APPLY, 1 or 2 products and a partials buffer");
     const int given = (dots.ndot > 0 && dots.dot_y[0]) + (dots.ndot > 1 && dots.dot_y[1]);
-    if (level == 0 && march_stencil(L, sizeof(T)) && !cov_zero && !partials && out && mode != MODE_SMOOTH &&
+    if (level == 0 && march_stencil(L, mode, sizeof(T)) && !cov_zero && !partials && out && mode != MODE_SMOOTH &&
         (dots.ndot == 0 || (given == 1 && std::is_same<T, double>::value)))
         return launch_march_stencil<T>(h, mode, B, cs, S, eta, coef_dev, out, 0, active, s, dots);
     const bool one = one_cell_a_thread(L);
@@ -761,7 +768,7 @@ ohm_status launch_resid_restrict_blk0(const ohm_hier *h, const T *B, const T *Bg
     const AmrLevelDev &L = h->amr[0];
     if (L.nb == 0) return OHM_OK;
     if (h->min_level > -1) return fail(OHM_ERR_ARG, "no dense level below level 0");
-    if (march_stencil(L, sizeof(T)))
+    if (march_stencil(L, MODE_RESID_RESTRICT, sizeof(T)))
         return launch_march_stencil<T>(h, MODE_RESID_RESTRICT, B, cs, S, eta, coef_dev, coarse, ccs, active, s);
     const int parts = tile_parts(L.nb);
     const bool pairs = ((uintptr_t)B | (uintptr_t)eta | (uintptr_t)(cs * sizeof(T))) % (2 * sizeof(T)) == 0;
@@ -814,7 +821,7 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
                                          "aligned", level, 2 * sizeof(T));
             if (coarse && (level != 0 || h->min_level > -1))
                 return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0 and a dense level below it");
-            if (level == 0 && L.nmarch > 0 &&
+            if (level == 0 && march_sweep<T>(L) &&
                 ((uintptr_t)S % (2 * sizeof(T)) | (uintptr_t)out64 % (2 * sizeof(double))) == 0)
                 return launch_march_sweep<T, double>(h, B, cs, S, eta, coef_dev, out64, active, s, coarse, ccs);
             if (coarse)
@@ -852,7 +859,7 @@ ohm_status launch_blk_sweep(const ohm_hier *h, int level, const T *B, long long 
     }
     if (coarse && (level != 0 || h->min_level > -1 || !B))
         return fail(OHM_ERR_ARG, "a fused coarse correction needs level 0, a dense level below it and an input");
-    if (level == 0 && L.nmarch > 0 && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
+    if (level == 0 && march_sweep<T>(L) && ((uintptr_t)S | (uintptr_t)out) % (2 * sizeof(T)) == 0) {
         return launch_march_sweep<T, T>(h, B, cs, S, eta, coef_dev, out, active, s, coarse, ccs);
     } else if (coarse) {
         blk_sweep<T, 2, false, false>(h, L, B, cs, S, eta, coef_dev, out, active, s, coarse, ccs, nullptr, 0, nullptr);

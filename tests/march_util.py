@@ -3,7 +3,9 @@ import ctypes
 
 import numpy as np
 
-FP64_SWEEPS, FP32_SWEEPS, OPERATOR = 1, 2, 4
+# the operator, and the residual of FP32 fields, march wherever any kernel does
+FP64_SWEEPS, FP32_SWEEPS, OPERATOR, FP64_RESIDUAL = 1, 2, 4, 8
+ALL = 15
 
 
 def march_plan(boxes):

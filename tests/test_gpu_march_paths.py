@@ -8,7 +8,7 @@ import pytest
 import ohm_inputs as gen
 
 from gpu_util import announce, cuda
-from march_util import FP32_SWEEPS, FP64_SWEEPS, OPERATOR, march_plan
+from march_util import ALL, march_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -22,8 +22,7 @@ def test_marching_box_equals_blocks(bb, dtype):
     import paper_1009_0798_amd as ohm
     announce(f"marching box == per block {bb} {dtype}")
     kernels, segs = march_plan([bb])
-    assert kernels & (FP64_SWEEPS if dtype == "f64" else FP32_SWEEPS) and kernels & OPERATOR
-    assert len(set(segs[:, 5].tolist())) == 2
+    assert kernels == ALL and len(set(segs[:, 5].tolist())) == 2
     tdt = torch.float64 if dtype == "f64" else torch.float32
     rng = np.random.default_rng(61)
     ijk = gen.full_level(bb)
@@ -66,7 +65,7 @@ def test_marching_batch_steps(precision, post):
     announce(f"marching batch steps precision {precision} post {post}")
     boxes = ODD[:4] + [(4, 4, 4)] * 56 + ODD[4:]
     kernels, segs = march_plan(boxes)
-    assert kernels == FP64_SWEEPS + FP32_SWEEPS + OPERATOR and len(set(segs[:, 5].tolist())) == 2
+    assert kernels == ALL and len(set(segs[:, 5].tolist())) == 2
     rng = np.random.default_rng(67)
     ijk = [gen.full_level(b) for b in boxes]
     dx = 0.05

@@ -4,7 +4,7 @@ about equal work, and no plan for base levels of few blocks."""
 import numpy as np
 import pytest
 
-from march_util import FP32_SWEEPS, FP64_SWEEPS, OPERATOR, march_plan
+from march_util import ALL, FP32_SWEEPS, FP64_RESIDUAL, FP64_SWEEPS, OPERATOR, march_plan
 
 
 def _check(boxes):
@@ -46,7 +46,13 @@ def test_random_handles():
     assert marching > 20
 
 
-def test_what_marches():
-    assert march_plan([(16, 16, 16)])[0] == FP64_SWEEPS + FP32_SWEEPS + OPERATOR
-    for boxes in ([(1, 1, 1)], [(8, 8, 8)], [(12, 12, 12)], [(4, 4, 4)] * 16, [(1, 64, 64)]):
-        assert march_plan(boxes)[0] == 0
+# sizes on either side of each kernel's line; those without a kernel were timed
+# and the kernel per block is the faster one there
+@pytest.mark.parametrize("boxes,kernels", [
+    ([(1, 1, 1)], 0), ([(8, 8, 8)], 0), ([(14, 14, 14)], 0), ([(4, 4, 4)] * 32, 0), ([(1, 64, 64)], 0),
+    ([(16, 16, 16)], ALL), ([(20, 16, 24)], ALL), ([(24, 24, 24)], ALL), ([(4, 4, 4)] * 64, ALL), ([(32, 32, 21)], ALL),
+    ([(19, 19, 19)], ALL - FP32_SWEEPS), ([(22, 22, 22)], ALL - FP32_SWEEPS), ([(27, 33, 12)], ALL),
+    ([(23, 40, 5)], OPERATOR + FP64_RESIDUAL), ([(27, 33, 7)], ALL - FP32_SWEEPS),
+    ([(4, 4, 4)] * 96, FP64_SWEEPS + OPERATOR), ([(12, 12, 12)] * 3, ALL)])
+def test_what_marches(boxes, kernels):
+    assert march_plan(boxes)[0] == kernels
