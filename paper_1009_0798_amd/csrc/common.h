@@ -73,15 +73,15 @@ struct AmrLevelDev {
     int *gprob = nullptr;      // [ng] problem of the ghost block
     uint8_t *cov = nullptr;    // [nb] octants covered by level+1 blocks (bit x+2y+4z)
     long long *range = nullptr;  // [nprob][2] first block of each problem and the one behind its last
-    double *inv_h2 = nullptr;  // [nprob] 1 / h^2 of this level per problem (0 if absent)
-    double *inv_h = nullptr;   // [nprob] 1 / h
+    double *inv_h2 = nullptr;  // [nprob] 1 / h^2 of this level per problem (0 if absent; behind range)
+    double *inv_h = nullptr;   // [nprob] 1 / h (behind inv_h2)
     int *dense_map = nullptr;  // level 0 only: [nb] cell offset of the block's 4^3 coarse
                                // cells inside the problem's first dense level (-1 level)
     // level 0 only: block at each position of the problems' boxes (x fastest,
     // problem after problem) and the column segments of the marching kernels
     int *bmap = nullptr;
     int nmarch = 0;            // (0: the level does not march)
-    int *march = nullptr;
+    int *march = nullptr;      // (behind bmap)
     bool march_sweep64 = false, march_sweep32 = false, march_resid64 = false;   // kernels that march (see hier.hip)
     MarchLists mlists = {};
     // refluxing: coarse cells of this level with faces next to covered cells

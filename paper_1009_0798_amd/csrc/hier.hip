@@ -6,7 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
-#include <functional>
+#include <map>
 #include <unordered_map>
 
 #include "common.h"
@@ -185,14 +185,17 @@ double march_planes(const std::vector<MarchPart> run[NXCD], int start, double al
             longest = std::max(longest, load / PLACES);
             continue;
         }
-        std::vector<double> place(PLACES, 0.0);
+        // each segment to the place that is done first: places by their planes
+        std::map<int, int> place{{0, PLACES}};
         for (const MarchPart &m : run[x])
-            for (int c = m.c0; c < m.c1; ++c) {
-                std::pop_heap(place.begin(), place.end(), std::greater<double>());
-                place.back() += m.planes + start;
-                std::push_heap(place.begin(), place.end(), std::greater<double>());
+            for (int n = m.c1 - m.c0; n > 0;) {
+                const auto first = place.begin();
+                const int k = std::min(n, first->second);
+                place[first->first + m.planes + start] += k;
+                n -= k;
+                if ((first->second -= k) == 0) place.erase(first);
             }
-        longest = std::max(longest, *std::max_element(place.begin(), place.end()));
+        longest = std::max(longest, (double)place.rbegin()->first);
     }
     return all_alone ? alone * longest : longest;
 }
@@ -229,11 +232,15 @@ MarchPlan march_plan(const std::vector<Box3> &boxes)
 {
     MarchPlan P;
     double blocks = 0.0;
-    for (const Box3 &b : boxes) blocks += (double)b[0] * b[1] * b[2];
+    int tallest = 0;
+    for (const Box3 &b : boxes) {
+        blocks += (double)b[0] * b[1] * b[2];
+        tallest = std::max(tallest, b[2]);
+    }
     std::vector<MarchPart> run[NXCD];
     double best = blocks / 140.0;
     if (best > 16)   // too few blocks for a plan that short
-        for (int s = 1; s <= MARCH_MAX_NBZ; ++s) {
+        for (int s = 1; s <= std::min(MARCH_MAX_NBZ, tallest); ++s) {
             march_runs(boxes, s, run);
             const double c = march_planes(run, 8, 0.65);
             if (c < best) {
@@ -262,17 +269,21 @@ ohm_status march_tables(ohm_hier *H)
     L.march_sweep64 = plan.sweep64;
     L.march_sweep32 = plan.sweep32;
     L.march_resid64 = plan.resid64;
-    std::vector<int> bmap(L.nb), march;
+    constexpr int INTS = sizeof(MarchTile) / sizeof(int);
+    // the block at each position of the boxes, then (a whole number of them
+    // behind the start) the segments
+    const int at = (L.nb + INTS - 1) / INTS * INTS;
+    std::vector<int> march(at);
     for (const ohm_prob_host &P : H->probs) {
         const int off = (int)P.boff[0], nx = P.bb[0], ny = P.bb[1];
         for (int b = 0; b < P.nb[0]; ++b) {
             const int32_t *q = &P.blocks[0][3 * b];
-            bmap[off + q[0] + nx * (q[1] + ny * q[2])] = off + b;
+            march[off + q[0] + nx * (q[1] + ny * q[2])] = off + b;
         }
     }
-    constexpr int INTS = sizeof(MarchTile) / sizeof(int);
+    auto segments = [&] { return ((int)march.size() - at) / INTS; };
     for (int x = 0; x < NXCD; ++x) {
-        L.mlists.first[x] = (int)march.size() / INTS;
+        L.mlists.first[x] = segments();
         for (const MarchPart &m : plan.run[x]) {
             const ohm_prob_host &P = H->probs[m.prob];
             const int nx = P.bb[0], ny = P.bb[1], nz = P.bb[2], cx = (nx + 1) / 2;
@@ -283,11 +294,12 @@ ohm_status march_tables(ohm_hier *H)
                 march.insert(march.end(), v, v + INTS);
             }
         }
-        L.mlists.longest = std::max(L.mlists.longest, (int)march.size() / INTS - L.mlists.first[x]);
+        L.mlists.longest = std::max(L.mlists.longest, segments() - L.mlists.first[x]);
     }
-    L.nmarch = L.mlists.first[NXCD] = (int)march.size() / INTS;
-    OHM_TRY(upload(&L.bmap, bmap));
-    return upload(&L.march, march);
+    OHM_TRY(upload(&L.bmap, march));
+    L.march = L.bmap + at;
+    L.nmarch = L.mlists.first[NXCD] = segments();
+    return OHM_OK;
 }
 
 }  // namespace
@@ -496,15 +508,22 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
         H->ng_host[l] = ng;
         L.complete27 = std::all_of(nbr.begin(), nbr.end(), [](int v) { return v >= 0; });
         L.fused = std::all_of(nbr.begin(), nbr.end(), [](int v) { return v != NBR_NONE; });
-        std::vector<double> ih2(nprob, 0.0), ih(nprob, 0.0);
+        // per problem: first block and the one behind its last, then 1 / h^2
+        // and 1 / h, in one table (an allocation and an upload are 10 us)
+        std::vector<long long> range(4 * (size_t)nprob, 0);
+        double *const ih2 = (double *)(range.data() + 2 * (size_t)nprob), *const ih = ih2 + nprob;
         for (int p = 0; p < nprob; ++p)
             if (l < H->probs[p].nlevels) {
-                double hh = H->probs[p].dx0 / (double)(1 << l);
+                const ohm_prob_host &P = H->probs[p];
+                const double hh = P.dx0 / (double)(1 << l);
+                range[2 * p] = P.boff[l];
+                range[2 * p + 1] = P.boff[l] + P.nb[l];
                 ih[p] = 1.0 / hh;
                 ih2[p] = 1.0 / (hh * hh);
             }
-        OHM_TRY(upload(&L.inv_h2, ih2));
-        OHM_TRY(upload(&L.inv_h, ih));
+        OHM_TRY(upload(&L.range, range));
+        L.inv_h2 = (double *)(L.range + 2 * (size_t)nprob);
+        L.inv_h = L.inv_h2 + nprob;
         OHM_TRY(upload(&L.nbr, nbr));
         OHM_TRY(upload(&L.prob, prob));
         OHM_TRY(upload(&L.ijk, ijk));
@@ -516,13 +535,6 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
             OHM_TRY(upload(&L.goctant, goctant));
             OHM_TRY(upload(&L.gprob, gprob));
         }
-        std::vector<long long> range;
-        for (const ohm_prob_host &P : H->probs) {
-            const bool has = l < P.nlevels;
-            range.push_back(has ? P.boff[l] : 0);
-            range.push_back(has ? P.boff[l] + P.nb[l] : 0);
-        }
-        OHM_TRY(upload(&L.range, range));
         if (l == 0) {
             OHM_TRY(upload(&L.dense_map, dmap));
             OHM_TRY(march_tables(H));
@@ -614,6 +626,9 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
         // face list and workgroup partition: whole entries per workgroup, at
         // most RF_WG_FACES faces
         std::vector<int> rff, rfs(nrf), rfw;
+        int faces = 0;
+        for (int e = 0; e < nrf; ++e) faces += __builtin_popcount(rf[RF_INTS * e + 2]);
+        rff.reserve(faces * (sizeof(RfFace) / sizeof(int)));
         int w_e0 = 0, w_f0 = 0, nface = 0;
         for (int e = 0; e <= nrf; ++e) {
             const int nf = e < nrf ? __builtin_popcount(rf[RF_INTS * e + 2]) : 0;
@@ -726,7 +741,7 @@ static void free_all(ohm_hier *H)
     for (int l = 0; l < OHM_MAX_LEVELS; ++l) {
         AmrLevelDev &L = H->amr[l];
         void *ptrs[] = {L.nbr, L.prob, L.ijk, L.parent, L.octant, L.gparent, L.goctant, L.gprob,
-                        L.cov, L.dense_map, L.bmap, L.march, L.rf, L.rff, L.rfs, L.rfw, L.range, L.inv_h2, L.inv_h};
+                        L.cov, L.dense_map, L.bmap, L.rf, L.rff, L.rfs, L.rfw, L.range};
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
     }
