@@ -177,7 +177,6 @@ struct ohm_hier {
     // host copies read by the step code (cn.hip)
     std::vector<std::vector<int>> blk_prob_host;  // per level
     // scratch for per-problem scalars uploaded by the primitives
-    double *d_scal = nullptr;        // [4 * nprob]
     double *d_part = nullptr;        // reduction partials
     size_t part_cap = 0;
     size_t table_bytes = 0;          // device bytes of the tables and scratch above

@@ -722,13 +722,12 @@ static ohm_status build(ohm_hier *H, const ohm_problem_desc *probs, int nprob)
     }
     // ---- scratch ---------------------------------------------------------------
     std::lock_guard<std::mutex> lock(capture_mutex());
-    OHM_HIP(hipMalloc((void **)&H->d_scal, sizeof(double) * 4 * nprob));
     OHM_HIP(hipHostMalloc((void **)&H->h_dots, sizeof(double) * (8 + 2 * ITER_SLOTS + 12) * nprob, hipHostMallocDefault));
     size_t maxnb = 1;
     for (int l = 0; l < H->nlev; ++l) maxnb = std::max(maxnb, (size_t)H->nb_host[l]);
     H->part_cap = maxnb * 8 + 64;
     OHM_HIP(hipMalloc((void **)&H->d_part, sizeof(double) * H->part_cap));
-    H->table_bytes = g_up_bytes + sizeof(double) * (4 * (size_t)nprob + H->part_cap);
+    H->table_bytes = g_up_bytes + sizeof(double) * H->part_cap;
     H->cinv_off.assign(nprob, -1);
     H->cinv_n.assign(nprob, 0);
     H->cinv_lamdt.assign(nprob, -1.0);
@@ -751,7 +750,7 @@ static void free_all(ohm_hier *H)
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
     }
-    void *ptrs[] = {H->d_scal, H->d_part, H->d_coarse_inv, H->d_ring, H->d_coarse_eta, H->d_coarse_flags};
+    void *ptrs[] = {H->d_part, H->d_coarse_inv, H->d_ring, H->d_coarse_eta, H->d_coarse_flags};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (H->h_dots) (void)hipHostFree(H->h_dots);
