@@ -176,7 +176,6 @@ struct ohm_hier {
     long long dense_cells[16] = {0};
     // host copies read by the step code (cn.hip)
     std::vector<std::vector<int>> blk_prob_host;  // per level
-    // scratch for per-problem scalars uploaded by the primitives
     double *d_part = nullptr;        // reduction partials
     size_t part_cap = 0;
     size_t table_bytes = 0;          // device bytes of the tables and scratch above
@@ -361,8 +360,6 @@ template <typename T>
 ohm_status launch_dense_smooth(const ohm_hier *h, int level, T *B, T *tmp, const T *S, const T *eta,
                                Coef coef_dev, int nsweeps, bool all, const int *active, hipStream_t s,
                                int flags = 0, const T *coarse = nullptr, T **last = nullptr, int ordering = 0);
-// dense level -> next coarser: coarse = restriction of S - L B; res is scratch
-// for handles where some continuing problem is not made of 8^3 tiles
 // from a zero guess: one red-black sweep into e, its residual and restriction
 // (levels for which dense_down_fuses)
 template <typename T>
@@ -370,6 +367,8 @@ bool dense_down_fuses(const ohm_hier *h, int level);
 template <typename T>
 ohm_status launch_dense_down(const ohm_hier *h, int level, T *e, const T *S, const T *eta, Coef coef_dev,
                              T *coarse, const int *active, hipStream_t s);
+// dense level -> next coarser: coarse = restriction of S - L B; res is scratch
+// for handles where some continuing problem is not made of 8^3 tiles
 template <typename T>
 ohm_status launch_dense_resid_restrict(const ohm_hier *h, int level, const T *B, const T *S, const T *eta,
                                        Coef coef_dev, T *res, T *coarse, const int *active, hipStream_t s);

@@ -705,8 +705,10 @@ k_reduce_blocks(int nprob, int nrange, const long long *__restrict__ range, cons
 // ---------------------------------------------------------------------------
 // The block stencil takes a thread per cell (8 instead of 20 tile loads in front
 // of one instead of two applications) while all groups of 512 threads are
-// resident at once, four to a compute unit.  FP64, us, two cells a thread / one:
-// 512 blocks 8.4 / 7.6, with the mean 9.4 / 8.6, 1,232 blocks 14.2 / 14.7.
+// resident at once, four to a compute unit.  us, two cells a thread / one: FP64
+// 512 blocks 8.4 / 7.6, with the mean 9.4 / 8.6, 1,024 blocks 12.8 / 11.9 (residual
+// 13.4 / 13.4), 1,232 blocks 14.2 / 14.7; FP32 512 blocks 6.2 / 5.9 (residual 6.5 /
+// 6.0), 1,024 9.1 / 8.2 (9.4 / 8.4).
 static bool one_cell_a_thread(const AmrLevelDev &L) { return L.nb <= 4 * COMPUTE_UNITS; }
 
 // Base levels with marching tables take the marching stencil (but see the FP64

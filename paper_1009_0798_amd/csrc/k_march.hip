@@ -15,8 +15,8 @@
 // segment) and asks the L2 for 2.5 instead of 6.7 lines per line, and its
 // loads run two planes ahead instead of in front of each block's updates.
 // Measured per launch on one box, us, sweep per block -> this kernel: FP64
-// 128^3 56 -> 44, 160x128x192 119 -> 83, 256^3 515 -> 324 (2.6 -> 4.1 TB/s of
-// algorithmic bytes); FP32 35 -> 29, 56 -> 42, 287 -> 193.
+// 128^3 47.6 -> 39.2, 160x128x192 110 -> 79, 256^3 505 -> 307 (2.7 -> 4.4 TB/s of
+// algorithmic bytes; other boxes up to 344); FP32 28.3 -> 24.4, 49 -> 39, 284 -> 189.
 #include <type_traits>
 
 #include "march.h"

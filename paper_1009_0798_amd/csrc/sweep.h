@@ -80,11 +80,12 @@ using WholeTile = Tile<8, 8>;
 // unit each.  A group alone on its unit waits out its chain (neighbour list,
 // tile, red cells, black cells, store), of which the updates take longer the
 // more cells it has; with every unit taken the parts' larger share of halo
-// cells costs more than that gives.  FP64 steps with the base level's tiles
-// whole, halved and quartered: 32^3 (64 tiles) 1189, 1147 and 1127 us, 40^3
-// (125) 1332, 1294 and 1330, 48^3 (216) 1977, 2007 and 2119; with the dense
-// levels of a 64^3 box (64, 8 and 1 tiles): 2240, 2119 and 2020.  A quarter's
-// sweep at 32^3 takes 4.9 us where the whole tile's took 6.1.
+// cells costs more than that gives.  Steps of six iterations (2 + 5 sweeps, 1
+// below the base) with the base level's tiles whole, halved and quartered, us:
+// FP64 32^3 (64 tiles) 1184, 1130 and 1099, 40^3 (125) 1295, 1256 and 1290, 48^3
+// (216) 1481, 1566 and 1798; mixed 1036, 1025 and 1007, 1134, 1124 and 1158, 1308,
+// 1341 and 1405.  With the dense levels of a 64^3 box (64, 8 and 1 tiles) so: FP64
+// 2073, 1924 and 1850, mixed 1627, 1621 and 1579.
 constexpr int COMPUTE_UNITS = 256;
 inline int tile_parts(int tiles) { return 4 * tiles <= COMPUTE_UNITS ? 4 : 2 * tiles <= COMPUTE_UNITS ? 2 : 1; }
 
