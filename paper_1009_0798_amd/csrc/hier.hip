@@ -207,10 +207,11 @@ double march_planes(const std::vector<MarchPart> run[NXCD], int start, double al
 //
 // FP64 sweep: 5.4 to 6.2 for every 512 blocks per block, 1.55 to 1.67 a plane
 // marching (with eight to start a segment), 1.1 to 1.2 where segments are alone on
-// their unit; with fields beyond the last-level cache both take a third more.  So
-// it marches from 140 blocks a plane on: 128^3 (24 planes) 47.7 -> 39.8, 160 x 128
-// x 192 110 -> 79, but not 112^3 (24 planes: 39.5 against 40.7) or 23 x 40 x 5
-// blocks (48, alone: 52.7 against 53.5).
+// their unit, so from 140 blocks a plane on: 128^3 (24 planes) 47.7 -> 39.8, but not
+// 112^3 (24 planes: 39.5 against 40.7) or 23 x 40 x 5 blocks (48, alone: 52.7 against
+// 53.5).  With fields beyond the last-level cache 7.2 to 7.9 against 1.6 to 2.2,
+// alone still 1.2: wherever the operator marches (160 x 128 x 192 110 -> 79, 168^3,
+// alone, 145 -> 112).
 // FP32 sweep: 3.0 to 3.6 per block, 0.93 to 1.0 a plane marching (with the four of
 // a segment's halo), 0.8 alone, so from 171 blocks a plane: 128^3 28.4 -> 24.2, 160 x
 // 128 x 192 48 -> 39, but not 152^3 (44.1 against 45.6), 176^3 (alone: 65.8 against
@@ -252,7 +253,7 @@ MarchPlan march_plan(const std::vector<Box3> &boxes)
     if (P.sb == 0) return P;
     // B, S, eta and the result of a sweep against the 256 MB last-level cache
     auto cached = [&](int elem) { return 10.0 * NC * elem * blocks <= (256 << 20); };
-    P.sweep64 = march_planes(P.run, 8, 0.69) < blocks / 140.0;
+    P.sweep64 = !cached(8) || march_planes(P.run, 8, 0.69) < blocks / 140.0;
     P.sweep32 = march_planes(P.run, 4, 0.83) < blocks / (cached(4) ? 171.0 : 140.0);
     P.resid64 = boxes.size() == 1 || !cached(8) || best < 10.0 + blocks / 222.0;
     return P;

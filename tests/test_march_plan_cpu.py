@@ -51,7 +51,8 @@ def test_random_handles():
 @pytest.mark.parametrize("boxes,kernels", [
     ([(1, 1, 1)], 0), ([(8, 8, 8)], 0), ([(14, 14, 14)], 0), ([(4, 4, 4)] * 32, 0), ([(1, 64, 64)], 0),
     ([(16, 16, 16)], ALL), ([(20, 16, 24)], ALL), ([(24, 24, 24)], ALL), ([(4, 4, 4)] * 64, ALL), ([(32, 32, 21)], ALL),
-    ([(19, 19, 19)], ALL - FP32_SWEEPS), ([(22, 22, 22)], ALL - FP32_SWEEPS), ([(27, 33, 12)], ALL),
+    ([(19, 19, 19)], ALL - FP32_SWEEPS), ([(22, 22, 22)], ALL - FP32_SWEEPS),
+    ([(21, 21, 21)], ALL - FP32_SWEEPS), ([(27, 33, 12)], ALL),
     ([(23, 40, 5)], OPERATOR + FP64_RESIDUAL), ([(27, 33, 7)], ALL - FP32_SWEEPS),
     ([(4, 4, 4)] * 96, FP64_SWEEPS + OPERATOR), ([(12, 12, 12)] * 3, ALL)])
 def test_what_marches(boxes, kernels):
