@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <unordered_map>
 
@@ -200,6 +201,29 @@ double march_planes(const std::vector<MarchPart> run[NXCD], int start, double al
     return all_alone ? alone * longest : longest;
 }
 
+// The same for the busiest of an XCD's 32 units as it works through its segments:
+// two at a time, each at half the unit's rate, a last one alone at 0.83 of the time
+// that two take.  (136 to 159 segments of two blocks an XCD, five on a unit: FP32
+// sweep 48 to 51 us, where two and three rounds of 64 take 45 and 60.)
+double march_unit_planes(const std::vector<MarchPart> run[NXCD], int start)
+{
+    constexpr int UNITS = 32;
+    double longest = 0.0;
+    for (int x = 0; x < NXCD; ++x) {
+        std::vector<std::pair<int, int>> unit(UNITS);   // planes of all its segments and of the longest
+        const auto later = std::greater<std::pair<int, int>>();
+        for (const MarchPart &m : run[x])
+            for (int c = m.c0; c < m.c1; ++c) {
+                std::pop_heap(unit.begin(), unit.end(), later);
+                unit.back().first += m.planes + start;
+                unit.back().second = std::max(unit.back().second, m.planes + start);
+                std::push_heap(unit.begin(), unit.end(), later);
+            }
+        for (const auto &u : unit) longest = std::max({longest, 0.5 * u.first, 0.83 * u.second});
+    }
+    return longest;
+}
+
 // The segments of the marching kernels for a base level of these boxes, in each
 // XCD's run (sb = 0: the level does not march), and which of the kernels are the
 // faster ones there.  Timed on 130 handles (boxes of 2,700 to 24,000 blocks,
@@ -212,11 +236,10 @@ double march_planes(const std::vector<MarchPart> run[NXCD], int start, double al
 // 53.5).  With fields beyond the last-level cache 7.2 to 7.9 against 1.6 to 2.2,
 // alone still 1.2: wherever the operator marches (160 x 128 x 192 110 -> 79, 168^3,
 // alone, 145 -> 112).
-// FP32 sweep: 3.0 to 3.6 per block, 0.93 to 1.0 a plane marching (with the four of
-// a segment's halo), 0.8 alone, so from 171 blocks a plane: 128^3 28.4 -> 24.2, 160 x
-// 128 x 192 48 -> 39, but not 152^3 (44.1 against 45.6), 176^3 (alone: 65.8 against
-// 76.1) or 96 problems of 32^3 (37.2 against 38.8).  Beyond the last-level cache
-// 3.8 to 4.4 against 1.0 to 1.3, so 140 (192^3 103 -> 83).
+// FP32 sweep: 3.0 to 3.6 per block, 0.93 to 1.0 a plane of a unit marching (with five
+// to start a segment), so from 161 blocks a plane: 128^3 28.4 -> 24.2, 160 x 128 x 192
+// 48 -> 39, but not 152^3 (44.1 against 45.6) or 176^3 (alone: 65.8 against 76.1).
+// Beyond the last-level cache 3.8 to 4.4 against 1.0 to 1.3, so 140 (192^3 103 -> 83).
 // Operator and residual: from 140 blocks a plane on, 0.65 for a plane alone.  L B
 // is 1.1 to 1.5 times as fast there in either type, the residual 1.0 to 1.25 times
 // (FP32 1.05 to 1.4); except the FP64 residual of several problems, whose calls
@@ -254,7 +277,7 @@ MarchPlan march_plan(const std::vector<Box3> &boxes)
     // B, S, eta and the result of a sweep against the 256 MB last-level cache
     auto cached = [&](int elem) { return 10.0 * NC * elem * blocks <= (256 << 20); };
     P.sweep64 = !cached(8) || march_planes(P.run, 8, 0.69) < blocks / 140.0;
-    P.sweep32 = march_planes(P.run, 4, 0.83) < blocks / (cached(4) ? 171.0 : 140.0);
+    P.sweep32 = march_unit_planes(P.run, 5) < blocks / (cached(4) ? 161.0 : 140.0);
     P.resid64 = boxes.size() == 1 || !cached(8) || best < 10.0 + blocks / 222.0;
     return P;
 }

@@ -54,6 +54,7 @@ def test_random_handles():
     ([(19, 19, 19)], ALL - FP32_SWEEPS), ([(22, 22, 22)], ALL - FP32_SWEEPS),
     ([(21, 21, 21)], ALL - FP32_SWEEPS), ([(27, 33, 12)], ALL),
     ([(23, 40, 5)], OPERATOR + FP64_RESIDUAL), ([(27, 33, 7)], ALL - FP32_SWEEPS),
-    ([(4, 4, 4)] * 96, FP64_SWEEPS + OPERATOR), ([(12, 12, 12)] * 3, ALL)])
+    ([(4, 4, 4)] * 96, ALL - FP64_RESIDUAL), ([(25, 18, 15)], ALL - FP32_SWEEPS), ([(4, 4, 4)] * 159, ALL),
+    ([(12, 12, 12)] * 3, ALL)])
 def test_what_marches(boxes, kernels):
     assert march_plan(boxes)[0] == kernels
